@@ -13,11 +13,11 @@
 // inverse transform is applied once, in the spectral multiplies):
 //   P1 z r2c of S densities            k_zfwd
 //   P2 y forward                       k_ystep<FWD>
-//   P3 x forward, weights, x inverse   k_xfwd      (S -> 8 stored fields)
-//   P4 y inverse                       k_ystep<INV> (8 -> 10: vector y components)
-//   P5 z c2r, FMT derivatives, z r2c   k_zderiv    (10 -> 10, FP64 pointwise)
-//   P6 y forward                       k_ystep<FWD> (10 -> 8: khat . F partial sums)
-//   P7 x forward, back-convolution, pair kernels, x inverse   k_xback (8 + S -> S)
+//   P3 x forward, weights, x inverse   k_xfwd      (S -> 7 stored fields)
+//   P4 y inverse                       k_ystep<INV> (7 -> 9: vector y components)
+//   P5 z c2r, FMT derivatives, z r2c   k_zderiv    (9 -> 9, FP64 pointwise)
+//   P6 y forward                       k_ystep<FWD> (9 -> 7: i s . F partial sums)
+//   P7 x forward, back-convolution, pair kernels, x inverse   k_xback (7 + S -> S)
 // (the vector densities carry one component per axis pass; see the
 // field-slot layout in pnp_kernels.hpp)
 //   P8 y inverse                       k_ystep<INV>
@@ -325,8 +325,7 @@ __device__ inline double d_j1x(double x) {
   return d_j1x(x, sn, cs);
 }
 
-// hs table [m][S][4] = (j0(kR), 4 pi R^3 j1(kR)/(kR), 4 pi R^2 j1(kR), 0)
-// (FP64 path only); pair table [m][j][i] (row length Sp) = G_ij, the combined
+// hs table [m][S][2] = (j0(kR), 4 pi R^3 j1(kR)/(kR)) (FP64 path only); pair table [m][j][i] (row length Sp) = G_ij, the combined
 // pair kernel, zero for i >= S.  One thread per (m, table entry): blockIdx.y
 // picks the entry (pair-table entries first, then the hs species), blockIdx.z
 // the instance.  G is symmetric, so the thread of entry (j, i) with i <= j
@@ -377,13 +376,8 @@ __global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ ta
     sincos(x, &sn, &cs);
     const double j1x = d_j1x(x, sn, cs);
     const double j0 = (x == 0.0) ? 1.0 : sn / x;
-    v4<T> w;
-    w.x = (T)j0;
-    w.y = (T)(4.0 * kPi * R * R * R * j1x);
-    w.z = (T)(4.0 * kPi * R * R * x * j1x);
-    w.w = (T)0;
-    const Buf hs = make_buf(a.hs_tab, (uint64_t)a.M * a.S * 4 * sizeof(T));
-    hs.template st<v4<T>>(w, (uint32_t)((m * a.S + i) * sizeof(v4<T>)));
+    const Buf hs = make_buf(a.hs_tab, (uint64_t)a.M * a.S * sizeof(cx<T>));
+    hs.template st<cx<T>>(mk<T>((T)j0, (T)(4.0 * kPi * R * R * R * j1x)), (uint32_t)((m * a.S + i) * sizeof(cx<T>)));
   }
 }
 
@@ -407,16 +401,15 @@ __device__ __forceinline__ uint32_t spec_row(uint32_t row_id) {
 }
 template <typename T, int N> constexpr uint32_t spec_nyq() { return (uint32_t)(N * spec_plane(N, sizeof(T))); }
 
-// v holds C[k] at k = t + TZ m; writes X[k] (k < H) and X[H] of one row.
-// zmul: store i s_z X instead (s_z = k below the Nyquist index, 0 at it).
-template <typename T, int N, int TZ, int EZ, typename BF>
-__device__ __forceinline__ void r2c_post(cx<T>* v, int t, const cx<T>* twN, cx<T>* row, const BF& f,
-                                         uint32_t soff, uint32_t row_id, bool zmul = false) {
+// The r2c post-step: v holds C[k] at k = t + TZ m and receives X[k] (k < H);
+// nyq receives X[H] in lane t = 0.  row: the row's LDS buffer.
+template <typename T, int N, int TZ, int EZ>
+__device__ __forceinline__ void r2c_post_w(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twN, cx<T>* row) {
   constexpr int H = N / 2;
-  constexpr uint32_t cs = sizeof(cx<T>);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) row[t + TZ * m] = v[m];
   lds_sync<row_in_wave<TZ>()>();
+  nyq = mk<T>(v[0].x - v[0].y, (T)0);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
     const int k = t + TZ * m;
@@ -424,13 +417,35 @@ __device__ __forceinline__ void r2c_post(cx<T>* v, int t, const cx<T>* twN, cx<T
     const cx<T> cm = cconj<T>(row[k == 0 ? 0 : H - k]);
     const cx<T> e = mk<T>((T)0.5 * (c.x + cm.x), (T)0.5 * (c.y + cm.y));
     const cx<T> d = mk<T>((T)0.5 * (c.x - cm.x), (T)0.5 * (c.y - cm.y));  // O = d / i
-    cx<T> x = cadd<T>(e, cmul<T>(twN[k], cmulmi<T>(d)));
-    if (zmul) x = cscale<T>(cmuli<T>(x), (T)k);
-    f.template st<cx<T>>(x, (spec_row<T, N>(row_id) + k) * cs, soff);
-    if (k == 0) f.template st<cx<T>>(zmul ? mk<T>((T)0, (T)0) : mk<T>(c.x - c.y, (T)0),
-                            (spec_nyq<T, N>() + row_id) * cs, soff);
+    v[m] = cadd<T>(e, cmul<T>(twN[k], cmulmi<T>(d)));
   }
   lds_sync<row_in_wave<TZ>()>();
+}
+
+// X[k] <- i s_z zs X[k] (s_z = k below the Nyquist index, 0 at it)
+template <typename T, int TZ, int EZ>
+__device__ __forceinline__ void mul_isz(cx<T>* v, cx<T>& nyq, int t, T zs) {
+#pragma unroll
+  for (int m = 0; m < EZ; ++m) v[m] = cscale<T>(cmuli<T>(v[m]), zs * (T)(t + TZ * m));
+  nyq = mk<T>((T)0, (T)0);
+}
+
+// store X[k] of one row and, from lane t = 0, its Nyquist value
+template <typename T, int N, int TZ, int EZ, typename BF>
+__device__ __forceinline__ void r2c_store(const cx<T>* v, cx<T> nyq, int t, const BF& f, uint32_t soff,
+                                          uint32_t row_id) {
+  constexpr uint32_t cs = sizeof(cx<T>);
+#pragma unroll
+  for (int m = 0; m < EZ; ++m) f.template st<cx<T>>(v[m], (spec_row<T, N>(row_id) + t + TZ * m) * cs, soff);
+  if (t == 0) f.template st<cx<T>>(nyq, (spec_nyq<T, N>() + row_id) * cs, soff);
+}
+
+template <typename T, int N, int TZ, int EZ, typename BF>
+__device__ __forceinline__ void r2c_post(cx<T>* v, int t, const cx<T>* twN, cx<T>* row, const BF& f,
+                                         uint32_t soff, uint32_t row_id) {
+  cx<T> nyq;
+  r2c_post_w<T, N, TZ, EZ>(v, nyq, t, twN, row);
+  r2c_store<T, N, TZ, EZ>(v, nyq, t, f, soff, row_id);
 }
 
 // raw loads for the c2r pre-step of one row: X[k] and X[H-k] (X[H] from the
@@ -495,10 +510,10 @@ __device__ __forceinline__ void c2r_mirror(cx<T>* xm, const cx<T>* xk, cx<T> xn,
 // X[H] build C[k] = (X[k] + conj X[H-k]) + i (X[k] - conj X[H-k]) W^-k; the
 // unnormalised length-H inverse of C is then n (a[2j] + i a[2j+1]).
 // xk0, xm0: X[k] and X[H - k] (X[H] for k = 0) at the lane's elements.
-// zmul: transform i s_z X instead of X (s_z = k below the Nyquist index, 0 at it)
+// zmul: transform i s_z zs X instead of X (s_z = k below the Nyquist index, 0 at it)
 template <typename T, int N, int TZ, int EZ>
 __device__ __forceinline__ void c2r_combine(cx<T>* v, const cx<T>* xk0, const cx<T>* xm0, int t,
-                                            const cx<T>* twN, bool zmul = false) {
+                                            const cx<T>* twN, bool zmul = false, T zs = (T)1) {
   constexpr int H = N / 2;
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
@@ -506,8 +521,8 @@ __device__ __forceinline__ void c2r_combine(cx<T>* v, const cx<T>* xk0, const cx
     cx<T> xk = xk0[m], xm = xm0[m];
     if (k == 0) { xk.y = (T)0; xm.y = (T)0; }
     if (zmul) {
-      xk = cscale<T>(cmuli<T>(xk), (T)k);
-      xm = k == 0 ? mk<T>((T)0, (T)0) : cscale<T>(cmuli<T>(xm), (T)(H - k));
+      xk = cscale<T>(cmuli<T>(xk), zs * (T)k);
+      xm = k == 0 ? mk<T>((T)0, (T)0) : cscale<T>(cmuli<T>(xm), zs * (T)(H - k));
     }
     const cx<T> cm = cconj<T>(xm);
     const cx<T> s = cadd<T>(xk, cm);
@@ -610,7 +625,10 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   uint32_t bad = 0u, badidx = 0xffffffffu;
   for (int s = 0; s < a.nreal; ++s) {
     cx<T> v[EZ], xk[EZ], xm[EZ];
-    const uint32_t si = (uint32_t)(s * a.fstride * sizeof(cx<T>));
+    // weighted-density output: the z components of the vector densities are
+    // i s_z [6] and i s_z k0 [3] (see the field-slot layout)
+    const bool zmul = (a.zmul_mask >> s) & 1u, grad = zmul && s == kFieldZ2;
+    const uint32_t si = (uint32_t)((grad ? kSlotN3 : s) * a.fstride * sizeof(cx<T>));
     if constexpr (mirror_lds<N>()) {
       cx<T> xn;
       c2r_load_k<T, N, TZ, EZ, false>(xk, xn, t, src, si, row);
@@ -618,7 +636,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     } else {
       c2r_load<T, N, TZ, EZ>(xk, xm, t, src, si, row);  // the policy is the default one here
     }
-    c2r_combine<T, N, TZ, EZ>(v, xk, xm, t, twN, (a.zmul_mask >> s) & 1u);
+    c2r_combine<T, N, TZ, EZ>(v, xk, xm, t, twN, zmul, grad ? (T)a.kscale : (T)1);
     fft_pencil<T, H, EZ, false>(v, t, twH, lp);
     const uint32_t so = (uint32_t)s * n3b;
     if (a.final_mode) {
@@ -650,8 +668,9 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   if (bad) raise_status(a.status, bad, badidx);
 }
 
-// P5: z c2r of the 10 weighted densities, the FMT derivatives (Sec. 2.3.1),
-// z r2c of the 10 derivative fields; in place on specB.  ln(1 - n3) and the
+// P5: z c2r of the 10 weighted densities (from nine spectra), the FMT
+// derivatives (Sec. 2.3.1), z r2c of the 10 derivative fields (into nine
+// spectra); in place on specB.  ln(1 - n3) and the
 // powers of 1 / (1 - n3) (and the White Bear coefficient) are evaluated in
 // float64; their products with the weighted densities in the FFT type (in
 // float64 for free-energy calls).
@@ -684,7 +703,7 @@ template <typename T, int N, int EZ = default_ezd<T, N>(), int V = 0> struct Geo
 // instructions per element instead of fourteen and ten.
 template <typename T, int N, int TZ, int EZ>
 __device__ __forceinline__ void c2r_combine_p(cx<T>* v, const cx<T>* xk0, const cx<T>* xm0, int t,
-                                              const cx<T>* twp, bool zmul = false) {
+                                              const cx<T>* twp, bool zmul = false, T zs = (T)1) {
   constexpr int H = N / 2;
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
@@ -692,8 +711,8 @@ __device__ __forceinline__ void c2r_combine_p(cx<T>* v, const cx<T>* xk0, const 
     cx<T> xk = xk0[m], xm = xm0[m];
     if (k == 0) { xk.y = (T)0; xm.y = (T)0; }
     if (zmul) {
-      xk = cscale<T>(cmuli<T>(xk), (T)k);
-      xm = k == 0 ? mk<T>((T)0, (T)0) : cscale<T>(cmuli<T>(xm), (T)(H - k));
+      xk = cscale<T>(cmuli<T>(xk), zs * (T)k);
+      xm = k == 0 ? mk<T>((T)0, (T)0) : cscale<T>(cmuli<T>(xm), zs * (T)(H - k));
     }
     const T cmx = xm.x, cmy = -xm.y;  // cm = conj(xm)
     const T dx = xk.x - cmx, dy = xk.y - cmy;
@@ -705,14 +724,13 @@ __device__ __forceinline__ void c2r_combine_p(cx<T>* v, const cx<T>* xk0, const 
   }
 }
 
-template <typename T, int N, int TZ, int EZ, typename BF>
-__device__ __forceinline__ void r2c_post_p(cx<T>* v, int t, const cx<T>* twp, cx<T>* row, const BF& f,
-                                           uint32_t soff, uint32_t row_id, bool zmul = false) {
+template <typename T, int N, int TZ, int EZ>
+__device__ __forceinline__ void r2c_post_p(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twp, cx<T>* row) {
   constexpr int H = N / 2;
-  constexpr uint32_t cs = sizeof(cx<T>);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) row[t + TZ * m] = v[m];
   lds_sync<row_in_wave<TZ>()>();
+  nyq = mk<T>(v[0].x - v[0].y, (T)0);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
     const int k = t + TZ * m;
@@ -721,11 +739,7 @@ __device__ __forceinline__ void r2c_post_p(cx<T>* v, int t, const cx<T>* twp, cx
     const T cmx = r.x, cmy = -r.y;  // cm = conj(C[H - k])
     const T dx = c.x - cmx, dy = c.y - cmy;
     const cx<T> P = twp[m];
-    cx<T> x = mk<T>(fma(P.x, dx, fma(-P.y, dy, cmx)), fma(P.x, dy, fma(P.y, dx, cmy)));
-    if (zmul) x = cscale<T>(cmuli<T>(x), (T)k);
-    f.template st<cx<T>>(x, (spec_row<T, N>(row_id) + k) * cs, soff);
-    if (k == 0) f.template st<cx<T>>(zmul ? mk<T>((T)0, (T)0) : mk<T>(c.x - c.y, (T)0),
-                            (spec_nyq<T, N>() + row_id) * cs, soff);
+    v[m] = mk<T>(fma(P.x, dx, fma(-P.y, dy, cmx)), fma(P.x, dy, fma(P.y, dx, cmy)));
   }
   lds_sync<row_in_wave<TZ>()>();
 }
@@ -884,12 +898,13 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
         twp[m] = mk<T>((T)0.5 + (T)0.5 * w.y, (T)-0.5 * w.x);
       }
     }
+    // the nine stored fields; n3's spectrum also gives n_2v,z (field kFieldZ2)
 #pragma unroll
-    for (int q = 0; q < kFields; ++q) {
+    for (int q = 0; q < kFieldZ2; ++q) {
       cx<T>* kc = kb[q % kBufs];
       cx<T>* mc = mb[kLds ? 0 : q % kBufs];
       if constexpr (kAhead > 0) {
-        if (q + kAhead < kFields) {
+        if (q + kAhead < kFieldZ2) {
           const int qa = q + kAhead, ba = qa % kBufs;
           if constexpr (kLds) c2r_load_k<T, N, TZ, EZ>(kb[ba], nb[ba], t, B, (uint32_t)qa * fbytes, row);
           else c2r_load<T, N, TZ, EZ>(kb[ba], mb[ba], t, B, (uint32_t)qa * fbytes, row);
@@ -899,13 +914,20 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
         else c2r_load<T, N, TZ, EZ>(kc, mc, t, B, (uint32_t)q * fbytes, row);
       }
       if constexpr (kLds) c2r_mirror<T, N, TZ, EZ>(mc, kc, nb[q % kBufs], t, lrow);
-      // the z component of each vector density is i s_z Q_b, formed here
-      if constexpr (kTwRegs) {
-        c2r_combine_p<T, N, TZ, EZ>(val + q * EZ, kc, mc, t, twp, q == kSlotZ || q == kSlotZ + kVecStride);
-        fft_pencil<T, N / 2, EZ, false>(val + q * EZ, t, twr, lp);
-      } else {
-        c2r_combine<T, N, TZ, EZ>(val + q * EZ, kc, mc, t, twN, q == kSlotZ || q == kSlotZ + kVecStride);
-        fft_pencil<T, N / 2, EZ, false>(val + q * EZ, t, (const cx<T>*)twH, lp);
+      // the z components of the vector densities, i s_z [6] and i s_z k0 [3],
+      // are formed here
+#pragma unroll
+      for (int g = 0; g < (q == kSlotN3 ? 2 : 1); ++g) {
+        cx<T>* vq = val + (g ? kFieldZ2 : q) * EZ;
+        const bool zm = q == kSlotZ || g != 0;
+        const T zs = g ? (T)a.kscale : (T)1;
+        if constexpr (kTwRegs) {
+          c2r_combine_p<T, N, TZ, EZ>(vq, kc, mc, t, twp, zm, zs);
+          fft_pencil<T, N / 2, EZ, false>(vq, t, twr, lp);
+        } else {
+          c2r_combine<T, N, TZ, EZ>(vq, kc, mc, t, twN, zm, zs);
+          fft_pencil<T, N / 2, EZ, false>(vq, t, (const cx<T>*)twH, lp);
+        }
       }
     }
   }
@@ -991,15 +1013,32 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
       __builtin_amdgcn_sched_barrier(0);  // one grid point at a time
     }
   }
+  // F_2z first: -i s_z k0 F_2z joins the spectrum of F_3
+  cx<T> z2[EZ];
 #pragma unroll
-  for (int q = 0; q < kFields; ++q) {
+  for (int i = 0; i < kFields; ++i) {
+    const int q = i == 0 ? kFieldZ2 : i == 1 ? kSlotN3 : i <= kSlotN3 + 1 ? i - 2 : i - 1;
+    cx<T>* vq = val + q * EZ;
     // the z components of the vector derivatives leave as i s_z F_z
+    const T zs = q == kSlotZ ? (T)1 : q == kFieldZ2 ? -(T)a.kscale : (T)0;
+    cx<T> nyq;
     if constexpr (kTwRegs) {
-      fft_pencil<T, N / 2, EZ, true>(val + q * EZ, t, twr, lp);
-      r2c_post_p<T, N, TZ, EZ>(val + q * EZ, t, twp, lrow, B, q * fbytes, row, q == kSlotZ || q == kSlotZ + kVecStride);
+      fft_pencil<T, N / 2, EZ, true>(vq, t, twr, lp);
+      r2c_post_p<T, N, TZ, EZ>(vq, nyq, t, twp, lrow);
     } else {
-      fft_pencil<T, N / 2, EZ, true>(val + q * EZ, t, (const cx<T>*)twH, lp);
-      r2c_post<T, N, TZ, EZ>(val + q * EZ, t, twN, lrow, B, q * fbytes, row, q == kSlotZ || q == kSlotZ + kVecStride);
+      fft_pencil<T, N / 2, EZ, true>(vq, t, (const cx<T>*)twH, lp);
+      r2c_post_w<T, N, TZ, EZ>(vq, nyq, t, twN, lrow);
+    }
+    if (q == kSlotZ || q == kFieldZ2) mul_isz<T, TZ, EZ>(vq, nyq, t, zs);
+    if (q == kFieldZ2) {
+#pragma unroll
+      for (int m = 0; m < EZ; ++m) z2[m] = vq[m];
+    } else {
+      if (q == kSlotN3) {
+#pragma unroll
+        for (int m = 0; m < EZ; ++m) vq[m] = cadd<T>(vq[m], z2[m]);
+      }
+      r2c_store<T, N, TZ, EZ>(vq, nyq, t, B, q * fbytes, row);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -1014,19 +1053,19 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
 // ---------------------------------------------------------------------------
 // y direction: c2c along y for every (x, kz) pencil of the main array and
 // every x row of the Nyquist plane; in place on `nf` fields of `sel`
-// (nf_code -1: S fields).  nf_code kVecMode: the ten FMT fields of specB
-// with the vector-component bookkeeping of the field-slot layout: the
-// inverse pass also writes [y] = i s_y Q_b next to Q_b; the forward pass
-// writes [z] = i s_y F_y + [z] and leaves [y] unused.
+// (nf_code -1: S fields).  nf_code kVecMode: the FMT fields of specB with the
+// vector-component bookkeeping of the field-slot layout: the inverse pass
+// also writes the y components, formed from [6] and [3]; the forward pass
+// adds those components' derivatives to [6] and [3] and leaves [y] unused.
 // ---------------------------------------------------------------------------
 constexpr int kVecMode = -2;
 
 template <typename T, int N, int EY, int TY>
-__device__ __forceinline__ void mul_isy(cx<T>* v, int t) {
+__device__ __forceinline__ void mul_isy(cx<T>* v, int t, T sc) {
 #pragma unroll
   for (int m = 0; m < EY; ++m) {
     const int ky = t + TY * m;
-    const T sy = ky == N / 2 ? (T)0 : (T)sgn_idx(ky, N);
+    const T sy = ky == N / 2 ? (T)0 : sc * (T)sgn_idx(ky, N);
     v[m] = cscale<T>(cmuli<T>(v[m]), sy);
   }
 }
@@ -1070,7 +1109,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
   for (int m = 0; m < EY; ++m) eo[m] = (off + (uint32_t)(t + TY * m) * es) * (uint32_t)sizeof(cx<T>);
   const uint32_t fbytes = (uint32_t)(a.fstride * sizeof(cx<T>));
   for (int f = 0; f < nf; ++f) {
-    if (vec && (f - kSlotX) % kVecStride != 0 && f > kSlotX) continue;  // [y], [z] below
+    if (vec && (f == kSlotN3 || (f > kSlotX && (f - kSlotX) % kVecStride != 0))) continue;  // [y], [z] below
     const uint32_t so = (uint32_t)f * fbytes;
     cx<T> v[EY];
 #pragma unroll
@@ -1083,15 +1122,17 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
 #pragma unroll 1
   for (int b = 0; b < 2; ++b) {
     const uint32_t sy_off = (uint32_t)(kSlotY + kVecStride * b) * fbytes;
-    const uint32_t sz_off = (uint32_t)(kSlotZ + kVecStride * b) * fbytes;
+    const uint32_t sz_off = (uint32_t)(b == 0 ? kSlotZ : kSlotN3) * fbytes;
+    // vector 2: k0 times the gradient of n3, and minus that on the way back
+    const T sc = b == 0 ? (T)1 : (T)(FWD ? -a.kscale : a.kscale);
     if constexpr (!FWD) {
-      // Q_b -> [y] = y-inverse of i s_y Q_b and [z] = y-inverse of Q_b
+      // Q -> [y] = y-inverse of i s_y sc Q and [z] = y-inverse of Q
       cx<T> q[EY], w[EY];
 #pragma unroll
       for (int m = 0; m < EY; ++m) q[m] = base.template ld<cx<T>>(eo[m], sz_off);
 #pragma unroll
       for (int m = 0; m < EY; ++m) w[m] = q[m];
-      mul_isy<T, N, EY, TY>(w, t);
+      mul_isy<T, N, EY, TY>(w, t, sc);
       fft_pencil<T, N, EY, false>(w, t, tw, lp);
 #pragma unroll
       for (int m = 0; m < EY; ++m) base.template st<cx<T>>(w[m], eo[m], sy_off);
@@ -1099,14 +1140,14 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
 #pragma unroll
       for (int m = 0; m < EY; ++m) base.template st<cx<T>>(q[m], eo[m], sz_off);
     } else {
-      // [z] <- i s_y (y-forward of F_y) + y-forward of [z]
+      // [z] <- i s_y sc (y-forward of F_y) + y-forward of [z]
       cx<T> fy[EY], g[EY];
 #pragma unroll
       for (int m = 0; m < EY; ++m) fy[m] = base.template ld<cx<T>>(eo[m], sy_off);
 #pragma unroll
       for (int m = 0; m < EY; ++m) g[m] = base.template ld<cx<T>>(eo[m], sz_off);
       fft_pencil<T, N, EY, true>(fy, t, tw, lp);
-      mul_isy<T, N, EY, TY>(fy, t);
+      mul_isy<T, N, EY, TY>(fy, t, sc);
       fft_pencil<T, N, EY, true>(g, t, tw, lp);
 #pragma unroll
       for (int m = 0; m < EY; ++m) base.template st<cx<T>>(cadd<T>(g[m], fy[m]), eo[m], sz_off);
@@ -1137,35 +1178,6 @@ struct XPencil {
 
 template <int N, int PX> constexpr int x_tiles() { return (N * (N / 2)) / PX + N / PX; }
 
-
-template <typename T>
-__device__ __forceinline__ T inv_sqrt_m(int m) {
-  if constexpr (sizeof(T) == 4) return m == 0 ? 0.0f : __builtin_amdgcn_rsqf((float)m);
-  else return m == 0 ? 0.0 : 1.0 / sqrt((double)m);
-}
-
-// per-lane k-space data of the EX elements a thread owns
-template <typename T, int N, int EX, int TX>
-struct XKs {
-  int mm[EX];   // integer |j|^2
-  T ux[EX];     // unit-vector components (0 on that axis's Nyquist plane)
-  T uy[EX];
-  T uz[EX];
-  __device__ __forceinline__ XKs(int t, int ky, int kz) {
-    constexpr int H = N / 2;
-    const int sy = sgn_idx(ky, N), sz = kz;
-#pragma unroll
-    for (int m = 0; m < EX; ++m) {
-      const int kx = t + TX * m;
-      const int sx = sgn_idx(kx, N);
-      mm[m] = sx * sx + sy * sy + sz * sz;
-      const T r = inv_sqrt_m<T>(mm[m]);
-      ux[m] = kx == H ? (T)0 : (T)sx * r;
-      uy[m] = ky == H ? (T)0 : (T)sy * r;
-      uz[m] = kz == H ? (T)0 : (T)sz * r;
-    }
-  }
-};
 
 template <typename T, int N>
 __device__ __forceinline__ uint64_t table_m(int /*unused*/) { return 3ull * (N / 2) * (N / 2) + 1; }
@@ -1208,11 +1220,11 @@ __device__ __forceinline__ void sincos_f32(float x, float& sn, float& cs) {
 }
 
 // Hard-sphere weights at |k| = k for radius R, in FP32 registers:
-// j0(kR), 4 pi R^3 j1(kR)/(kR) (ball) and 4 pi R^2 j1(kR) (shell magnitude).
+// j0(kR) and 4 pi R^3 j1(kR)/(kR) (ball).
 // j1(x)/x switches to its Taylor series below x = 1, where the closed form
 // loses digits to cancellation.
 template <bool SIGNBITS = false>
-__device__ __forceinline__ void hs_weights_f32(float k, float R, float& j0, float& w3, float& v2) {
+__device__ __forceinline__ void hs_weights_f32(float k, float R, float& j0, float& w3) {
   const float x = k * R;
   float sn, cs;
   sincos_f32<SIGNBITS>(x, sn, cs);
@@ -1225,23 +1237,19 @@ __device__ __forceinline__ void hs_weights_f32(float k, float R, float& j0, floa
   const float rx = __builtin_amdgcn_rcpf(x);  // 1 ulp; inf at x = 0, where both uses take their series
   const float j1x = x < 1.0f ? ser : (sn - x * cs) * rx * rx * rx;
   j0 = x < 1e-3f ? 1.0f - x2 * 0.166666667f : sn * rx;
-  const float a2 = 12.5663706144f * R * R;
-  w3 = a2 * R * j1x;
-  v2 = a2 * x * j1x;
+  w3 = 12.5663706144f * R * R * R * j1x;
 }
 
 // Weights of species i at the integer class m = |j|^2: computed in registers
 // for FP32, gathered from the FP64 table otherwise.
 template <typename T, bool SIGNBITS = false>
-__device__ __forceinline__ void hs_weights(const EvalArgs& a, const Buf& hs, int S, int i, int m, T& j0, T& w3,
-                                           T& v2) {
+__device__ __forceinline__ void hs_weights(const EvalArgs& a, const Buf& hs, int S, int i, int m, T& j0, T& w3) {
   if constexpr (sizeof(T) == 4) {
-    hs_weights_f32<SIGNBITS>((float)a.kscale * __builtin_sqrtf((float)m), (float)a.R[i], j0, w3, v2);
+    hs_weights_f32<SIGNBITS>((float)a.kscale * __builtin_sqrtf((float)m), (float)a.R[i], j0, w3);
   } else {
-    const v4<T> w = hs.template ld<v4<T>>((uint32_t)(m * S + i) * (uint32_t)sizeof(v4<T>));
+    const cx<T> w = hs.template ld<cx<T>>((uint32_t)(m * S + i) * (uint32_t)sizeof(cx<T>));
     j0 = w.x;
     w3 = w.y;
-    v2 = w.z;
   }
 }
 
@@ -1255,28 +1263,28 @@ __device__ __forceinline__ void hs_weights(const EvalArgs& a, const Buf& hs, int
 // rest from its mirror's slots.  Callers alternate between two buffers, so
 // one barrier per call suffices (a thread writes a buffer again only after
 // the barrier of the call in between).
-struct WTrip {
-  float j0, w3, v2;
+struct WPair {
+  float j0, w3;
 };
 
 template <int N, int EX, int TX, int PX>
-__device__ __forceinline__ void x_weights_shared(float kscale, float R, const int* mm, int t, int p, WTrip* buf,
-                                                 float* j0, float* w3, float* v2) {
+__device__ __forceinline__ void x_weights_shared(float kscale, float R, const int* mm, int t, int p, WPair* buf,
+                                                 float* j0, float* w3) {
   constexpr int EH = EX / 2;
   static_assert(EX % 2 == 0 && TX * EX == N, "mirror map");
 #pragma unroll
   for (int e = 0; e < EH; ++e) {
-    WTrip w;
-    hs_weights_f32<true>(kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3, w.v2);
+    WPair w;
+    hs_weights_f32<true>(kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3);
     buf[(e * TX + t) * PX + p] = w;
   }
-  WTrip ny{0.0f, 0.0f, 0.0f};
-  if (t == 0) hs_weights_f32<true>(kscale * __builtin_sqrtf((float)mm[EH]), R, ny.j0, ny.w3, ny.v2);
+  WPair ny{0.0f, 0.0f};
+  if (t == 0) hs_weights_f32<true>(kscale * __builtin_sqrtf((float)mm[EH]), R, ny.j0, ny.w3);
   __syncthreads();
   const int tm = t == 0 ? 0 : TX - t;
 #pragma unroll
   for (int e = 0; e < EX; ++e) {
-    WTrip w;
+    WPair w;
     if (e < EH) {
       w = buf[(e * TX + t) * PX + p];
     } else {
@@ -1286,7 +1294,6 @@ __device__ __forceinline__ void x_weights_shared(float kscale, float R, const in
     }
     j0[e] = w.j0;
     w3[e] = w.w3;
-    v2[e] = w.v2;
   }
 }
 
@@ -1296,19 +1303,10 @@ __device__ __forceinline__ T s_axis(int k) {
   return k == N / 2 ? (T)0 : (T)sgn_idx(k, N);
 }
 
-// unit-vector component c of k at element kx of a pencil (0 on that axis's
-// Nyquist plane)
-template <typename T, int N>
-__device__ __forceinline__ T khat(int c, int kx, int ky, int kz, int m) {
-  const T r = inv_sqrt_m<T>(m);
-  if (c == 0) return kx == N / 2 ? (T)0 : (T)sgn_idx(kx, N) * r;
-  if (c == 1) return ky == N / 2 ? (T)0 : (T)sgn_idx(ky, N) * r;
-  return kz == N / 2 ? (T)0 : (T)kz * r;
-}
-
-// field slot of the q-th field the back pass reads (0..3, [x]1, [z]1, [x]2, [z]2)
+// field slot of the q-th field the back pass reads: 0..2, [x] and [z] of
+// vector 1, n3 (with [z] of vector 2), [x] of vector 2
 __device__ __forceinline__ constexpr int back_field(int q) {
-  return q < 4 ? q : kSlotX + (q - 4) / 2 * kVecStride + ((q - 4) % 2) * (kSlotZ - kSlotX);
+  return q < 3 ? q : q == 3 ? kSlotX : q == 4 ? kSlotZ : q == 5 ? kSlotN3 : kSlotX + kVecStride;
 }
 
 // Per-lane addressing of an x tile: element m of the lane's pencil sits at
@@ -1330,8 +1328,8 @@ struct XAddr {
 //
 // P3: forward weights.  For every k: n^_a(k) = sum_i rho^_i(k) conj(w^_i^a(k))
 // (correlation, Sec. 2.3.1); scalars w0 = j0, w1 = R j0, w2 = 4 pi R^2 j0,
-// w3 = 4 pi R^3 j1(kR)/(kR); vectors conj(-i khat V) = +i khat V with
-// V2 = 4 pi R^2 j1(kR), V1 = V2 / (4 pi R).
+// w3 = 4 pi R^3 j1(kR)/(kR); vectors conj(-i khat V2) = +i k w3 and the same
+// over 4 pi R (the field-slot layout).
 // The species pencils stream through two register buffers: the loads of
 // species i + 1 are in flight while species i is transformed.
 template <typename T, int N, int EX = Geo<T, N>::EX, int PX = Geo<T, N>::PX>
@@ -1348,7 +1346,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   // time.
   constexpr int EH = EX / 2;
   constexpr int kRegion = EH * TX * PX;
-  __shared__ WTrip wall[sizeof(T) == 4 ? 3 * kRegion + 3 * PX : 1];
+  __shared__ WPair wall[sizeof(T) == 4 ? 3 * kRegion + 3 * PX : 1];
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
   if (!a.hs_on) return;  // uniform per block
@@ -1356,7 +1354,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   const XPencil<T, N, PX> pc(tile, p);
   const LdsPencil2<T> lp{xch + p, xch + PX * N + p, PX};
   const int S = a.S;
-  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(v4<T>) : 0);
+  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(cx<T>) : 0);
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
@@ -1370,7 +1368,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
       mm[m] = sx * sx + sy * sy + sz * sz;
     }
   }
-  cx<T> acc[6][EX];
+  cx<T> acc[5][EX];  // n0..n3, Q
   cx<T> b0[EX], b1[EX];
   // the first species' pencil is in flight while the twiddle table is built
 #pragma unroll
@@ -1384,13 +1382,13 @@ __global__ void __launch_bounds__((PX * (N / EX)))
           const float R = (float)a.R[c];
 #pragma unroll
           for (int e = 0; e < EH; ++e) {
-            WTrip w;
-            hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3, w.v2);
+            WPair w;
+            hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3);
             wall[c * kRegion + (e * TX + t) * PX + p] = w;
           }
           if (t == 0) {
-            WTrip w;
-            hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[EH]), R, w.j0, w.w3, w.v2);
+            WPair w;
+            hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[EH]), R, w.j0, w.w3);
             wall[3 * kRegion + c * PX + p] = w;
           }
         }
@@ -1409,8 +1407,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
         for (int m = 0; m < EX; ++m) nxt[m] = A.template ld<cx<T>>(xa.vo, (uint32_t)(i + 1) * fbytes + m * xa.mstride);
       }
       fft_pencil<T, N, EX, true>(cur, t, tw, lp);
-      const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)a.inv4piR[i];
-      float sj0[EX], ss3[EX], svv[EX];
+      const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)(a.inv4piR[i] * a.kscale);
+      float sj0[EX], ss3[EX];
       if constexpr (sizeof(T) == 4) {
         if (i < 3 && pre) {
           // own slot, the mirror's slot, or thread 0's column kx = N/2
@@ -1421,36 +1419,34 @@ __global__ void __launch_bounds__((PX * (N / EX)))
             const int idx = m < EH ? i * kRegion + (m * TX + t) * PX + p
                             : (t == 0 && m == EH) ? 3 * kRegion + i * PX + p
                                                   : i * kRegion + (em * TX + tm) * PX + p;
-            const WTrip w = wall[idx];
-            sj0[m] = w.j0; ss3[m] = w.w3; svv[m] = w.v2;
+            const WPair w = wall[idx];
+            sj0[m] = w.j0; ss3[m] = w.w3;
           }
         } else {
           x_weights_shared<N, EX, TX, PX>((float)a.kscale, (float)a.R[i], mm, t, p, wall + (i & 1) * kRegion, sj0,
-                                          ss3, svv);
+                                          ss3);
         }
       }
 #pragma unroll
       for (int m = 0; m < EX; ++m) {
-        T j0, s3, vv;
+        T j0, s3;
         if constexpr (sizeof(T) == 4) {
-          j0 = sj0[m]; s3 = ss3[m]; vv = svv[m];
+          j0 = sj0[m]; s3 = ss3[m];
         } else {
-          hs_weights<T>(a, hs, S, i, mm[m], j0, s3, vv);
+          hs_weights<T>(a, hs, S, i, mm[m], j0, s3);
         }
         if (i == 0) {
           acc[0][m] = cscale<T>(cur[m], j0);
           acc[1][m] = cscale<T>(cur[m], j0 * R);
           acc[2][m] = cscale<T>(cur[m], j0 * ar);
           acc[3][m] = cscale<T>(cur[m], s3);
-          acc[4][m] = cscale<T>(cur[m], vv * i4);
-          acc[5][m] = cscale<T>(cur[m], vv);
+          acc[4][m] = cscale<T>(cur[m], s3 * i4);
         } else {
           cfma<T>(acc[0][m], cur[m], j0);
           cfma<T>(acc[1][m], cur[m], j0 * R);
           cfma<T>(acc[2][m], cur[m], j0 * ar);
           cfma<T>(acc[3][m], cur[m], s3);
-          cfma<T>(acc[4][m], cur[m], vv * i4);
-          cfma<T>(acc[5][m], cur[m], vv);
+          cfma<T>(acc[4][m], cur[m], s3 * i4);
         }
       }
     }
@@ -1466,33 +1462,29 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
     for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)o * fbytes + m * xa.mstride);
   }
-  // vector weighted densities n_bv,c = +i khat_c A_b (A_1 = sum rho V1, A_2 =
-  // sum rho V2): stored as [x] = i s_x Q_b and [z] = Q_b with Q_b = A_b / |j|
+  // vector weighted densities: [4] = i s_x Q and [6] = Q, [7] = i s_x k0 n3
   // (the y and z components are formed by the y and z passes)
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
+  for (int c = 0; c < 3; ++c) {
+    cx<T> v[EX];
+    const int src = c < 2 ? 4 : kSlotN3;
+    const T f = c < 2 ? sc : sc * (T)a.kscale;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      cx<T> v[EX];
+    for (int m = 0; m < EX; ++m)
+      v[m] = c == 1 ? cscale<T>(acc[src][m], f) : cmuli<T>(cscale<T>(acc[src][m], f * s_axis<T, N>(t + TX * m)));
+    fft_pencil<T, N, EX, false>(v, t, tw, lp);
+    const int slot = c == 0 ? kSlotX : c == 1 ? kSlotZ : kSlotX + kVecStride;
 #pragma unroll
-      for (int m = 0; m < EX; ++m) {
-        const cx<T> q = cscale<T>(acc[4 + b][m], inv_sqrt_m<T>(mm[m]) * sc);
-        v[m] = c == 0 ? cmuli<T>(cscale<T>(q, s_axis<T, N>(t + TX * m))) : q;
-      }
-      fft_pencil<T, N, EX, false>(v, t, tw, lp);
-      const int slot = (c == 0 ? kSlotX : kSlotZ) + kVecStride * b;
-#pragma unroll
-      for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)slot * fbytes + m * xa.mstride);
-    }
+    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)slot * fbytes + m * xa.mstride);
   }
 }
 
 // P7: back-convolution (Sec. 2.3.1, convolution orientation: no conjugate)
 // plus the pair kernels of Sec. 2.3.2 / 2.3.4:
-//   mu^_i = j0_i (F0 + R_i F1 + 4 pi R_i^2 F2) + w3_i F3
-//           - i V2_i (D1 / (4 pi R_i) + D2) + sum_j G_ij rho^_j,
-// with F_a the derivative spectra and D_b = khat . (vector derivative b).
-// For S <= CH <= 4: the ten derivative pencils and then the S density pencils
+//   mu^_i = j0_i (F0 + R_i F1 + 4 pi R_i^2 F2)
+//           + w3_i (F3 - k0 i s.F_2v - k0 i s.F_1v / (4 pi R_i)) + sum_j G_ij rho^_j,
+// with F_a the derivative spectra and k = k0 s (the field-slot layout).
+// For S <= CH <= 4: the seven derivative pencils and then the S density pencils
 // stream through two register buffers (the next pencil, and the next pair-
 // table row, are in flight during each transform); the derivative spectra
 // fold into the CH outputs before the density phase starts.
@@ -1513,14 +1505,14 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   // element's other half is its mirror's (see x_weights_shared)
   constexpr bool kPre = sizeof(T) == 4 && CH <= 3;
   constexpr int EH = EX / 2;
-  __shared__ WTrip wpre[kPre ? CH * EH * TX * PX + CH * PX : 1];
+  __shared__ WPair wpre[kPre ? CH * EH * TX * PX + CH * PX : 1];
   if (a.S > CH) return;  // uniform per block
   const int p = threadIdx.x % PX, t = threadIdx.x / PX;
   const XPencil<T, N, PX> pc(tile, p);
   const LdsPencil2<T> lp{xch + p, xch + PX * N + p, PX};
   const int S = a.S;
   const bool hs_on = a.hs_on, pair_on = a.pair_on;
-  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(v4<T>) : 0);
+  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(cx<T>) : 0);
   const Buf pt = make_buf(a.pair_tab, pair_on ? table_m<T, N>(0) * S * a.Sp * sizeof(T) : 0);
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, hs_on ? spec_bytes<T>(a, kFields) : 0);
@@ -1544,7 +1536,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
     for (int m = 0; m < EX; ++m) b0[m] = B.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
   } else if (pair_on) {
 #pragma unroll
-    for (int m = 0; m < EX; ++m) b0[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
+    for (int m = 0; m < EX; ++m) b1[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
   }
   if constexpr (kPre) {
     if (hs_on) {
@@ -1553,13 +1545,13 @@ __global__ void __launch_bounds__((PX * (N / EX)))
         const float R = (float)a.R[c < S ? c : 0];
 #pragma unroll
         for (int e = 0; e < EH; ++e) {
-          WTrip w;
-          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3, w.v2);
+          WPair w;
+          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3);
           wpre[((c * EH + e) * TX + t) * PX + p] = w;
         }
         if (t == 0) {
-          WTrip w;
-          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[EH]), R, w.j0, w.w3, w.v2);
+          WPair w;
+          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[EH]), R, w.j0, w.w3);
           wpre[CH * EH * TX * PX + c * PX + p] = w;
         }
       }
@@ -1568,9 +1560,9 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   init_twiddles<T, N>(tw);
   __syncthreads();
   if (hs_on) {
-    // F[0..3]: scalar derivative spectra; F[4 + b] = i (khat . F_bv) =
-    // (i s_x F_bx + [z]) / |j| (see the field-slot layout)
-    cx<T> F[6][EX];
+    // F[0..2]: scalar derivative spectra; F[3] = [3] - i s_x k0 [7], the
+    // spectrum that w3 multiplies; F[4] = i s_x [4] + [6] (vector 1)
+    cx<T> F[5][EX];
 #pragma unroll
     for (int q = 0; q < kBackFields; ++q) {
       cx<T>* cur = (q & 1) ? b1 : b0;
@@ -1586,27 +1578,21 @@ __global__ void __launch_bounds__((PX * (N / EX)))
       }
       fft_pencil<T, N, EX, true>(cur, t, tw, lp);
       const int f = back_field(q);
-      if (f < 4) {
 #pragma unroll
-        for (int m = 0; m < EX; ++m) F[f][m] = cur[m];
-      } else {
-        const int b = (f - kSlotX) / kVecStride;
-        const bool xs = (f - kSlotX) % kVecStride == 0;
-#pragma unroll
-        for (int m = 0; m < EX; ++m) {
-          const T r = inv_sqrt_m<T>(mm[m]);
-          if (xs) F[4 + b][m] = cscale<T>(cmuli<T>(cur[m]), s_axis<T, N>(t + TX * m) * r);
-          else cfma<T>(F[4 + b][m], cur[m], r);
-        }
+      for (int m = 0; m < EX; ++m) {
+        if (f == kSlotX) F[4][m] = cscale<T>(cmuli<T>(cur[m]), s_axis<T, N>(t + TX * m));
+        else if (f == kSlotZ) F[4][m] = cadd<T>(F[4][m], cur[m]);
+        else if (f == kSlotX + kVecStride) cfma<T>(F[3][m], cmulmi<T>(cur[m]), s_axis<T, N>(t + TX * m) * (T)a.kscale);
+        else F[f][m] = cur[m];
       }
     }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int i = c < S ? c : 0;
-      const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)a.inv4piR[i];
+      const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)(a.inv4piR[i] * a.kscale);
 #pragma unroll
       for (int m = 0; m < EX; ++m) {
-        T j0, w3, v2;
+        T j0, w3;
         if constexpr (kPre) {
           // own slot, the mirror's slot, or thread 0's column kx = N/2
           const int tm = t == 0 ? 0 : TX - t;
@@ -1614,20 +1600,18 @@ __global__ void __launch_bounds__((PX * (N / EX)))
           const int idx = m < EH ? ((c * EH + m) * TX + t) * PX + p
                           : (t == 0 && m == EH) ? CH * EH * TX * PX + c * PX + p
                                                 : ((c * EH + em) * TX + tm) * PX + p;
-          const WTrip w = wpre[idx];
-          j0 = w.j0; w3 = w.w3; v2 = w.v2;
+          const WPair w = wpre[idx];
+          j0 = w.j0; w3 = w.w3;
         } else {
-          hs_weights<T>(a, hs, S, i, mm[m], j0, w3, v2);
+          hs_weights<T>(a, hs, S, i, mm[m], j0, w3);
         }
         cx<T> s0 = F[0][m];
         cfma<T>(s0, F[1][m], R);
         cfma<T>(s0, F[2][m], ar);
         cx<T> u = cscale<T>(s0, j0);
-        cfma<T>(u, F[3][m], w3);
-        // -i V2 (D1 / (4 pi R) + D2) with F[4 + b] = i D_b
-        cx<T> dv = F[5][m];
-        cfma<T>(dv, F[4][m], i4);
-        cfma<T>(u, dv, -v2);
+        cx<T> w = F[3][m];
+        cfma<T>(w, F[4][m], -i4);
+        cfma<T>(u, w, w3);
         out[c][m] = u;
       }
       // one species at a time: hoisting the weights of later species ahead
@@ -1640,18 +1624,18 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
       for (int m = 0; m < EX; ++m) out[c][m] = mk<T>((T)0, (T)0);
   }
-  // the density stream starts in b0: without HS it was loaded at the start;
-  // with HS after the last of the (even number of) derivative fields, into
+  // the density stream starts in b1: without HS it was loaded at the start;
+  // with HS after the last of the (odd number of) derivative fields, into
   // the buffer that field left free
-  static_assert(kBackFields % 2 == 0, "the density stream continues in b0");
+  static_assert(kBackFields % 2 == 1, "the density stream continues in b1");
   if (pair_on && sizeof(T) == 8) {
     // FP64: pair-table rows gathered after each transform (two buffers of
     // double rows would not fit the register budget)
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       if (j < S) {  // uniform
-        cx<T>* cur = (j & 1) ? b1 : b0;
-        cx<T>* nxt = (j & 1) ? b0 : b1;
+        cx<T>* cur = (j & 1) ? b0 : b1;
+        cx<T>* nxt = (j & 1) ? b1 : b0;
         if (j + 1 < S) {
 #pragma unroll
           for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, (uint32_t)(j + 1) * fbytes + m * xa.mstride);
@@ -1674,8 +1658,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       if (j < S) {  // uniform
-        cx<T>* cur = (j & 1) ? b1 : b0;
-        cx<T>* nxt = (j & 1) ? b0 : b1;
+        cx<T>* cur = (j & 1) ? b0 : b1;
+        cx<T>* nxt = (j & 1) ? b1 : b0;
         if (j + 1 < S) {
 #pragma unroll
           for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, (uint32_t)(j + 1) * fbytes + m * xa.mstride);
@@ -1728,19 +1712,27 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   const XPencil<T, N, PX> pc(tile, p);
   const LdsPencil2<T> lp{xch + p, xch + PX * N + p, PX};
   const int S = a.S;
-  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(v4<T>) : 0);
+  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(cx<T>) : 0);
   const Buf pt = make_buf(a.pair_tab, a.pair_on ? table_m<T, N>(0) * S * a.Sp * sizeof(T) : 0);
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, a.hs_on ? spec_bytes<T>(a, kFields) : 0);
   const BufN<N> C = make_buf<stream_policy<N>()>(a.specC, spec_bytes<T>(a, S));
   const uint32_t fbytes = (uint32_t)(a.fstride * sizeof(cx<T>));
-  const XKs<T, N, EX, TX> ks(t, pc.ky, pc.kz);
+  int mm[EX];
+  {
+    const int sy = sgn_idx(pc.ky, N), sz = pc.kz;
+#pragma unroll
+    for (int m = 0; m < EX; ++m) {
+      const int sx = sgn_idx(t + TX * m, N);
+      mm[m] = sx * sx + sy * sy + sz * sz;
+    }
+  }
   uint32_t eo[EX];
 #pragma unroll
   for (int m = 0; m < EX; ++m) eo[m] = (pc.off + (uint32_t)(t + TX * m) * pc.es) * (uint32_t)sizeof(cx<T>);
-  cx<T> F[6][EX];
+  cx<T> F[5][EX];  // as in k_xback
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
+  for (int q = 0; q < 5; ++q)
 #pragma unroll
     for (int m = 0; m < EX; ++m) F[q][m] = mk<T>((T)0, (T)0);
   if (a.hs_on) {
@@ -1760,22 +1752,18 @@ __global__ void __launch_bounds__((PX * (N / EX)))
         }
       }
     }
-    // F[4 + b] = i (khat . F_bv) = (i s_x F_bx + [z]) / |j| (field-slot layout)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int c = 0; c < 3; ++c) {
+      cx<T> v[EX];
+      const int slot = c == 0 ? kSlotX : c == 1 ? kSlotZ : kSlotX + kVecStride;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        cx<T> v[EX];
-        const int slot = (c == 0 ? kSlotX : kSlotZ) + kVecStride * b;
+      for (int m = 0; m < EX; ++m) v[m] = B.template ldnt<cx<T>>(eo[m], (uint32_t)slot * fbytes);
+      fft_pencil<T, N, EX, true>(v, t, tw, lp);
 #pragma unroll
-        for (int m = 0; m < EX; ++m) v[m] = B.template ldnt<cx<T>>(eo[m], (uint32_t)slot * fbytes);
-        fft_pencil<T, N, EX, true>(v, t, tw, lp);
-#pragma unroll
-        for (int m = 0; m < EX; ++m) {
-          const T r = inv_sqrt_m<T>(ks.mm[m]);
-          if (c == 0) cfma<T>(F[4 + b][m], cmuli<T>(v[m]), s_axis<T, N>(t + TX * m) * r);
-          else cfma<T>(F[4 + b][m], v[m], r);
-        }
+      for (int m = 0; m < EX; ++m) {
+        if (c == 0) F[4][m] = cscale<T>(cmuli<T>(v[m]), s_axis<T, N>(t + TX * m));
+        else if (c == 1) F[4][m] = cadd<T>(F[4][m], v[m]);
+        else cfma<T>(F[3][m], cmulmi<T>(v[m]), s_axis<T, N>(t + TX * m) * (T)a.kscale);
       }
     }
   }
@@ -1797,7 +1785,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
         for (int m = 0; m < EX; ++m) {
           // G_{i0..i0+3, j} in one gather: row [m][j][.] of the pair table
-          const v4<T> g = pt.template ld<v4<T>>((uint32_t)((ks.mm[m] * S + j) * a.Sp + i0) * (uint32_t)sizeof(T));
+          const v4<T> g = pt.template ld<v4<T>>((uint32_t)((mm[m] * S + j) * a.Sp + i0) * (uint32_t)sizeof(T));
           cfma<T>(out[0][m], v[m], g.x);
           if constexpr (CH > 1) cfma<T>(out[1][m], v[m], g.y);
           if constexpr (CH > 2) cfma<T>(out[2][m], v[m], g.z);
@@ -1810,22 +1798,20 @@ __global__ void __launch_bounds__((PX * (N / EX)))
       const int i = i0 + c;
       if (i < S) {  // uniform across the block
         cx<T> v[EX];
-        const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)a.inv4piR[i];
+        const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)(a.inv4piR[i] * a.kscale);
 #pragma unroll
         for (int m = 0; m < EX; ++m) {
           cx<T> u = out[c][m];
           if (a.hs_on) {
-            T j0, w3, v2;
-            hs_weights<T>(a, hs, S, i, ks.mm[m], j0, w3, v2);
+            T j0, w3;
+            hs_weights<T>(a, hs, S, i, mm[m], j0, w3);
             cx<T> sc0 = F[0][m];
             cfma<T>(sc0, F[1][m], R);
             cfma<T>(sc0, F[2][m], ar);
             cfma<T>(u, sc0, j0);
-            cfma<T>(u, F[3][m], w3);
-            // -i V2 (D1 / (4 pi R) + D2) with F[4 + b] = i D_b
-            cx<T> dv = F[5][m];
-            cfma<T>(dv, F[4][m], i4);
-            cfma<T>(u, dv, -v2);
+            cx<T> w = F[3][m];
+            cfma<T>(w, F[4][m], -i4);
+            cfma<T>(u, w, w3);
           }
           v[m] = cscale<T>(u, sc);
         }

@@ -10,18 +10,33 @@ constexpr int kMaxPairs = kMaxSpecies * (kMaxSpecies + 1) / 2;
 constexpr int kFields = 10;  // n0, n1, n2, n3, n1v(x,y,z), n2v(x,y,z)
 
 // Storage of the two vector weighted densities n_bv (b = 1, 2) and of their
-// derivative fields.  n_bv,c(k) = i s_c Q_b(k) with Q_b = A_b / |j| the
-// spectrum of a real field and s_c the signed index along axis c (0 on that
-// axis's Nyquist plane), so each component is formed in the pass that
-// transforms its own axis.  Field slots 4..6 hold vector 1, 7..9 vector 2:
-//   after the x-forward pass:  [x] = i s_x Q_b, [z] = Q_b        ([y] unused)
-//   after the y-inverse pass:  [x], [y] = i s_y Q_b, [z] = Q_b    (z multiply
-//                              by i s_z is applied inside the z pass)
-//   after the z derivative pass: [x] = F_x, [y] = F_y, [z] = i s_z F_z
-//   after the y-forward pass:  [x] = F_x, [z] = i s_y F_y + i s_z F_z
-// and the back pass forms i |j| (khat . F) = i s_x F_x + [z].
+// derivative fields.  Every vector weight is the gradient of a ball weight
+// (omega_2v = -grad omega_3, omega_1v = omega_2v / (4 pi R)), so with
+// k0 = 2 pi / L and s_c the signed index along axis c (0 on that axis's
+// Nyquist plane)
+//   n_1v,c(k) = i s_c Q(k),  Q = k0 sum_i rho_i w_i^3 / (4 pi R_i),
+//   n_2v,c(k) = i s_c k0 n_3(k),
+// and each component is formed in the pass that transforms its own axis.
+// Vector 2 needs no spectrum of its own: its y and z components are formed
+// from that of n3, and the derivative with respect to them joins that of n3
+// on the way back (the back pass multiplies both by w_i^3).  Against a second
+// [z] slot for vector 2: one field less in every pass from the x forward to
+// the back pass, 436 instead of 468 bytes per grid point at three species in
+// mixed precision, and two y transforms and one x transform less each way
+// (256^3 mixed 85 us less per evaluation of 1.66 ms; 128^3 FP64 496 -> 455 us).
+// Field slots 4..6 hold vector 1, 7..8 vector 2 (slot 9 is a real field of
+// the weighted-density output only; no pass stores a spectrum there):
+//   after the x-forward pass:  [4] = i s_x Q, [6] = Q, [7] = i s_x k0 n3, [3] = n3
+//   after the y-inverse pass:  also [5] = i s_y Q, [8] = i s_y k0 n3
+//                              (the z pass forms i s_z [6] and i s_z k0 [3])
+//   after the z derivative pass: [4], [5] = F_1x, F_1y, [6] = i s_z F_1z,
+//                              [7], [8] = F_2x, F_2y, [3] = F_3 - i s_z k0 F_2z
+//   after the y-forward pass:  [6] += i s_y F_1y, [3] -= i s_y k0 F_2y
+// and the back pass forms i s_x F_1x + [6] and [3] - i s_x k0 F_2x.
 constexpr int kSlotX = 4, kSlotY = 5, kSlotZ = 6, kVecStride = 3;
-constexpr int kBackFields = 8;  // fields the back pass reads: 0..3, 4, 6, 7, 9
+constexpr int kSlotN3 = 3;                       // n3, and the [z] slot of vector 2
+constexpr int kFieldZ2 = kSlotZ + kVecStride;    // the real field n_2v,z
+constexpr int kBackFields = 7;  // fields the back pass reads: 0..2, 4, 6, 3, 7
 
 // Spectral field layout: the main block [kx][ky][kz < n/2] with each kx
 // plane (n * n/2 complex values) followed by spec_pad unused values, then the
@@ -63,9 +78,9 @@ struct EvalArgs {
   int32_t hs_wb;      // 1: modified (White Bear) hard-sphere functional, 0: Rosenfeld
   const double* rho;  // [S][n^3] input densities
   void* specA;        // S spectral fields (densities)
-  void* specB;        // 10 spectral fields (weighted densities, then derivatives)
+  void* specB;        // 9 spectral fields in 10 slots (weighted densities, then derivatives)
   void* specC;        // S spectral fields (chemical potentials)
-  const void* hs_tab;    // [M][S][4]: j0(kR), 4 pi R^3 j1(kR)/(kR), 4 pi R^2 j1(kR), 0
+  const void* hs_tab;    // [M][S][2]: j0(kR), 4 pi R^3 j1(kR)/(kR)
                          // (FP64 path only; the FP32 path evaluates them in registers)
   const void* pair_tab;  // [M][S][Sp]: entry [m][j][i] = combined pair kernel G_ij
   double* out;        // real output [nreal][n^3] (mu_ex or weighted densities)
