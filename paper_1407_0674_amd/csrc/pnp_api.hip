@@ -555,9 +555,11 @@ struct Split {
 
 // ea: device arg tables; fmask: the hard-sphere functionals among the
 // instances (1 Rosenfeld, 2 White Bear, 0 no HS term); sm: their species
-// counts; n: the grid size of the launch list.
+// counts; n: the grid size of the launch list; tables: build the radial
+// tables (false when an earlier sequence of the same call built them in the
+// same workspace).
 void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableArgs* ta, int count, int M,
-                  int fmask, const SpeciesMix& sm, hipStream_t s, int n) {
+                  int fmask, const SpeciesMix& sm, hipStream_t s, int n, bool tables = true) {
   PassTimer pt{c, s};
   Split sp(c, s, n);
   const int mp = sp.main_part();
@@ -570,12 +572,12 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
   // run: 1.657 ms per evaluation beside the y pass, 1.666 ms beside the z
   // pass).
   bool tab_pending = false;
-  if (!sp.on) {
+  if (!sp.on && tables) {
     pt.begin(0); op.at(0)->tables(ta, count, M, sm.maxS, s); pt.end();
   }
   pt.begin(1); op.at(1)->zfwd(ea, count, s); pt.end();
   sp.fork();
-  if (sp.on) {
+  if (sp.on && tables) {
     PassTimer ps{c, sp.nyq()};
     ps.begin(0); op.at(0)->tables(ta, count, M, sm.maxS, sp.nyq()); ps.end();
     tab_pending = true;
@@ -1057,7 +1059,7 @@ pnp_status pnp_equilibrium(pnp_ctx ctx, const pnp_grid* g, int32_t S, const pnp_
   if (hipSetDevice(ctx->device) != hipSuccess) return device_check(ctx, "set device");
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
-  unsigned long long* res = (unsigned long long*)(w + L.energy);
+  unsigned long long* res = (unsigned long long*)(w + L.status) + 1;  // words 2 and 3
   const long n3 = (long)d.n * d.n * d.n;
   double rbmb[2 * kMaxSpecies];
   for (int i = 0; i < S; ++i) { rbmb[2 * i] = sp[i].rho_bulk; rbmb[2 * i + 1] = mb[i]; }
@@ -1072,25 +1074,22 @@ pnp_status pnp_equilibrium(pnp_ctx ctx, const pnp_grid* g, int32_t S, const pnp_
   upload_args(ctx, &ta, 1, &ea, 1, s, dta, dea);
   const double* drb = (const double*)upload(ctx, rbmb, sizeof(double) * 2 * S, s);
   if (!dta || !dea || !drb) return device_check(ctx, "argument upload");
-  const int blocks = (int)std::min<long>(((long)S * n3 + 255) / 256, 4096);
   *iters = 0;
   *residual = INFINITY;
   for (int it = 1; it <= max_iter; ++it) {
-    run_sequence(ctx, select_ops(ctx, d.precision, d.n, 1), dea, dta, 1, L.M, hs_mask(d), mix_of(S), s, d.n);
-    if (hipMemsetAsync(res, 0, sizeof(unsigned long long), s) != hipSuccess) return device_check(ctx, "reset");
-    hipLaunchKernelGGL(k_picard, dim3(blocks), dim3(256), 0, s, rho, (const double*)mu, beta_v, n3, (int)S, drb,
-                       lambda, res, fixed);
+    // the radial tables depend on the problem only: the first step's serve all
+    run_sequence(ctx, select_ops(ctx, d.precision, d.n, 1), dea, dta, 1, L.M, hs_mask(d), mix_of(S), s, d.n, it == 1);
+    hipLaunchKernelGGL(k_picard, update_grid(n3, S), dim3(256), 0, s, rho, (const double*)mu, beta_v, n3, drb, lambda,
+                       res, fixed);
     st = device_check(ctx, "picard launch");
     if (st != PNP_OK) return st;
-    unsigned long long rbits = 0;
-    uint32_t stw[2] = {0, 0};
-    if (hipMemcpyAsync(&rbits, res, sizeof(rbits), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(stw, w + L.status, sizeof(stw), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    uint32_t stw[4] = {0, 0, 0, 0};
+    if (hipMemcpyAsync(stw, w + L.status, sizeof(stw), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return device_check(ctx, "residual read");
     st = status_of(ctx, stw);
     *iters = it;
-    std::memcpy(residual, &rbits, sizeof(double));
+    std::memcpy(residual, stw + 2, sizeof(double));
     if (st != PNP_OK) return st;
     if (!std::isfinite(*residual)) return fail(ctx, PNP_E_NONFINITE, "non-finite density update");
     if (*residual <= tol) break;
@@ -1391,9 +1390,8 @@ pnp_status pnp_plan_create(pnp_ctx ctx, int32_t count, pnp_request* reqs, const 
         if (reqs[r].status != PNP_OK) continue;
         const pnp_request& q = reqs[r];
         const long n3 = (long)q.grid.nx * q.grid.ny * q.grid.nz;
-        const int blocks = (int)std::min<long>((q.S * n3 + 255) / 256, 4096);
-        hipLaunchKernelGGL(k_relax, dim3(blocks), dim3(256), 0, cs, (double*)q.rho, (const double*)q.mu_ex, n3,
-                           (int)q.S, (const double*)(blk + rb_off[r]), relax[r].lambda, relax[r].clip,
+        hipLaunchKernelGGL(k_relax, update_grid(n3, q.S), dim3(256), 0, cs, (double*)q.rho, (const double*)q.mu_ex, n3,
+                           (const double*)(blk + rb_off[r]), relax[r].lambda, relax[r].clip,
                            (const uint32_t*)p->status[r], fixed_mask(q.S, q.species));
       }
     ctx->capturing = false;
@@ -1613,8 +1611,7 @@ pnp_status pnp_relax_densities(pnp_ctx ctx, const pnp_grid* g, int32_t S, const 
   const double* drb = (const double*)upload(ctx, rb, sizeof(double) * 2 * S, s);
   if (!drb) return device_check(ctx, "argument upload");
   const long n3 = (long)g->nx * g->ny * g->nz;
-  const int blocks = (int)std::min<long>((S * n3 + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_relax, dim3(blocks), dim3(256), 0, s, rho, mu, n3, (int)S, drb, lambda, clip,
+  hipLaunchKernelGGL(k_relax, update_grid(n3, S), dim3(256), 0, s, rho, mu, n3, drb, lambda, clip,
                      (const uint32_t*)nullptr, fixed_mask(S, sp));
   return device_check(ctx, "relax launch");
 }

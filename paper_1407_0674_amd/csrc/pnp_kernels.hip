@@ -553,6 +553,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     gp<uint32_t> st = gbl(a.status);
     st[0] = 0u;
     st[1] = 0xffffffffu;
+    st[2] = st[3] = 0u;
   }
   __syncthreads();
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;

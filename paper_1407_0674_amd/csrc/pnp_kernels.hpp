@@ -54,7 +54,8 @@ constexpr int64_t spec_pad(int n, int tsize) { return n >= 192 ? (tsize == 4 ? 4
 constexpr int64_t spec_plane(int n, int tsize) { return (int64_t)n * (n / 2) + spec_pad(n, tsize); }
 constexpr int64_t spec_fstride(int n, int tsize) { return n * spec_plane(n, tsize) + (int64_t)n * n; }
 
-// status word bits (word 0); word 1 holds the smallest offending flat index
+// status word bits (word 0); word 1 holds the smallest offending flat index,
+// words 2 and 3 the residual of a Picard step (a double's bit pattern)
 enum : uint32_t { kStPacking = 1u, kStNonFinite = 2u, kStOverflow = 4u };
 
 // Per-instance description read by every pass kernel (device resident).
@@ -85,7 +86,7 @@ struct EvalArgs {
   const void* pair_tab;  // [M][S][Sp]: entry [m][j][i] = combined pair kernel G_ij
   double* out;        // real output [nreal][n^3] (mu_ex or weighted densities)
   double* slot;       // [S][n^3] exp(-mu) or null
-  uint32_t* status;   // two words
+  uint32_t* status;   // four words, cleared by the first pass
   double* phi_part;   // per-workgroup sums of Phi_hs from the derivative pass, or null
   // aperiodic mode: the first pass reads an ext_n^3 domain [S][ext_n]^3 and
   // treats it as zero-extended onto the n^3 grid (domain at the corner); with

@@ -22,19 +22,27 @@ __global__ void __launch_bounds__(256) k_copy(const uint4* __restrict__ src, uin
   }
 }
 
+// Grid of the density updates over [S][n3]: one species per blockIdx.y, so no
+// thread divides a flat index by n3 (a 64-bit division per element costs more
+// than its memory traffic).
+inline dim3 update_grid(long n3, int S) {
+  const long b = (n3 + 255) / 256;
+  return dim3((unsigned)(b < 2048 ? b : 2048), (unsigned)S);
+}
+
 // relaxation of the consumer stub: rho <- (1 - l) rho + l rho_b exp(g),
 // g = mu_b - mu limited to [-clip, clip] when clip > 0
 // status: the evaluation's status word, or null; a raised status leaves rho
 // untouched (uniform over the grid)
 // fixed: bit s set = species s is stationary (its density is not touched)
-__global__ void k_relax(double* rho, const double* mu, long n3, int S, const double* rho_b_mu_b,
-                        double lambda, double clip, const uint32_t* status, uint32_t fixed) {
-  if (status && status[0] != 0u) return;
-  const long total = (long)S * n3;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int s = (int)(e / n3);
-    if ((fixed >> s) & 1u) continue;
-    const double rb = rho_b_mu_b[2 * s], mb = rho_b_mu_b[2 * s + 1];
+__global__ void k_relax(double* rho, const double* mu, long n3, const double* rho_b_mu_b, double lambda, double clip,
+                        const uint32_t* status, uint32_t fixed) {
+  const int s = blockIdx.y;
+  if ((status && status[0] != 0u) || ((fixed >> s) & 1u)) return;
+  const double rb = rho_b_mu_b[2 * s], mb = rho_b_mu_b[2 * s + 1];
+  rho += s * n3;
+  mu += s * n3;
+  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n3; e += (long)gridDim.x * blockDim.x) {
     double g = mb - mu[e];
     if (clip > 0.0) g = fmin(fmax(g, -clip), clip);
     rho[e] = (1.0 - lambda) * rho[e] + lambda * rb * exp(g);
@@ -94,15 +102,22 @@ __global__ void __launch_bounds__(256) k_energy_final(const double* phi_part, in
 // (integer max of such patterns is the max of the values: exact and
 // independent of the order of the updates).  Stationary species (bit s of
 // fixed) keep their densities and do not enter the residual.
-__global__ void __launch_bounds__(256) k_picard(double* rho, const double* mu, const double* beta_v, long n3, int S,
+// *res starts at 0 (the evaluation's first pass clears it).  Atomics on one
+// word take about 12 ns each, one after the other: a workgroup reduces first,
+// and leaves its atomic out when the word already holds as much (two species
+// at 48^3: 43 us with one atomic per wavefront, 6 us so).
+__global__ void __launch_bounds__(256) k_picard(double* rho, const double* mu, const double* beta_v, long n3,
                                                 const double* rb_mb, double lambda, unsigned long long* res,
                                                 uint32_t fixed) {
+  __shared__ double red[4];
+  const int s = blockIdx.y;
+  if ((fixed >> s) & 1u) return;  // uniform
+  const double rb = rb_mb[2 * s], mb = rb_mb[2 * s + 1];
+  rho += s * n3;
+  mu += s * n3;
+  if (beta_v) beta_v += s * n3;
   double r = 0.0;
-  const long total = (long)S * n3;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int s = (int)(e / n3);
-    if ((fixed >> s) & 1u) continue;
-    const double rb = rb_mb[2 * s], mb = rb_mb[2 * s + 1];
+  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n3; e += (long)gridDim.x * blockDim.x) {
     const double g = mb - mu[e] - (beta_v ? beta_v[e] : 0.0);
     const double old = rho[e];
     const double nw = (1.0 - lambda) * old + lambda * rb * exp(g);
@@ -111,7 +126,13 @@ __global__ void __launch_bounds__(256) k_picard(double* rho, const double* mu, c
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) r = fmax(r, __shfl_xor(r, o, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(res, (unsigned long long)__double_as_longlong(r));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = r;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    r = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(r);
+    if (bits > __hip_atomic_load(res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(res, bits);
+  }
 }
 
 // per-term mode: slot = exp(-(hs + el + sh))
