@@ -167,6 +167,9 @@ struct Derived {
 // 2 White Bear, 0 no hard-sphere term
 inline int hs_mask(const Derived& d) { return d.hs ? (d.wb ? 2 : 1) : 0; }
 
+// The status region: four words, the k = 0 parts of the results at 64 bytes.
+constexpr size_t kDcOffset = 64, kStatusBytes = kDcOffset + kMaxSpecies * sizeof(double);
+
 struct Layout {
   size_t status, energy, hs, pair, pair2, A, B, C, total;
   long fstride;
@@ -191,7 +194,7 @@ Layout layout_of(int n, int S, int precision, bool hs, bool pairs, bool per_term
   L.fstride = (long)spec_fstride(n, (int)ts);
   const size_t prow = (size_t)S * padded_species(S);
   size_t o = 0;
-  L.status = o; o = up(o + 64);
+  L.status = o; o = up(o + kStatusBytes);
   // free-energy partial sums: one per derivative-pass workgroup (at most n^2),
   // kEnergyBlocks pairs from the pair-energy pass, and the four results
   L.energy = o; o = up(o + sizeof(double) * ((size_t)n * n + 2 * kEnergyBlocks + 4));
@@ -346,6 +349,7 @@ void fill_eval_args(EvalArgs& e, const Derived& d, const pnp_species* sp, const 
   e.hs_tab = ws + L.hs;
   e.pair_tab = ws + L.pair;
   e.status = (uint32_t*)(ws + L.status);
+  e.dc = (double*)(ws + L.status + kDcOffset);
   e.final_mode = 1;
   e.nreal = d.S;
 }
@@ -474,13 +478,13 @@ constexpr SchedDefault kSchedDefault[] = {
     {8, passes({3, 7, 9}), passes({3, 7})},
     {16, passes({3, 4, 5, 6, 7, 8, 9}), passes({1, 3, 4, 6, 7, 9})},
     {24, passes({1, 4, 6, 9}), passes({1, 2, 4, 6, 8, 9})},
-    {32, passes({1, 2, 3, 4, 5, 6, 7, 8, 9}), passes({1, 2, 3, 4, 6, 8, 9})},
-    {48, passes({1, 9}), passes({1, 2, 6, 9})},
+    {32, passes({1, 2, 3, 4, 5, 6, 7, 8, 9}), passes({1, 2, 3, 4, 6, 7, 8, 9})},
+    {48, passes({1, 7, 9}), passes({1, 2, 6, 7, 9})},
     {64, passes({1, 2, 3, 4, 5, 6, 7, 8, 9}), passes({1, 2, 4, 6, 8, 9})},
-    {96, passes({1, 9}), passes({9})},
-    {128, passes({1, 2, 3, 4, 6, 8, 9}), passes({1, 2, 4, 6, 8, 9})},
-    {192, passes({1, 3, 7, 9}), passes({3, 9})},
-    {256, passes({1, 9}), passes({1, 9})},
+    {96, passes({1, 7, 9}), passes({7, 9})},
+    {128, passes({1, 2, 3, 4, 6, 7, 8, 9}), passes({1, 2, 4, 6, 7, 8, 9})},
+    {192, passes({1, 9}), passes({3, 7, 9})},
+    {256, passes({1, 3, 7, 9}), passes({1, 9})},
 };
 
 uint32_t default_sched(int precision, int n) {
@@ -488,18 +492,6 @@ uint32_t default_sched(int precision, int n) {
     if (d.n == n) return precision == PNP_MIXED ? d.mixed : d.fp64;
   return 0u;
 }
-
-// The full launch sequence for `count` instances of one size and precision.
-// Species counts of a launch list: the largest, and the largest among the
-// instances with at most four species (0: none), which select the back-pass
-// kernels.
-struct SpeciesMix {
-  int maxS = 1, small = 0;
-  void add(int S) {
-    maxS = std::max(maxS, S);
-    if (S <= 4) small = std::max(small, S);
-  }
-};
 
 inline SpeciesMix mix_of(int S) {
   SpeciesMix m;
@@ -573,13 +565,13 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
   // pass).
   bool tab_pending = false;
   if (!sp.on && tables) {
-    pt.begin(0); op.at(0)->tables(ta, count, M, sm.maxS, s); pt.end();
+    pt.begin(0); op.at(0)->tables(ta, count, M, sm.maxS(), s); pt.end();
   }
   pt.begin(1); op.at(1)->zfwd(ea, count, s); pt.end();
   sp.fork();
   if (sp.on && tables) {
     PassTimer ps{c, sp.nyq()};
-    ps.begin(0); op.at(0)->tables(ta, count, M, sm.maxS, sp.nyq()); ps.end();
+    ps.begin(0); op.at(0)->tables(ta, count, M, sm.maxS(), sp.nyq()); ps.end();
     tab_pending = true;
   }
   pt.begin(2); op.at(2)->ystep(ea, count, 0, -1, true, mp, s); pt.end();
@@ -589,8 +581,8 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
       sp.join();
       tab_pending = false;
     }
-    pt.begin(3); op.at(3)->xfwd(ea, count, mp, s); pt.end();
-    if (sp.on) op.at(3)->xfwd(ea, count, kPartNyquist, sp.nyq());
+    pt.begin(3); op.at(3)->xfwd(ea, count, sm, mp, s); pt.end();
+    if (sp.on) op.at(3)->xfwd(ea, count, sm, kPartNyquist, sp.nyq());
     pt.begin(4); op.at(4)->ystep(ea, count, 1, kVecMode, false, mp, s); pt.end();
     if (sp.on) op.at(4)->ystep(ea, count, 1, kVecMode, false, kPartNyquist, sp.nyq());
     sp.join();
@@ -601,8 +593,8 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
     if (sp.on) op.at(6)->ystep(ea, count, 1, kVecMode, true, kPartNyquist, sp.nyq());
   }
   if (tab_pending) sp.join();
-  pt.begin(7); op.at(7)->xback(ea, count, sm.small, sm.maxS > 4, mp, s); pt.end();
-  if (sp.on) op.at(7)->xback(ea, count, sm.small, sm.maxS > 4, kPartNyquist, sp.nyq());
+  pt.begin(7); op.at(7)->xback(ea, count, sm, mp, s); pt.end();
+  if (sp.on) op.at(7)->xback(ea, count, sm, kPartNyquist, sp.nyq());
   pt.begin(8); op.at(8)->ystep(ea, count, 2, -1, false, mp, s); pt.end();
   if (sp.on) op.at(8)->ystep(ea, count, 2, -1, false, kPartNyquist, sp.nyq());
   sp.join();
@@ -741,14 +733,15 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   if (d.sw) os.at(0)->tables(dta + 1, 1, L.M, S, s);
   pt.end();
   Split sq(ctx, s, d.n);
+  const SpeciesMix sm = mix_of(S);
   const int mp = sq.main_part();
   pt.begin(1); os.at(1)->zfwd(dea, 1, s); pt.end();
   sq.fork();
   pt.begin(2); os.at(2)->ystep(dea, 1, 0, -1, true, mp, s); pt.end();
   if (sq.on) os.at(2)->ystep(dea, 1, 0, -1, true, kPartNyquist, sq.nyq());
   if (d.hs) {
-    pt.begin(3); os.at(3)->xfwd(dea, 1, mp, s); pt.end();
-    if (sq.on) os.at(3)->xfwd(dea, 1, kPartNyquist, sq.nyq());
+    pt.begin(3); os.at(3)->xfwd(dea, 1, sm, mp, s); pt.end();
+    if (sq.on) os.at(3)->xfwd(dea, 1, sm, kPartNyquist, sq.nyq());
     pt.begin(4); os.at(4)->ystep(dea, 1, 1, kVecMode, false, mp, s); pt.end();
     if (sq.on) os.at(4)->ystep(dea, 1, 1, kVecMode, false, kPartNyquist, sq.nyq());
     sq.join();
@@ -758,8 +751,8 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
     if (sq.on) os.at(6)->ystep(dea, 1, 1, kVecMode, true, kPartNyquist, sq.nyq());
   }
   for (int k = 1; k < 4; ++k) {
-    pt.begin(7); os.at(7)->xback(dea + k, 1, S <= 4 ? S : 0, S > 4, mp, s); pt.end();
-    if (sq.on) os.at(7)->xback(dea + k, 1, S <= 4 ? S : 0, S > 4, kPartNyquist, sq.nyq());
+    pt.begin(7); os.at(7)->xback(dea + k, 1, sm, mp, s); pt.end();
+    if (sq.on) os.at(7)->xback(dea + k, 1, sm, kPartNyquist, sq.nyq());
     pt.begin(8); os.at(8)->ystep(dea + k, 1, 2, -1, false, mp, s); pt.end();
     if (sq.on) os.at(8)->ystep(dea + k, 1, 2, -1, false, kPartNyquist, sq.nyq());
     sq.join();
@@ -1130,7 +1123,7 @@ pnp_status pnp_weighted_densities(pnp_ctx ctx, const pnp_grid* g, int32_t S, con
   os.at(0)->tables(dta, 1, L.M, S, s);
   os.at(1)->zfwd(dea, 1, s);
   os.at(2)->ystep(dea, 1, 0, -1, true, kPartAll, s);
-  os.at(3)->xfwd(dea, 1, kPartAll, s);
+  os.at(3)->xfwd(dea, 1, mix_of(S), kPartAll, s);
   os.at(4)->ystep(dea, 1, 1, kVecMode, false, kPartAll, s);
   os.at(9)->zinv(dea, 1, 1, s);
   st = device_check(ctx, "launch");
@@ -1633,7 +1626,7 @@ pnp_status pnp_debug_rfft3(pnp_ctx ctx, const pnp_grid* g, int32_t precision, in
   EvalArgs ea;
   std::memset(&ea, 0, sizeof(ea));
   ea.n = n; ea.S = count; ea.fstride = L.fstride; ea.specA = w + L.A; ea.specC = w + L.A;
-  ea.status = (uint32_t*)(w + L.status); ea.rho = in; ea.out = out; ea.nreal = count; ea.final_mode = 0;
+  ea.status = (uint32_t*)(w + L.status); ea.dc = (double*)(w + L.status + kDcOffset); ea.rho = in; ea.out = out; ea.nreal = count; ea.final_mode = 0;
   const EvalArgs* dea = (const EvalArgs*)upload(ctx, &ea, sizeof(ea), s);
   if (!dea) return device_check(ctx, "argument upload");
   if (!inverse) {

@@ -82,6 +82,13 @@ constexpr int alt_ept(int len, int prim, int per, bool dbl = false) {
                                                                        : prim;
 }
 
+// Elements per thread of the streamed x passes (primary schedule).
+template <typename T, int N> constexpr int default_ex() {
+  if (N % 3 == 0) return N >= 48 ? 12 : 6;
+  if (sizeof(T) == 4) return N >= 128 ? 16 : 8;
+  return N >= 128 ? 8 : 4;
+}
+
 template <typename T, int N, int V = 0> struct Geo {
   static constexpr int H = N / 2;
   static constexpr bool R3 = (N % 3 == 0);
@@ -98,9 +105,18 @@ template <typename T, int N, int V = 0> struct Geo {
   static constexpr int TY = N / EY;
   // x passes
   static constexpr int PX = narrow(pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), V);
-  static constexpr int EX0 = R3 ? 6 : (sizeof(T) == 4 ? (N >= 8 ? 8 : N) : (N >= 4 ? 4 : N));
+  static constexpr int EX0 = default_ex<T, N>();
   static constexpr int EX = SEC ? alt_ept(N, EX0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EX0;
   static constexpr int TX = N / EX;
+  // the x passes that hold accumulators in registers (k_xfwd_acc and the
+  // chunked back pass), which leave less room
+  static constexpr int EXG0 = R3 ? 6 : (sizeof(T) == 4 ? 8 : 4);
+  static constexpr int EXG = SEC ? alt_ept(N, EXG0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EXG0;
+  // whether the forward pass is the streamed kernel (see k_xfwd_acc)
+  static constexpr bool kXStream = sizeof(T) == 4 && N >= 128;
+  // the streamed x passes: the largest species count on EX elements per
+  // thread, and the elements per thread of four species where that is three
+  static constexpr int kXMax = N >= 256 ? 3 : 4;
   // tiles per instance
   static constexpr int tiles_z = (N * N) / RZ;
   static constexpr int tiles_y = (N * H) / PY + N / PY;
@@ -554,6 +570,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     st[0] = 0u;
     st[1] = 0xffffffffu;
     st[2] = st[3] = 0u;
+    for (int s = 0; s < a.S; ++s) gbl(a.dc)[s] = 0.0;
   }
   __syncthreads();
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;
@@ -623,9 +640,12 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   constexpr uint32_t n3b = n3 * sizeof(double);
   const BufN<N> out = make_buf<stream_policy<N>()>(a.out, (uint64_t)a.nreal * n3b);
   const BufN<N> slot = make_buf<stream_policy<N>()>(a.slot, a.slot ? (uint64_t)a.nreal * n3b : 0);
+  const Buf dcb = make_buf(a.dc, a.final_mode ? kMaxSpecies * sizeof(double) : 0);
   uint32_t bad = 0u, badidx = 0xffffffffu;
   for (int s = 0; s < a.nreal; ++s) {
     cx<T> v[EZ], xk[EZ], xm[EZ];
+    // in flight with the row (the buffer is empty for a plain real output)
+    const double dc = dcb.template ld<double>((uint32_t)s * (uint32_t)sizeof(double));
     // weighted-density output: the z components of the vector densities are
     // i s_z [6] and i s_z k0 [3] (see the field-slot layout)
     const bool zmul = (a.zmul_mask >> s) & 1u, grad = zmul && s == kFieldZ2;
@@ -641,7 +661,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     fft_pencil<T, H, EZ, false>(v, t, twH, lp);
     const uint32_t so = (uint32_t)s * n3b;
     if (a.final_mode) {
-      const double c = a.cfin[s];
+      const double c = a.cfin[s] + dc;
 #pragma unroll
       for (int m = 0; m < EZ; ++m) {
         const uint32_t j = row * H + t + TZ * m;  // index of the point pair (2j, 2j+1)
@@ -1309,6 +1329,7 @@ __device__ __forceinline__ T s_axis(int k) {
 __device__ __forceinline__ constexpr int back_field(int q) {
   return q < 3 ? q : q == 3 ? kSlotX : q == 4 ? kSlotZ : q == 5 ? kSlotN3 : kSlotX + kVecStride;
 }
+static_assert(back_field(5) == kSlotN3, "the k = 0 sum of the streamed back pass reads it there");
 
 // Per-lane addressing of an x tile: element m of the lane's pencil sits at
 // byte vo + m * mstride (+ the field offset).  Both strides are uniform over
@@ -1323,19 +1344,167 @@ struct XAddr {
   }
 };
 
-// The x passes exchange through two LDS buffers in turn (LdsPencil2): one
-// workgroup barrier per FFT stage instead of two (measured at 256^3: x
-// forward 257 -> 241 us, back pass 353 -> 332 us).
+// The streamed x passes (P3 and P7 for S <= CH <= 4).
 //
+// A pencil group transforms S + 7 spectra each way, and the pass is bound by
+// memory only if a compute unit works on two groups at once: with one (the
+// former layout: 512 threads, two exchange buffers and 114 KB of LDS at 256^3)
+// its loads, LDS exchanges and arithmetic took turns at the barriers, at
+// 46 % (forward) and 40 % (back) of 8 TB/s.  Hence
+//  * many elements per thread (16 in FP32: two radix-16 stages and one
+//    exchange at 256^3), so that a group is 256 threads of at most 256
+//    registers;
+//  * one exchange buffer, of real parts only where it has to be half as large
+//    (SPLIT), beside the weights: at most 80 KB per group;
+//  * the weights (j0, w3) of all species at the N / 2 + 1 distinct |s_x| of
+//    each pencil in LDS, made once per group (FP32: evaluated; FP64: gathered
+//    from the table) while the first pencils are in flight, and read per use,
+//    so that the registers hold the S species (forward) or the S results
+//    (back) and no accumulators of the derivative fields.
+template <typename T, int N, int PX, int CH>
+struct XWeights {
+  static constexpr int W = N / 2 + 1;
+  static constexpr int count = CH * W * PX;
+  // fill for the thread's pencil (lane p of PX) with threads t of TX
+  template <int TX>
+  static __device__ __forceinline__ void fill(cx<T>* wl, const EvalArgs& a, const Buf& hs, int S, int t, int p, int ky,
+                                              int kz) {
+    const int sy = sgn_idx(ky, N), m0 = sy * sy + kz * kz;
+#pragma unroll 2
+    for (int sx = t; sx < W; sx += TX) {
+      const int m = sx * sx + m0;
+      const T k = sizeof(T) == 4 ? (T)a.kscale * __builtin_sqrtf((float)m) : (T)0;
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (c < S) {  // uniform
+          cx<T> w;
+          if constexpr (sizeof(T) == 4) {
+            float j0, w3;
+            hs_weights_f32<true>(k, (float)a.R[c], j0, w3);
+            w = mk<T>(j0, w3);
+          } else w = hs.template ld<cx<T>>((uint32_t)(m * S + c) * (uint32_t)sizeof(cx<T>));
+          wl[(c * W + sx) * PX + p] = w;
+        }
+    }
+  }
+  // (j0, w3) of species c at element m of thread t (kx = t + TX m)
+  template <int TX>
+  static __device__ __forceinline__ cx<T> at(const cx<T>* wl, int c, int m, int t, int p) {
+    const int kx = t + TX * m;
+    return wl[(c * W + (2 * TX * m >= N ? N - kx : kx)) * PX + p];
+  }
+};
+
+// Exchange buffers of a streamed x pass: two in turn (one barrier per
+// exchange) up to 96^3, whose launches leave room for them beside the few
+// groups that each compute unit gets and whose time is the latency of the
+// barriers (S = 3 mixed back pass at 64^3: 18.2 us with one buffer, 15.2 us
+// with two); above, one, of real parts only (kXSplit) where two groups per
+// compute unit need that.
+enum : int { kXSplit = 0, kXOne = 1, kXTwo = 2 };
+template <typename T, int N, int PX, int CH>
+constexpr int x_buffers() {
+  constexpr size_t w = sizeof(cx<T>) * (size_t)(CH * (N / 2 + 1) * PX + N), x = sizeof(cx<T>) * (size_t)PX * N;
+  return N <= 96 ? kXTwo : w + x > 81920 && w + x / 2 <= 81920 ? kXSplit : kXOne;
+}
+template <typename T, int N, int PX, int B> struct XView {
+  static constexpr int size = B == kXTwo ? 4 * PX * N : B == kXOne ? 2 * PX * N : PX * N;  // values of T
+  using type = typename std::conditional<B == kXTwo, LdsPencil2<T>,
+                                         typename std::conditional<B == kXOne, LdsPencil<T>, LdsPencilSplit<T>>::type>::type;
+  static __device__ __forceinline__ type make(T* b, int p) {
+    if constexpr (B == kXTwo) return type{(cx<T>*)b + p, (cx<T>*)b + PX * N + p, PX};
+    else if constexpr (B == kXOne) return type{(cx<T>*)b + p, PX};
+    else return type{b + p, PX};
+  }
+};
+
 // P3: forward weights.  For every k: n^_a(k) = sum_i rho^_i(k) conj(w^_i^a(k))
 // (correlation, Sec. 2.3.1); scalars w0 = j0, w1 = R j0, w2 = 4 pi R^2 j0,
 // w3 = 4 pi R^3 j1(kR)/(kR); vectors conj(-i khat V2) = +i k w3 and the same
 // over 4 pi R (the field-slot layout).
-// The species pencils stream through two register buffers: the loads of
-// species i + 1 are in flight while species i is transformed.
-template <typename T, int N, int EX = Geo<T, N>::EX, int PX = Geo<T, N>::PX>
+// lo: instances with fewer than lo or more than CH species belong to another
+// kernel of the same launch list and are skipped here.
+template <typename T, int N, int CH, int EX, int PX>
+__global__ void __launch_bounds__((PX * (N / EX)), 2)
+    k_xfwd(const EvalArgs* __restrict__ args, int lo, int part) {
+  constexpr int TX = N / EX;
+  using XV = XView<T, N, PX, x_buffers<T, N, PX, CH>()>;
+  using XW = XWeights<T, N, PX, CH>;
+  __shared__ cx<T> tw[N];
+  __shared__ __align__(16) T xch[XV::size];
+  __shared__ cx<T> wl[XW::count];
+  int tile;
+  const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
+  const int S = a.S;
+  if (!a.hs_on || S < lo || S > CH) return;  // uniform per block
+  const int p = threadIdx.x % PX, t = threadIdx.x / PX;
+  const XPencil<T, N, PX> pc(tile, p);
+  const auto lp = XV::make(xch, p);
+  const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(cx<T>) : 0);
+  const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
+  const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
+  const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
+  const XAddr<T, N, EX, PX> xa(pc, t);
+  // the pencils of all species are in flight while the tables are made
+  cx<T> r[CH][EX];
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if (c < S) {  // uniform
+#pragma unroll
+      for (int m = 0; m < EX; ++m) r[c][m] = A.template ld<cx<T>>(xa.vo, (uint32_t)c * fbytes + m * xa.mstride);
+    }
+  XW::template fill<TX>(wl, a, hs, S, t, p, pc.ky, pc.kz);
+  init_twiddles<T, N>(tw);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if (c < S) fft_pencil<T, N, EX, true>(r[c], t, tw, lp);
+  const T sc = (T)a.inv_n3;
+  // outputs: n0, n1, n2 from j0; n3 and its [x] component, Q and its [x]
+  // component from w3 (the y and z components are formed by the y and z passes)
+#pragma unroll
+  for (int o = 0; o < kBackFields; ++o) {
+    constexpr int slots[kBackFields] = {0, 1, 2, kSlotN3, kSlotX + kVecStride, kSlotZ, kSlotX};
+    cx<T> v[EX];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+      if (c < S) {
+        const T f = sc * (o == 0 ? (T)1 : o == 1 ? (T)a.R[c] : o == 2 ? (T)a.area[c] : o < 5 ? (T)1
+                                                                                    : (T)(a.inv4piR[c] * a.kscale));
+#pragma unroll
+        for (int m = 0; m < EX; ++m) {
+          const cx<T> w = XW::template at<TX>(wl, c, m, t, p);
+          const T g = (o < 3 ? w.x : w.y) * f;
+          if (c == 0) v[m] = cscale<T>(r[c][m], g);
+          else cfma<T>(v[m], r[c][m], g);
+        }
+      }
+    if (o == 4 || o == 6) {
+      const T f = o == 4 ? (T)a.kscale : (T)1;
+#pragma unroll
+      for (int m = 0; m < EX; ++m) v[m] = cmuli<T>(cscale<T>(v[m], f * s_axis<T, N>(t + TX * m)));
+    }
+    fft_pencil<T, N, EX, false>(v, t, tw, lp);
+#pragma unroll
+    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)slots[o] * fbytes + m * xa.mstride);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// P3 with the five spectra (n0..n3, Q) as accumulators in registers; the
+// species pencils stream through two register buffers (the loads of species
+// i + 1 are in flight while species i is transformed).  Any species count.
+// Against the streamed kernel, which reads the weights once per output
+// instead of once per species but needs fewer elements per compute unit in
+// registers (three species): better in FP64 (128^3: 45 against 56 us; 192^3:
+// 162 against 185 us) and below 128^3 in FP32 (64^3: 14.3 against 15.2 us);
+// worse from 128^3 on in FP32 (192^3: 106 against 88 us, 256^3: 181 against
+// 176 us), where only one of its groups fits a compute unit.
+// min_s: instances with fewer species run the streamed kernel of the same
+// launch list and are skipped here (1: every instance runs here).
+template <typename T, int N, int EX, int PX>
 __global__ void __launch_bounds__((PX * (N / EX)))
-    k_xfwd(const EvalArgs* __restrict__ args, int part) {
+    k_xfwd_acc(const EvalArgs* __restrict__ args, int min_s, int part) {
   constexpr int TX = N / EX;
   __shared__ cx<T> tw[N];
   __shared__ cx<T> xch[2 * PX * N];
@@ -1350,7 +1519,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   __shared__ WPair wall[sizeof(T) == 4 ? 3 * kRegion + 3 * PX : 1];
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
-  if (!a.hs_on) return;  // uniform per block
+  if (!a.hs_on || a.S < min_s) return;  // uniform per block
   const int p = threadIdx.x % PX, t = threadIdx.x / PX;
   const XPencil<T, N, PX> pc(tile, p);
   const LdsPencil2<T> lp{xch + p, xch + PX * N + p, PX};
@@ -1485,33 +1654,28 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 //   mu^_i = j0_i (F0 + R_i F1 + 4 pi R_i^2 F2)
 //           + w3_i (F3 - k0 i s.F_2v - k0 i s.F_1v / (4 pi R_i)) + sum_j G_ij rho^_j,
 // with F_a the derivative spectra and k = k0 s (the field-slot layout).
-// For S <= CH <= 4: the seven derivative pencils and then the S density pencils
-// stream through two register buffers (the next pencil, and the next pair-
-// table row, are in flight during each transform); the derivative spectra
-// fold into the CH outputs before the density phase starts.
-// Instances with more species than CH belong to the chunked kernel of the
-// same launch list and are skipped here.
-template <typename T, int N, int CH, int EX = Geo<T, N>::EX, int PX = Geo<T, N>::PX>
-__global__ void __launch_bounds__((PX * (N / EX)))
-    k_xback(const EvalArgs* __restrict__ args, int part) {
+// The seven derivative pencils and then the S density pencils stream through
+// two register buffers (the next pencil is in flight during each transform)
+// into the results.
+// lo: instances with fewer than lo or more than CH species belong to another
+// kernel of the same launch list and are skipped here.
+template <typename T, int N, int CH, int EX, int PX>
+__global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <= 3 ? 4 : 2)
+    k_xback(const EvalArgs* __restrict__ args, int lo, int part) {
   static_assert(CH >= 1 && CH <= 4, "output chunk");
   constexpr int TX = N / EX;
+  using XV = XView<T, N, PX, x_buffers<T, N, PX, CH>()>;
+  using XW = XWeights<T, N, PX, CH>;
   __shared__ cx<T> tw[N];
-  __shared__ cx<T> xch[2 * PX * N];
+  __shared__ __align__(16) T xch[XV::size];
+  __shared__ cx<T> wl[XW::count];
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
-  // FP32 with at most three outputs: the weights of every output species for
-  // the first half of each thread's elements (and the column kx = N/2 of
-  // thread 0), evaluated while the first pencil loads are in flight; an
-  // element's other half is its mirror's (see x_weights_shared)
-  constexpr bool kPre = sizeof(T) == 4 && CH <= 3;
-  constexpr int EH = EX / 2;
-  __shared__ WPair wpre[kPre ? CH * EH * TX * PX + CH * PX : 1];
-  if (a.S > CH) return;  // uniform per block
+  const int S = a.S;
+  if (S < lo || S > CH) return;  // uniform per block
   const int p = threadIdx.x % PX, t = threadIdx.x / PX;
   const XPencil<T, N, PX> pc(tile, p);
-  const LdsPencil2<T> lp{xch + p, xch + PX * N + p, PX};
-  const int S = a.S;
+  const auto lp = XV::make(xch, p);
   const bool hs_on = a.hs_on, pair_on = a.pair_on;
   const Buf hs = make_buf(a.hs_tab, sizeof(T) == 8 ? table_m<T, N>(0) * S * sizeof(cx<T>) : 0);
   const Buf pt = make_buf(a.pair_tab, pair_on ? table_m<T, N>(0) * S * a.Sp * sizeof(T) : 0);
@@ -1520,50 +1684,50 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   const BufN<N> C = make_buf<stream_policy<N>()>(a.specC, spec_bytes<T>(a, S));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
   const XAddr<T, N, EX, PX> xa(pc, t);
-  int mm[EX];
-  {
-    const int sy = sgn_idx(pc.ky, N), sz = pc.kz;
-#pragma unroll
-    for (int m = 0; m < EX; ++m) {
-      const int sx = sgn_idx(t + TX * m, N);
-      mm[m] = sx * sx + sy * sy + sz * sz;
-    }
-  }
   cx<T> out[CH][EX];
   cx<T> b0[EX], b1[EX];
-  // the first pencil of the stream is in flight while the twiddle table is built
+  // FP32: the k = 0 coefficient of each result is summed in double by the
+  // lane that owns it, left out of the transform and added by the last pass
+  // in double (a.dc): an error in it is an error of the whole field, and the
+  // field without it is smaller, so its rounding is too.
+  constexpr bool kDc = sizeof(T) == 4;
+  __shared__ T dcv[kBackFields + CH + 1];  // the k = 0 coefficients of the pencils
+  const bool own0 = kDc && tile == 0 && threadIdx.x == 0;
+  // Up to 96^3 no branch separates one transform from the next (every lane
+  // stores, the others into the last word; results past S are summed but
+  // never stored: 64^3 back pass 16.5 -> 15.9 us).  On larger grids the
+  // branches keep the scheduler from holding two fields' work in registers
+  // (256^3, without them 309 instead of 247 us).
+  constexpr bool kFree = N <= 96;
+  auto keep0 = [&](int q, T x) {
+    if constexpr (kDc && kFree) dcv[own0 ? q : kBackFields + CH] = x;
+    else if (own0) dcv[q] = x;
+  };
+  // the first pencil of the stream is in flight while the tables are made
   if (hs_on) {
 #pragma unroll
     for (int m = 0; m < EX; ++m) b0[m] = B.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
+    XW::template fill<TX>(wl, a, hs, S, t, p, pc.ky, pc.kz);
   } else if (pair_on) {
 #pragma unroll
     for (int m = 0; m < EX; ++m) b1[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
   }
-  if constexpr (kPre) {
-    if (hs_on) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const float R = (float)a.R[c < S ? c : 0];
-#pragma unroll
-        for (int e = 0; e < EH; ++e) {
-          WPair w;
-          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[e]), R, w.j0, w.w3);
-          wpre[((c * EH + e) * TX + t) * PX + p] = w;
-        }
-        if (t == 0) {
-          WPair w;
-          hs_weights_f32<true>((float)a.kscale * __builtin_sqrtf((float)mm[EH]), R, w.j0, w.w3);
-          wpre[CH * EH * TX * PX + c * PX + p] = w;
-        }
-      }
-    }
-  }
   init_twiddles<T, N>(tw);
   __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int m = 0; m < EX; ++m) out[c][m] = mk<T>((T)0, (T)0);
   if (hs_on) {
-    // F[0..2]: scalar derivative spectra; F[3] = [3] - i s_x k0 [7], the
-    // spectrum that w3 multiplies; F[4] = i s_x [4] + [6] (vector 1)
-    cx<T> F[5][EX];
+    // the thread's weights in registers where they fit (small grids)
+    constexpr bool kWReg = N <= 96 && CH * EX * sizeof(T) <= 96;
+    cx<T> wr[kWReg ? CH : 1][kWReg ? EX : 1];
+    if constexpr (kWReg) {
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int m = 0; m < EX; ++m) wr[c][m] = XW::template at<TX>(wl, c, m, t, p);
+    }
 #pragma unroll
     for (int q = 0; q < kBackFields; ++q) {
       cx<T>* cur = (q & 1) ? b1 : b0;
@@ -1573,65 +1737,39 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
         for (int m = 0; m < EX; ++m) nxt[m] = B.template ldnt<cx<T>>(xa.vo, (uint32_t)f1 * fbytes + m * xa.mstride);
       } else if (pair_on) {
-        // the first density pencil is in flight during the last transform and the fold
+        // the first density pencil is in flight during the last transform
 #pragma unroll
         for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
       }
       fft_pencil<T, N, EX, true>(cur, t, tw, lp);
       const int f = back_field(q);
+      // [4] and [7] are x components: i s_x times the field
+      if (f == kSlotX || f == kSlotX + kVecStride) {
 #pragma unroll
-      for (int m = 0; m < EX; ++m) {
-        if (f == kSlotX) F[4][m] = cscale<T>(cmuli<T>(cur[m]), s_axis<T, N>(t + TX * m));
-        else if (f == kSlotZ) F[4][m] = cadd<T>(F[4][m], cur[m]);
-        else if (f == kSlotX + kVecStride) cfma<T>(F[3][m], cmulmi<T>(cur[m]), s_axis<T, N>(t + TX * m) * (T)a.kscale);
-        else F[f][m] = cur[m];
+        for (int m = 0; m < EX; ++m) cur[m] = cscale<T>(cmuli<T>(cur[m]), s_axis<T, N>(t + TX * m));
       }
-    }
+      keep0(q, cur[0].x);
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int i = c < S ? c : 0;
-      const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)(a.inv4piR[i] * a.kscale);
+      for (int c = 0; c < CH; ++c)
+        if (kFree || c < S) {
+          const T g = f == 0 ? (T)1 : f == 1 ? (T)a.R[c] : f == 2 ? (T)a.area[c] : f == kSlotN3 ? (T)1
+                      : f == kSlotX + kVecStride ? -(T)a.kscale : -(T)(a.inv4piR[c] * a.kscale);
 #pragma unroll
-      for (int m = 0; m < EX; ++m) {
-        T j0, w3;
-        if constexpr (kPre) {
-          // own slot, the mirror's slot, or thread 0's column kx = N/2
-          const int tm = t == 0 ? 0 : TX - t;
-          const int em = t == 0 ? EX - m : EX - 1 - m;
-          const int idx = m < EH ? ((c * EH + m) * TX + t) * PX + p
-                          : (t == 0 && m == EH) ? CH * EH * TX * PX + c * PX + p
-                                                : ((c * EH + em) * TX + tm) * PX + p;
-          const WPair w = wpre[idx];
-          j0 = w.j0; w3 = w.w3;
-        } else {
-          hs_weights<T>(a, hs, S, i, mm[m], j0, w3);
+          for (int m = 0; m < EX; ++m) {
+            if (EX > 8 && m % 8 == 0) __builtin_amdgcn_sched_barrier(0);  // few weights in registers at a time
+            const cx<T> w = kWReg ? wr[kWReg ? c : 0][kWReg ? m : 0] : XW::template at<TX>(wl, c, m, t, p);
+            cfma<T>(out[c][m], cur[m], (f < 3 ? w.x : w.y) * g);
+          }
         }
-        cx<T> s0 = F[0][m];
-        cfma<T>(s0, F[1][m], R);
-        cfma<T>(s0, F[2][m], ar);
-        cx<T> u = cscale<T>(s0, j0);
-        cx<T> w = F[3][m];
-        cfma<T>(w, F[4][m], -i4);
-        cfma<T>(u, w, w3);
-        out[c][m] = u;
-      }
-      // one species at a time: hoisting the weights of later species ahead
-      // (they do not depend on F) would keep them live beside F and spill
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (EX > 8) __builtin_amdgcn_sched_barrier(0);
     }
-  } else {
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-      for (int m = 0; m < EX; ++m) out[c][m] = mk<T>((T)0, (T)0);
   }
   // the density stream starts in b1: without HS it was loaded at the start;
   // with HS after the last of the (odd number of) derivative fields, into
   // the buffer that field left free
   static_assert(kBackFields % 2 == 1, "the density stream continues in b1");
-  if (pair_on && sizeof(T) == 8) {
-    // FP64: pair-table rows gathered after each transform (two buffers of
-    // double rows would not fit the register budget)
+  if (pair_on) {
+    const int sy = sgn_idx(pc.ky, N), m0 = sy * sy + pc.kz * pc.kz;
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       if (j < S) {  // uniform
@@ -1641,10 +1779,25 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 #pragma unroll
           for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, (uint32_t)(j + 1) * fbytes + m * xa.mstride);
         }
+        // G_{0..3, j} of row [m][j][.]: one gather per element, issued before
+        // the transform where the registers hold them, else eight at a time
+        // after it
+        auto gather = [&](int m) {
+          const int sx = sgn_idx(t + TX * m, N);
+          return pt.template ld<v4<T>>((uint32_t)(((sx * sx + m0) * S + j) * a.Sp) * (uint32_t)sizeof(T));
+        };
+        constexpr bool kEarly = N <= 96 && EX * sizeof(T) <= 32;
+        v4<T> ge[kEarly ? EX : 1];
+        if constexpr (kEarly) {
+#pragma unroll
+          for (int m = 0; m < EX; ++m) ge[m] = gather(m);
+        }
         fft_pencil<T, N, EX, true>(cur, t, tw, lp);
+        keep0(kBackFields + j, cur[0].x);
 #pragma unroll
         for (int m = 0; m < EX; ++m) {
-          const v4<T> g = pt.template ld<v4<T>>((uint32_t)((mm[m] * S + j) * a.Sp) * (uint32_t)sizeof(T));
+          if (EX > 8 && m % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+          const v4<T> g = kEarly ? ge[kEarly ? m : 0] : gather(m);
           cfma<T>(out[0][m], cur[m], g.x);
           if constexpr (CH > 1) cfma<T>(out[1][m], cur[m], g.y);
           if constexpr (CH > 2) cfma<T>(out[2][m], cur[m], g.z);
@@ -1652,42 +1805,36 @@ __global__ void __launch_bounds__((PX * (N / EX)))
         }
       }
     }
-  } else if (pair_on) {
-    // G_{0..3, j} of row [m][j][.]: one gather per element, issued before the
-    // transform of the same species' pencil (its latency hides behind it)
-    v4<T> g[EX];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      if (j < S) {  // uniform
-        cx<T>* cur = (j & 1) ? b0 : b1;
-        cx<T>* nxt = (j & 1) ? b1 : b0;
-        if (j + 1 < S) {
-#pragma unroll
-          for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, (uint32_t)(j + 1) * fbytes + m * xa.mstride);
-        }
-#pragma unroll
-        for (int m = 0; m < EX; ++m) g[m] = pt.template ld<v4<T>>((uint32_t)((mm[m] * S + j) * a.Sp) * (uint32_t)sizeof(T));
-        fft_pencil<T, N, EX, true>(cur, t, tw, lp);
-#pragma unroll
-        for (int m = 0; m < EX; ++m) {
-          cfma<T>(out[0][m], cur[m], g[m].x);
-          if constexpr (CH > 1) cfma<T>(out[1][m], cur[m], g[m].y);
-          if constexpr (CH > 2) cfma<T>(out[2][m], cur[m], g[m].z);
-          if constexpr (CH > 3) cfma<T>(out[3][m], cur[m], g[m].w);
-        }
+  }
+  if (own0) {
+    // j0 = 1, w3 = 4 pi R^3 / 3 and the pair rows at k = 0; the vector fields
+    // have no part there (s = 0)
+    gp<double> g = gbl(a.dc);
+#pragma unroll 1
+    for (int c = 0; c < S; ++c) {
+      double d = 0.0;
+      if (hs_on) {
+        const double R = a.R[c], ar = a.area[c];
+        d = (double)dcv[0] + R * (double)dcv[1] + ar * (double)dcv[2] + ar * R / 3.0 * (double)dcv[5];
       }
+      if (pair_on)
+#pragma unroll 1
+        for (int j = 0; j < S; ++j)
+          d += (double)pt.template ld<T>((uint32_t)(j * a.Sp + c) * (uint32_t)sizeof(T)) * (double)dcv[kBackFields + j];
+      g[c] = d * a.inv_n3;
     }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) out[c][0] = mk<T>((T)0, (T)0);
   }
   const T sc = (T)a.inv_n3;
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     if (c < S) {  // uniform
-      cx<T> v[EX];
 #pragma unroll
-      for (int m = 0; m < EX; ++m) v[m] = cscale<T>(out[c][m], sc);
-      fft_pencil<T, N, EX, false>(v, t, tw, lp);
+      for (int m = 0; m < EX; ++m) out[c][m] = cscale<T>(out[c][m], sc);
+      fft_pencil<T, N, EX, false>(out[c], t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EX; ++m) C.template st<cx<T>>(v[m], xa.vo, (uint32_t)c * fbytes + m * xa.mstride);
+      for (int m = 0; m < EX; ++m) C.template st<cx<T>>(out[c][m], xa.vo, (uint32_t)c * fbytes + m * xa.mstride);
     }
   }
 }
@@ -1696,8 +1843,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 // (the derivative spectra stay in registers; each chunk re-streams the
 // density pencils).
 // min_s: instances with fewer species run the streamed kernel of the same
-// launch list and are skipped here (1: every instance runs here).
-template <typename T, int N, int CH, int EX = Geo<T, N>::EX, int PX = Geo<T, N>::PX>
+// launch list and are skipped here.
+template <typename T, int N, int CH, int EX, int PX>
 __global__ void __launch_bounds__((PX * (N / EX)))
     k_xback_chunked(const EvalArgs* __restrict__ args, int min_s, int part) {
   static_assert(CH >= 1 && CH <= 4, "output chunk");
@@ -1731,7 +1878,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   uint32_t eo[EX];
 #pragma unroll
   for (int m = 0; m < EX; ++m) eo[m] = (pc.off + (uint32_t)(t + TX * m) * pc.es) * (uint32_t)sizeof(cx<T>);
-  cx<T> F[5][EX];  // as in k_xback
+  cx<T> F[5][EX];  // n0..n2, [3] - i s_x k0 [7], i s_x [4] + [6]
 #pragma unroll
   for (int q = 0; q < 5; ++q)
 #pragma unroll

@@ -87,6 +87,8 @@ struct EvalArgs {
   double* out;        // real output [nreal][n^3] (mu_ex or weighted densities)
   double* slot;       // [S][n^3] exp(-mu) or null
   uint32_t* status;   // four words, cleared by the first pass
+  double* dc;         // [S] k = 0 part of each result where the back pass sums it in
+                      // double (FP32, up to four species); cleared by the first pass
   double* phi_part;   // per-workgroup sums of Phi_hs from the derivative pass, or null
   // aperiodic mode: the first pass reads an ext_n^3 domain [S][ext_n]^3 and
   // treats it as zero-extended onto the n^3 grid (domain at the corner); with

@@ -11,13 +11,28 @@
 
 namespace pnp {
 
+// The species counts of a launch list (they select the x-pass kernels).
+struct SpeciesMix {
+  uint32_t mask = 0;  // bit S set: some instance has S species
+  void add(int S) { mask |= 1u << S; }
+  bool has(int S) const { return (mask >> S) & 1u; }
+  // the largest count up to hi (0: none)
+  int upto(int hi) const {
+    int m = 0;
+    for (int S = 1; S <= hi; ++S)
+      if (has(S)) m = S;
+    return m;
+  }
+  int maxS() const { return upto(kMaxSpecies); }
+};
+
 struct Ops {
   void (*tables)(const TableArgs*, int, int, int, hipStream_t);
   void (*zfwd)(const EvalArgs*, int, hipStream_t);
   void (*ystep)(const EvalArgs*, int, int, int, bool, int, hipStream_t);  // count, sel, nf, fwd, part
-  void (*xfwd)(const EvalArgs*, int, int, hipStream_t);                   // count, part
+  void (*xfwd)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);   // count, species, part
   void (*zderiv)(const EvalArgs*, int, bool, int, hipStream_t);
-  void (*xback)(const EvalArgs*, int, int, bool, int, hipStream_t);  // count, smax, large, part
+  void (*xback)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);  // count, species, part
   int zderiv_tiles;  // workgroups of the derivative pass per instance
   void (*zinv)(const EvalArgs*, int, int, hipStream_t);
   void (*xplain)(const EvalArgs*, int, int, bool, hipStream_t);

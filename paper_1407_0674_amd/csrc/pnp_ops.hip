@@ -36,6 +36,10 @@ template <typename T, int N, int V = 0> struct Launch {
   // part: kPartAll, kPartMain (main-array tiles) or kPartNyquist (Nyquist-plane tiles)
   static int tiles_y(int part) { return part == kPartAll ? G::tiles_y : part == kPartMain ? (N * G::H) / G::PY : N / G::PY; }
   static int tiles_x(int part) { return part == kPartAll ? G::tiles_x : part == kPartMain ? (N * G::H) / G::PX : N / G::PX; }
+  // the general x passes keep the same pencils per workgroup
+  static constexpr int TXG = N / G::EXG;
+  static constexpr bool four = G::kXMax < 4;
+  static constexpr int EX4 = G::EX > 8 ? 8 : G::EX > 4 ? 4 : G::EX;  // of four species where kXMax is three
   static void ystep(const EvalArgs* a, int count, int sel, int nf, bool fwd, int part, hipStream_t s) {
     const dim3 g(count * tiles_y(part)), b(G::PY * G::TY);
     if (fwd)
@@ -43,9 +47,27 @@ template <typename T, int N, int V = 0> struct Launch {
     else
       hipLaunchKernelGGL((k_ystep<T, N, false, V>), g, b, 0, s, a, sel, nf, part);
   }
-  static void xfwd(const EvalArgs* a, int count, int part, hipStream_t s) {
-    hipLaunchKernelGGL((k_xfwd<T, N, G::EX, G::PX>), dim3(count * tiles_x(part)), dim3(G::PX * G::TX), 0, s, a,
-                       part);
+  // The x passes of a launch list: the streamed kernels for up to kXMax
+  // species (compiled for the largest such count in the list; an instance's
+  // arithmetic does not depend on it), the accumulating ones above; at 256^3
+  // the back pass of four species is a streamed kernel of its own (16 elements
+  // per thread would not fit its registers).  Each skips the others' instances.
+  static void xfwd(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
+    const dim3 g(count * tiles_x(part)), b(G::PX * G::TX);
+    int general = 1;  // fewest species of the accumulating kernel
+    if constexpr (G::kXStream) {
+      general = 5;
+      switch (sm.upto(G::kXMax)) {
+        case 1: hipLaunchKernelGGL((k_xfwd<T, N, 1, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+        case 2: hipLaunchKernelGGL((k_xfwd<T, N, 2, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+        case 3: hipLaunchKernelGGL((k_xfwd<T, N, 3, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+        case 4: if constexpr (!four) hipLaunchKernelGGL((k_xfwd<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+        default: break;
+      }
+      if constexpr (four) general = 4;
+    }
+    if (sm.maxS() >= general)
+      hipLaunchKernelGGL((k_xfwd_acc<T, N, G::EXG, G::PX>), g, dim3(G::PX * TXG), 0, s, a, general, part);
   }
   // phi: also sum Phi_hs per workgroup (free-energy calls); fmask: the
   // hard-sphere functionals among the instances (1 Rosenfeld, 2 White Bear),
@@ -61,27 +83,19 @@ template <typename T, int N, int V = 0> struct Launch {
       else hipLaunchKernelGGL((k_zderiv<T, N, false, true, EZD, V>), g, b, 0, s, a);
     }
   }
-  // smax: the largest species count among the launch's instances with at
-  // most four species (0: none); large: some instance has more than four.
-  // The FP32 path runs the streamed kernel for the former and the chunked one
-  // for the latter (each skips the other's instances), so an instance gets
-  // the arithmetic of its single call in any launch list.
-  static void xback(const EvalArgs* a, int count, int smax, bool large, int part, hipStream_t s) {
+  static void xback(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
     const dim3 g(count * tiles_x(part)), b(G::PX * G::TX);
-    if constexpr (sizeof(T) == 8) {
-      // FP64: the streamed kernel does not fit the register file; the chunked
-      // one keeps every spectrum in registers without spilling
-      hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, 1, part);
-    } else {
-      switch (smax) {
-        case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX>), g, b, 0, s, a, part); break;
-        case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX>), g, b, 0, s, a, part); break;
-        case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX>), g, b, 0, s, a, part); break;
-        case 4: hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, part); break;
-        default: break;
-      }
-      if (large) hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, 5, part);
+    switch (sm.upto(G::kXMax)) {
+      case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+      case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+      case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+      case 4: if constexpr (!four) hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+      default: break;
     }
+    if constexpr (four)
+      if (sm.has(4)) hipLaunchKernelGGL((k_xback<T, N, 4, EX4, G::PX>), g, dim3(G::PX * (N / EX4)), 0, s, a, 4, part);
+    if (sm.maxS() > 4)
+      hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EXG, G::PX>), g, dim3(G::PX * TXG), 0, s, a, 5, part);
   }
   static void zinv(const EvalArgs* a, int count, int sel, hipStream_t s) {
     hipLaunchKernelGGL((k_zinv<T, N, V>), dim3(count * G::tiles_z), dim3(G::RZ * G::TZ), 0, s, a, sel);
