@@ -480,7 +480,7 @@ constexpr SchedDefault kSchedDefault[] = {
     {24, passes({1, 4, 6, 9}), passes({1, 2, 4, 6, 8, 9})},
     {32, passes({1, 2, 3, 4, 5, 6, 7, 8, 9}), passes({1, 2, 3, 4, 6, 7, 8, 9})},
     {48, passes({1, 7, 9}), passes({1, 2, 6, 7, 9})},
-    {64, passes({1, 2, 3, 4, 5, 6, 7, 8, 9}), passes({1, 2, 4, 6, 8, 9})},
+    {64, passes({1, 2, 3, 4, 6, 7, 8, 9}), passes({1, 2, 4, 6, 8, 9})},
     {96, passes({1, 7, 9}), passes({7, 9})},
     {128, passes({1, 2, 3, 4, 6, 7, 8, 9}), passes({1, 2, 4, 6, 7, 8, 9})},
     {192, passes({1, 9}), passes({3, 7, 9})},
@@ -567,15 +567,15 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
   if (!sp.on && tables) {
     pt.begin(0); op.at(0)->tables(ta, count, M, sm.maxS(), s); pt.end();
   }
-  pt.begin(1); op.at(1)->zfwd(ea, count, s); pt.end();
+  pt.begin(1); op.at(1)->zfwd(ea, count, sm.maxS(), s); pt.end();
   sp.fork();
   if (sp.on && tables) {
     PassTimer ps{c, sp.nyq()};
     ps.begin(0); op.at(0)->tables(ta, count, M, sm.maxS(), sp.nyq()); ps.end();
     tab_pending = true;
   }
-  pt.begin(2); op.at(2)->ystep(ea, count, 0, -1, true, mp, s); pt.end();
-  if (sp.on) op.at(2)->ystep(ea, count, 0, -1, true, kPartNyquist, sp.nyq());
+  pt.begin(2); op.at(2)->ystep(ea, count, 0, -1, sm.maxS(), true, mp, s); pt.end();
+  if (sp.on) op.at(2)->ystep(ea, count, 0, -1, sm.maxS(), true, kPartNyquist, sp.nyq());
   if (fmask) {
     if (tab_pending && op.precision == PNP_FP64) {
       sp.join();
@@ -583,22 +583,22 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
     }
     pt.begin(3); op.at(3)->xfwd(ea, count, sm, mp, s); pt.end();
     if (sp.on) op.at(3)->xfwd(ea, count, sm, kPartNyquist, sp.nyq());
-    pt.begin(4); op.at(4)->ystep(ea, count, 1, kVecMode, false, mp, s); pt.end();
-    if (sp.on) op.at(4)->ystep(ea, count, 1, kVecMode, false, kPartNyquist, sp.nyq());
+    pt.begin(4); op.at(4)->ystep(ea, count, 1, kVecMode, sm.maxS(), false, mp, s); pt.end();
+    if (sp.on) op.at(4)->ystep(ea, count, 1, kVecMode, sm.maxS(), false, kPartNyquist, sp.nyq());
     sp.join();
     tab_pending = false;
     pt.begin(5); op.at(5)->zderiv(ea, count, false, fmask, s); pt.end();
     sp.fork();
-    pt.begin(6); op.at(6)->ystep(ea, count, 1, kVecMode, true, mp, s); pt.end();
-    if (sp.on) op.at(6)->ystep(ea, count, 1, kVecMode, true, kPartNyquist, sp.nyq());
+    pt.begin(6); op.at(6)->ystep(ea, count, 1, kVecMode, sm.maxS(), true, mp, s); pt.end();
+    if (sp.on) op.at(6)->ystep(ea, count, 1, kVecMode, sm.maxS(), true, kPartNyquist, sp.nyq());
   }
   if (tab_pending) sp.join();
   pt.begin(7); op.at(7)->xback(ea, count, sm, mp, s); pt.end();
   if (sp.on) op.at(7)->xback(ea, count, sm, kPartNyquist, sp.nyq());
-  pt.begin(8); op.at(8)->ystep(ea, count, 2, -1, false, mp, s); pt.end();
-  if (sp.on) op.at(8)->ystep(ea, count, 2, -1, false, kPartNyquist, sp.nyq());
+  pt.begin(8); op.at(8)->ystep(ea, count, 2, -1, sm.maxS(), false, mp, s); pt.end();
+  if (sp.on) op.at(8)->ystep(ea, count, 2, -1, sm.maxS(), false, kPartNyquist, sp.nyq());
   sp.join();
-  pt.begin(9); op.at(9)->zinv(ea, count, 2, s); pt.end();
+  pt.begin(9); op.at(9)->zinv(ea, count, 2, sm.maxS(), s); pt.end();
 }
 
 // the FFT schedule of (precision, n) and the tuned tile shapes for a launch
@@ -735,28 +735,28 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   Split sq(ctx, s, d.n);
   const SpeciesMix sm = mix_of(S);
   const int mp = sq.main_part();
-  pt.begin(1); os.at(1)->zfwd(dea, 1, s); pt.end();
+  pt.begin(1); os.at(1)->zfwd(dea, 1, S, s); pt.end();
   sq.fork();
-  pt.begin(2); os.at(2)->ystep(dea, 1, 0, -1, true, mp, s); pt.end();
-  if (sq.on) os.at(2)->ystep(dea, 1, 0, -1, true, kPartNyquist, sq.nyq());
+  pt.begin(2); os.at(2)->ystep(dea, 1, 0, -1, S, true, mp, s); pt.end();
+  if (sq.on) os.at(2)->ystep(dea, 1, 0, -1, S, true, kPartNyquist, sq.nyq());
   if (d.hs) {
     pt.begin(3); os.at(3)->xfwd(dea, 1, sm, mp, s); pt.end();
     if (sq.on) os.at(3)->xfwd(dea, 1, sm, kPartNyquist, sq.nyq());
-    pt.begin(4); os.at(4)->ystep(dea, 1, 1, kVecMode, false, mp, s); pt.end();
-    if (sq.on) os.at(4)->ystep(dea, 1, 1, kVecMode, false, kPartNyquist, sq.nyq());
+    pt.begin(4); os.at(4)->ystep(dea, 1, 1, kVecMode, S, false, mp, s); pt.end();
+    if (sq.on) os.at(4)->ystep(dea, 1, 1, kVecMode, S, false, kPartNyquist, sq.nyq());
     sq.join();
     pt.begin(5); os.at(5)->zderiv(dea, 1, phi_part != nullptr, hs_mask(d), s); pt.end();
     sq.fork();
-    pt.begin(6); os.at(6)->ystep(dea, 1, 1, kVecMode, true, mp, s); pt.end();
-    if (sq.on) os.at(6)->ystep(dea, 1, 1, kVecMode, true, kPartNyquist, sq.nyq());
+    pt.begin(6); os.at(6)->ystep(dea, 1, 1, kVecMode, S, true, mp, s); pt.end();
+    if (sq.on) os.at(6)->ystep(dea, 1, 1, kVecMode, S, true, kPartNyquist, sq.nyq());
   }
   for (int k = 1; k < 4; ++k) {
     pt.begin(7); os.at(7)->xback(dea + k, 1, sm, mp, s); pt.end();
     if (sq.on) os.at(7)->xback(dea + k, 1, sm, kPartNyquist, sq.nyq());
-    pt.begin(8); os.at(8)->ystep(dea + k, 1, 2, -1, false, mp, s); pt.end();
-    if (sq.on) os.at(8)->ystep(dea + k, 1, 2, -1, false, kPartNyquist, sq.nyq());
+    pt.begin(8); os.at(8)->ystep(dea + k, 1, 2, -1, S, false, mp, s); pt.end();
+    if (sq.on) os.at(8)->ystep(dea + k, 1, 2, -1, S, false, kPartNyquist, sq.nyq());
     sq.join();
-    pt.begin(9); os.at(9)->zinv(dea + k, 1, 2, s); pt.end();
+    pt.begin(9); os.at(9)->zinv(dea + k, 1, 2, S, s); pt.end();
     if (k < 3) sq.fork();  // the next term's Nyquist tiles rewrite what this z pass read
   }
   const long sn3 = (long)S * n3;
@@ -1121,11 +1121,11 @@ pnp_status pnp_weighted_densities(pnp_ctx ctx, const pnp_grid* g, int32_t S, con
   upload_args(ctx, &ta, 1, &ea, 1, s, dta, dea);
   if (!dta || !dea) return device_check(ctx, "argument upload");
   os.at(0)->tables(dta, 1, L.M, S, s);
-  os.at(1)->zfwd(dea, 1, s);
-  os.at(2)->ystep(dea, 1, 0, -1, true, kPartAll, s);
+  os.at(1)->zfwd(dea, 1, S, s);
+  os.at(2)->ystep(dea, 1, 0, -1, S, true, kPartAll, s);
   os.at(3)->xfwd(dea, 1, mix_of(S), kPartAll, s);
-  os.at(4)->ystep(dea, 1, 1, kVecMode, false, kPartAll, s);
-  os.at(9)->zinv(dea, 1, 1, s);
+  os.at(4)->ystep(dea, 1, 1, kVecMode, S, false, kPartAll, s);
+  os.at(9)->zinv(dea, 1, 1, kFields, s);
   st = device_check(ctx, "launch");
   if (st != PNP_OK) return st;
   if (p->flags & PNP_FLAG_ASYNC) return PNP_OK;
@@ -1630,15 +1630,15 @@ pnp_status pnp_debug_rfft3(pnp_ctx ctx, const pnp_grid* g, int32_t precision, in
   const EvalArgs* dea = (const EvalArgs*)upload(ctx, &ea, sizeof(ea), s);
   if (!dea) return device_check(ctx, "argument upload");
   if (!inverse) {
-    op->zfwd(dea, 1, s);
-    op->ystep(dea, 1, 0, -1, true, kPartAll, s);
+    op->zfwd(dea, 1, count, s);
+    op->ystep(dea, 1, 0, -1, count, true, kPartAll, s);
     op->xplain(dea, 1, count, true, s);
     op->xport(dea, count, out, 1, s);
   } else {
     op->xport(dea, count, (double*)in, 0, s);
     op->xplain(dea, 1, count, false, s);
-    op->ystep(dea, 1, 0, -1, false, kPartAll, s);
-    op->zinv(dea, 1, 0, s);
+    op->ystep(dea, 1, 0, -1, count, false, kPartAll, s);
+    op->zinv(dea, 1, 0, count, s);
   }
   pnp_status st = device_check(ctx, "launch");
   if (st != PNP_OK) return st;

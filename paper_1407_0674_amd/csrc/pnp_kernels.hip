@@ -419,18 +419,18 @@ template <typename T, int N> constexpr uint32_t spec_nyq() { return (uint32_t)(N
 
 // The r2c post-step: v holds C[k] at k = t + TZ m and receives X[k] (k < H);
 // nyq receives X[H] in lane t = 0.  row: the row's LDS buffer.
-template <typename T, int N, int TZ, int EZ>
-__device__ __forceinline__ void r2c_post_w(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twN, cx<T>* row) {
+template <typename T, int N, int TZ, int EZ, class L>
+__device__ __forceinline__ void r2c_post_w(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twN, const L& row) {
   constexpr int H = N / 2;
 #pragma unroll
-  for (int m = 0; m < EZ; ++m) row[t + TZ * m] = v[m];
+  for (int m = 0; m < EZ; ++m) row.st(t + TZ * m, v[m]);
   lds_sync<row_in_wave<TZ>()>();
   nyq = mk<T>(v[0].x - v[0].y, (T)0);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
     const int k = t + TZ * m;
     const cx<T> c = v[m];
-    const cx<T> cm = cconj<T>(row[k == 0 ? 0 : H - k]);
+    const cx<T> cm = cconj<T>(row.ld(k == 0 ? 0 : H - k));
     const cx<T> e = mk<T>((T)0.5 * (c.x + cm.x), (T)0.5 * (c.y + cm.y));
     const cx<T> d = mk<T>((T)0.5 * (c.x - cm.x), (T)0.5 * (c.y - cm.y));  // O = d / i
     v[m] = cadd<T>(e, cmul<T>(twN[k], cmulmi<T>(d)));
@@ -456,8 +456,8 @@ __device__ __forceinline__ void r2c_store(const cx<T>* v, cx<T> nyq, int t, cons
   if (t == 0) f.template st<cx<T>>(nyq, (spec_nyq<T, N>() + row_id) * cs, soff);
 }
 
-template <typename T, int N, int TZ, int EZ, typename BF>
-__device__ __forceinline__ void r2c_post(cx<T>* v, int t, const cx<T>* twN, cx<T>* row, const BF& f,
+template <typename T, int N, int TZ, int EZ, typename BF, class L>
+__device__ __forceinline__ void r2c_post(cx<T>* v, int t, const cx<T>* twN, const L& row, const BF& f,
                                          uint32_t soff, uint32_t row_id) {
   cx<T> nyq;
   r2c_post_w<T, N, TZ, EZ>(v, nyq, t, twN, row);
@@ -508,16 +508,16 @@ __device__ __forceinline__ void c2r_load_k(cx<T>* xk, cx<T>& xn, int t, const BF
 
 // X[H - k] of the lane's elements k = t + TZ m (X[H] for k = 0) through the
 // row's LDS buffer, which is free again on return
-template <typename T, int N, int TZ, int EZ>
-__device__ __forceinline__ void c2r_mirror(cx<T>* xm, const cx<T>* xk, cx<T> xn, int t, cx<T>* row) {
+template <typename T, int N, int TZ, int EZ, class L>
+__device__ __forceinline__ void c2r_mirror(cx<T>* xm, const cx<T>* xk, cx<T> xn, int t, const L& row) {
   constexpr int H = N / 2;
 #pragma unroll
-  for (int m = 0; m < EZ; ++m) row[t + TZ * m] = xk[m];
+  for (int m = 0; m < EZ; ++m) row.st(t + TZ * m, xk[m]);
   lds_sync<row_in_wave<TZ>()>();
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
     const int k = t + TZ * m;
-    xm[m] = k == 0 ? xn : row[H - k];
+    xm[m] = k == 0 ? xn : row.ld(H - k);
   }
   lds_sync<row_in_wave<TZ>()>();
 }
@@ -547,12 +547,27 @@ __device__ __forceinline__ void c2r_combine(cx<T>* v, const cx<T>* xk0, const cx
   }
 }
 
+// One row in LDS with one value of padding after every 2^SH (the strided writes
+// of the radix stages spread over the banks; SH = 30: none) and GAP values
+// between rows.
+template <typename T, bool WAVE, int SH, int GAP = 0> struct LdsRow {
+  cx<T>* base;
+  static constexpr bool wave = WAVE;
+  static constexpr __host__ __device__ int at(int i) { return i + (i >> SH); }
+  static constexpr __host__ __device__ int pitch(int n) { return n + (n >> SH) + GAP; }
+  __device__ __forceinline__ void st(int pos, cx<T> v) const { base[at(pos)] = v; }
+  __device__ __forceinline__ cx<T> ld(int pos) const { return base[at(pos)]; }
+  __device__ __forceinline__ void sync() const { lds_sync<WAVE>(); }
+  __device__ __forceinline__ void done() const { lds_sync<WAVE>(); }
+};
+
 template <typename T>
 __device__ __forceinline__ uint64_t spec_bytes(const EvalArgs& a, int nf) {
   return (uint64_t)nf * a.fstride * sizeof(cx<T>);
 }
 
-// P1: z r2c of the S input densities (float64) into specA
+// P1: z r2c of the S input densities (float64) into specA (each gridDim.y-th
+// species per workgroup)
 template <typename T, int N, int V = 0>
 __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     k_zfwd(const EvalArgs* __restrict__ args) {
@@ -565,23 +580,23 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   const EvalArgs& a = args[inst_of(G::tiles_z, tile)];
   init_twiddles<T, H>(twH);
   init_twiddles<T, N>(twN);
-  if (tile == 0 && threadIdx.x == 0) {
+  if (tile == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     gp<uint32_t> st = gbl(a.status);
     st[0] = 0u;
     st[1] = 0xffffffffu;
     st[2] = st[3] = 0u;
-    for (int s = 0; s < a.S; ++s) gbl(a.dc)[s] = 0.0;
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) gbl(a.dc)[s] = 0.0;
   }
   __syncthreads();
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;
   const uint32_t row = (uint32_t)(tile * RZ + r);
-  cx<T>* lrow = xch + r * H;
-  const LdsPencil<T, row_in_wave<TZ>()> lp{lrow, 1};
+  const LdsPencil<T, row_in_wave<TZ>()> lp{xch + r * H, 1};
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, a.S));
   if (a.ext_n == 0) {
     constexpr uint32_t n3b = (uint32_t)N * N * N * sizeof(double);
     const BufN<N> rho = make_buf<stream_policy<N>()>(a.rho, (uint64_t)a.S * n3b);
-    for (int s = 0; s < a.S; ++s) {
+    for (int s = blockIdx.y; s < a.S; s += gridDim.y) {
       cx<T> v[EZ];
 #pragma unroll
       for (int m = 0; m < EZ; ++m) {
@@ -589,7 +604,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
         v[m] = mk<T>((T)p.x, (T)p.y);
       }
       fft_pencil<T, H, EZ, true>(v, t, twH, lp);
-      r2c_post<T, N, TZ, EZ>(v, t, twN, lrow, A, (uint32_t)(s * a.fstride * sizeof(cx<T>)), row);
+      r2c_post<T, N, TZ, EZ>(v, t, twN, lp, A, (uint32_t)(s * a.fstride * sizeof(cx<T>)), row);
     }
   } else {
     // zero extension of the (even-sized) domain: the point pair (2j, 2j+1)
@@ -598,7 +613,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     const bool row_in = x < nd && y < nd;
     const uint32_t d3b = nd * nd * nd * (uint32_t)sizeof(double);
     const BufN<N> rho = make_buf<stream_policy<N>()>(a.rho, a.ext_bulk ? 0 : (uint64_t)a.S * d3b);
-    for (int s = 0; s < a.S; ++s) {
+    for (int s = blockIdx.y; s < a.S; s += gridDim.y) {
       cx<T> v[EZ];
 #pragma unroll
       for (int m = 0; m < EZ; ++m) {
@@ -611,7 +626,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
         v[m] = mk<T>((T)p.x, (T)p.y);
       }
       fft_pencil<T, H, EZ, true>(v, t, twH, lp);
-      r2c_post<T, N, TZ, EZ>(v, t, twN, lrow, A, (uint32_t)(s * a.fstride * sizeof(cx<T>)), row);
+      r2c_post<T, N, TZ, EZ>(v, t, twN, lp, A, (uint32_t)(s * a.fstride * sizeof(cx<T>)), row);
     }
   }
 }
@@ -642,7 +657,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   const BufN<N> slot = make_buf<stream_policy<N>()>(a.slot, a.slot ? (uint64_t)a.nreal * n3b : 0);
   const Buf dcb = make_buf(a.dc, a.final_mode ? kMaxSpecies * sizeof(double) : 0);
   uint32_t bad = 0u, badidx = 0xffffffffu;
-  for (int s = 0; s < a.nreal; ++s) {
+  for (int s = blockIdx.y; s < a.nreal; s += gridDim.y) {
     cx<T> v[EZ], xk[EZ], xm[EZ];
     // in flight with the row (the buffer is empty for a plain real output)
     const double dc = dcb.template ld<double>((uint32_t)s * (uint32_t)sizeof(double));
@@ -653,7 +668,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     if constexpr (mirror_lds<N>()) {
       cx<T> xn;
       c2r_load_k<T, N, TZ, EZ, false>(xk, xn, t, src, si, row);
-      c2r_mirror<T, N, TZ, EZ>(xm, xk, xn, t, xch + r * H);
+      c2r_mirror<T, N, TZ, EZ>(xm, xk, xn, t, lp);
     } else {
       c2r_load<T, N, TZ, EZ>(xk, xm, t, src, si, row);  // the policy is the default one here
     }
@@ -745,18 +760,18 @@ __device__ __forceinline__ void c2r_combine_p(cx<T>* v, const cx<T>* xk0, const 
   }
 }
 
-template <typename T, int N, int TZ, int EZ>
-__device__ __forceinline__ void r2c_post_p(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twp, cx<T>* row) {
+template <typename T, int N, int TZ, int EZ, class L>
+__device__ __forceinline__ void r2c_post_p(cx<T>* v, cx<T>& nyq, int t, const cx<T>* twp, const L& row) {
   constexpr int H = N / 2;
 #pragma unroll
-  for (int m = 0; m < EZ; ++m) row[t + TZ * m] = v[m];
+  for (int m = 0; m < EZ; ++m) row.st(t + TZ * m, v[m]);
   lds_sync<row_in_wave<TZ>()>();
   nyq = mk<T>(v[0].x - v[0].y, (T)0);
 #pragma unroll
   for (int m = 0; m < EZ; ++m) {
     const int k = t + TZ * m;
     const cx<T> c = v[m];
-    const cx<T> r = row[k == 0 ? 0 : H - k];
+    const cx<T> r = row.ld(k == 0 ? 0 : H - k);
     const T cmx = r.x, cmy = -r.y;  // cm = conj(C[H - k])
     const T dx = c.x - cmx, dy = c.y - cmy;
     const cx<T> P = twp[m];
@@ -795,11 +810,13 @@ struct LogEntry {
 };
 constexpr int kLogTable = 256;
 
+__device__ __forceinline__ LogEntry log_table_entry(int j) {
+  const double ic = 1.0 / (0.5 + ((double)j + 0.5) / 512.0);
+  return LogEntry{ic, -log(ic)};
+}
+
 __device__ __forceinline__ void log_table_init(LogEntry* tab) {
-  for (int j = threadIdx.x; j < kLogTable; j += blockDim.x) {
-    const double ic = 1.0 / (0.5 + ((double)j + 0.5) / 512.0);
-    tab[j] = LogEntry{ic, -log(ic)};
-  }
+  for (int j = threadIdx.x; j < kLogTable; j += blockDim.x) tab[j] = log_table_entry(j);
 }
 
 __device__ __forceinline__ double log_f64(double u, const LogEntry* tab) {
@@ -852,6 +869,55 @@ __device__ __forceinline__ void wb_coeff(double x, double inv, double lnu, doubl
   dg = small ? dgs : dgl;
 }
 
+// The ten derivatives of Phi_hs at one grid point (Sec. 2.3.1):
+//   Phi_hs = -n0 ln(1 - n3) + (n1 n2 - n1v.n2v) / (1 - n3)
+//            + (n2^3 - 3 n2 n2v.n2v) phi3(n3)
+// with phi3 = 1 / (24 pi (1 - n3)^2) (Rosenfeld) or the modified form (WB).
+// f: n0..n3, n1v, n2v; d: the derivatives; returns Phi_hs (PHI only).
+// P: type of the products of the weighted densities with the singular factors.
+template <typename P, bool PHI, bool WB>
+__device__ __forceinline__ double fmt_point(const P* f, P* d, const LogEntry* logt) {
+  constexpr double inv8pi = 1.0 / (8.0 * kPi), inv12pi = 1.0 / (12.0 * kPi), inv4pi = 1.0 / (4.0 * kPi);
+  constexpr double inv24pi = 1.0 / (24.0 * kPi), inv36pi = 1.0 / (36.0 * kPi);
+  const P n0 = f[0], n1 = f[1], n2 = f[2], n3 = f[3];
+  const P a1x = f[4], a1y = f[5], a1z = f[6], a2x = f[7], a2y = f[8], a2z = f[9];
+  double phi = 0.0;
+  // the logarithm and the powers of 1 / (1 - n3) in double
+  const double n3d = (double)n3, u = 1.0 - n3d;
+  const double inv = recip_f64(u), inv2 = inv * inv, inv3 = inv2 * inv;
+  // -ln(1 - n3): log of the rounded u plus the first-order correction for
+  // the rounding of u, which equals log1p(-n3) to working precision
+  const double d0 = -(log_f64(u, logt) - ((u - 1.0) + n3d) * inv);
+  const P i1 = (P)inv, i2 = (P)inv2;
+  const P v12 = a1x * a2x + a1y * a2y + a1z * a2z;
+  const P v22 = a2x * a2x + a2y * a2y + a2z * a2z;
+  d[0] = (P)d0;
+  P c2;  // 6 n2 phi3: the n2v coefficient of d[7..9]
+  d[1] = n2 * i1;
+  if constexpr (WB) {
+    double g, dg;
+    wb_coeff(n3d, inv, -d0, g, dg);
+    const P p3 = (P)(g * inv36pi), dp3 = (P)(dg * inv36pi);  // phi3 and its derivative
+    c2 = (P)6 * n2 * p3;
+    if constexpr (PHI) phi = n0 * d0 + (n1 * n2 - v12) * inv + (n2 * n2 * n2 - 3.0 * n2 * v22) * p3;
+    d[2] = n1 * i1 + (P)3 * (n2 * n2 - v22) * p3;
+    d[3] = n0 * i1 + (n1 * n2 - v12) * i2 + (n2 * n2 * n2 - (P)3 * n2 * v22) * dp3;
+  } else {
+    // Rosenfeld: 3 phi3 = 1 / (8 pi u^2), phi3' = 1 / (12 pi u^3), 6 n2 phi3 = n2 / (4 pi u^2)
+    c2 = n2 * i2 * (P)inv4pi;
+    if constexpr (PHI) phi = n0 * d0 + (n1 * n2 - v12) * inv + (n2 * n2 * n2 - 3.0 * n2 * v22) * inv2 * inv24pi;
+    d[2] = n1 * i1 + (n2 * n2 - v22) * i2 * (P)inv8pi;
+    d[3] = n0 * i1 + (n1 * n2 - v12) * i2 + (n2 * n2 * n2 - (P)3 * n2 * v22) * (P)inv3 * (P)inv12pi;
+  }
+  d[4] = -a2x * i1;
+  d[5] = -a2y * i1;
+  d[6] = -a2z * i1;
+  d[7] = -a1x * i1 - c2 * a2x;
+  d[8] = -a1y * i1 - c2 * a2y;
+  d[9] = -a1z * i1 - c2 * a2z;
+  return phi;
+}
+
 // PHI: also sum Phi_hs per workgroup into a.phi_part (free-energy calls)
 // WB: the functional this variant evaluates (White Bear or Rosenfeld); blocks
 // of instances that select the other one exit, so a launch list holding both
@@ -868,15 +934,19 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
   constexpr int H = D::H, TZ = D::TZD, EZ = D::EZD, RD = D::RDD;
   __shared__ cx<T> twH[H];
   __shared__ cx<T> twN[N];
-  __shared__ cx<T> xch[RD * H];
+  // padded rows where that was measured faster (256^3 mixed 306 -> 287 us, 128^3
+  // mixed 40 -> 37; 128^3 FP64, two elements per thread, 83 -> 101)
+  using Row = LdsRow<T, row_in_wave<TZ>(), sizeof(T) == 4 && EZ == 4 ? 2 : 30>;
+  constexpr int P0 = Row::pitch(H);
+  __shared__ cx<T> xch[RD * P0];
+  __shared__ cx<T> z2l[EZ < 6 ? 1 : RD * H];
   __shared__ LogEntry logt[kLogTable];
   int tile;
   const EvalArgs& a = args[inst_of(D::tiles, tile)];
   if (!a.hs_on || (a.hs_wb != 0) != WB) return;  // uniform per block
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;
   const uint32_t row = (uint32_t)(tile * RD + r);
-  cx<T>* lrow = xch + r * H;
-  const LdsPencil<T, row_in_wave<TZ>()> lp{lrow, 1};
+  const Row lp{xch + r * P0};
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
   cx<T> val[kFields * EZ];
@@ -934,7 +1004,7 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
         if constexpr (kLds) c2r_load_k<T, N, TZ, EZ>(kc, nb[0], t, B, (uint32_t)q * fbytes, row);
         else c2r_load<T, N, TZ, EZ>(kc, mc, t, B, (uint32_t)q * fbytes, row);
       }
-      if constexpr (kLds) c2r_mirror<T, N, TZ, EZ>(mc, kc, nb[q % kBufs], t, lrow);
+      if constexpr (kLds) c2r_mirror<T, N, TZ, EZ>(mc, kc, nb[q % kBufs], t, lp);
       // the z components of the vector densities, i s_z [6] and i s_z k0 [3],
       // are formed here
 #pragma unroll
@@ -969,8 +1039,6 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
     }
   }
   uint32_t bad = 0u, badidx = 0xffffffffu;
-  const double inv8pi = 1.0 / (8.0 * kPi), inv12pi = 1.0 / (12.0 * kPi), inv4pi = 1.0 / (4.0 * kPi);
-  const double inv24pi = 1.0 / (24.0 * kPi), inv36pi = 1.0 / (36.0 * kPi);
   double phi = 0.0;  // Phi_hs summed over this thread's grid points
   // type of the products of the weighted densities with those factors: the
   // FFT type, except for free-energy calls (double throughout, Phi summed in
@@ -983,49 +1051,13 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
       P f[kFields];
 #pragma unroll
       for (int q = 0; q < kFields; ++q) f[q] = h ? (P)val[q * EZ + m].y : (P)val[q * EZ + m].x;
-      const P n0 = f[0], n1 = f[1], n2 = f[2], n3 = f[3];
-      const P a1x = f[4], a1y = f[5], a1z = f[6], a2x = f[7], a2y = f[8], a2z = f[9];
+      const P n3 = f[kSlotN3];
       if (!(n3 < (P)1)) {
         bad |= isfinite(n3) ? kStPacking : kStNonFinite;
         badidx = min(badidx, row * N + 2 * (t + TZ * m) + h);
       }
-      // the logarithm and the powers of 1 / (1 - n3) in double
-      const double n3d = (double)n3, u = 1.0 - n3d;
-      const double inv = recip_f64(u), inv2 = inv * inv, inv3 = inv2 * inv;
-      // -ln(1 - n3): log of the rounded u plus the first-order correction for
-      // the rounding of u, which equals log1p(-n3) to working precision
-      const double d0 = -(log_f64(u, logt) - ((u - 1.0) + n3d) * inv);
-      const P i1 = (P)inv, i2 = (P)inv2;
-      const P v12 = a1x * a2x + a1y * a2y + a1z * a2z;
-      const P v22 = a2x * a2x + a2y * a2y + a2z * a2z;
       P d[kFields];
-      d[0] = (P)d0;
-      // Phi_hs (Sec. 2.3.1): -n0 ln(1 - n3) + (n1 n2 - n1v.n2v) / (1 - n3)
-      //                      + (n2^3 - 3 n2 n2v.n2v) phi3(n3)
-      // with phi3 = 1 / (24 pi (1 - n3)^2) (Rosenfeld) or the modified form
-      P c2;  // 6 n2 phi3: the n2v coefficient of d[7..9]
-      d[1] = n2 * i1;
-      if constexpr (WB) {
-        double g, dg;
-        wb_coeff(n3d, inv, -d0, g, dg);
-        const P p3 = (P)(g * inv36pi), dp3 = (P)(dg * inv36pi);  // phi3 and its derivative
-        c2 = (P)6 * n2 * p3;
-        if constexpr (PHI) phi += n0 * d0 + (n1 * n2 - v12) * inv + (n2 * n2 * n2 - 3.0 * n2 * v22) * p3;
-        d[2] = n1 * i1 + (P)3 * (n2 * n2 - v22) * p3;
-        d[3] = n0 * i1 + (n1 * n2 - v12) * i2 + (n2 * n2 * n2 - (P)3 * n2 * v22) * dp3;
-      } else {
-        // Rosenfeld: 3 phi3 = 1 / (8 pi u^2), phi3' = 1 / (12 pi u^3), 6 n2 phi3 = n2 / (4 pi u^2)
-        c2 = n2 * i2 * (P)inv4pi;
-        if constexpr (PHI) phi += n0 * d0 + (n1 * n2 - v12) * inv + (n2 * n2 * n2 - 3.0 * n2 * v22) * inv2 * inv24pi;
-        d[2] = n1 * i1 + (n2 * n2 - v22) * i2 * (P)inv8pi;
-        d[3] = n0 * i1 + (n1 * n2 - v12) * i2 + (n2 * n2 * n2 - (P)3 * n2 * v22) * (P)inv3 * (P)inv12pi;
-      }
-      d[4] = -a2x * i1;
-      d[5] = -a2y * i1;
-      d[6] = -a2z * i1;
-      d[7] = -a1x * i1 - c2 * a2x;
-      d[8] = -a1y * i1 - c2 * a2y;
-      d[9] = -a1z * i1 - c2 * a2z;
+      phi += fmt_point<P, PHI, WB>(f, d, logt);
 #pragma unroll
       for (int q = 0; q < kFields; ++q) {
         if (h) val[q * EZ + m].y = (T)d[q];
@@ -1035,7 +1067,8 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
     }
   }
   // F_2z first: -i s_z k0 F_2z joins the spectrum of F_3
-  cx<T> z2[EZ];
+  // (kept in registers, or where those are short, in LDS by the same thread)
+  cx<T> z2r[kTwRegs ? EZ : 1];
 #pragma unroll
   for (int i = 0; i < kFields; ++i) {
     const int q = i == 0 ? kFieldZ2 : i == 1 ? kSlotN3 : i <= kSlotN3 + 1 ? i - 2 : i - 1;
@@ -1045,23 +1078,205 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
     cx<T> nyq;
     if constexpr (kTwRegs) {
       fft_pencil<T, N / 2, EZ, true>(vq, t, twr, lp);
-      r2c_post_p<T, N, TZ, EZ>(vq, nyq, t, twp, lrow);
+      r2c_post_p<T, N, TZ, EZ>(vq, nyq, t, twp, lp);
     } else {
       fft_pencil<T, N / 2, EZ, true>(vq, t, (const cx<T>*)twH, lp);
-      r2c_post_w<T, N, TZ, EZ>(vq, nyq, t, twN, lrow);
+      r2c_post_w<T, N, TZ, EZ>(vq, nyq, t, twN, lp);
     }
     if (q == kSlotZ || q == kFieldZ2) mul_isz<T, TZ, EZ>(vq, nyq, t, zs);
     if (q == kFieldZ2) {
 #pragma unroll
-      for (int m = 0; m < EZ; ++m) z2[m] = vq[m];
+      for (int m = 0; m < EZ; ++m) {
+        if constexpr (kTwRegs) z2r[m] = vq[m];
+        else z2l[m * (RD * TZ) + threadIdx.x] = vq[m];
+      }
     } else {
       if (q == kSlotN3) {
 #pragma unroll
-        for (int m = 0; m < EZ; ++m) vq[m] = cadd<T>(vq[m], z2[m]);
+        for (int m = 0; m < EZ; ++m) vq[m] = cadd<T>(vq[m], kTwRegs ? z2r[kTwRegs ? m : 0] : z2l[kTwRegs ? 0 : m * (RD * TZ) + threadIdx.x]);
       }
       r2c_store<T, N, TZ, EZ>(vq, nyq, t, B, q * fbytes, row);
     }
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if (bad) raise_status(a.status, bad, badidx);
+  if constexpr (PHI) {
+    __shared__ double red[16];
+    const double tot = block_sum(phi, red);
+    if (threadIdx.x == 0) a.phi_part[tile] = tot;
+  }
+}
+
+// P5 on grids up to 96^3: the same pass with one wavefront per field.  The
+// wavefronts of a workgroup transform the same RW rows of the ten fields side
+// by side, the ten real values of every grid point meet in LDS for the
+// derivatives, and wavefront f transforms its derivative field back.  On small
+// grids the chain of twenty transforms one after the other in each thread was
+// the pass's whole time, and with a factor 3 its six elements per thread left
+// only radix-2 stages; here 12 fit (FP32).  Three species, before and after:
+// FP64 16^3 11.4 -> 7.2 us, 48^3 37.8 -> 13.7, 96^3 78.5 -> 52.7; mixed 32^3
+// 11.4 -> 7.9, 48^3 25.7 -> 10.6, 96^3 39.9 -> 33.9 us.  From 128^3 on it is
+// the slower one (mixed 256^3 312 -> 500 us): ten wavefronts are three on two of
+// the four SIMDs, so one workgroup fills a compute unit, and more data pass
+// through LDS.
+template <typename T, int N>
+constexpr int default_ezf() {
+  constexpr int H = N / 2;
+  if (H % 3 == 0) return H >= 48 && sizeof(T) == 4 ? 12 : 6;
+  return H >= (sizeof(T) == 4 ? 16 : 32) ? 4 : 2;
+}
+constexpr bool ezf_ok(int len, int ept) { return plan_ok(len, ept) && 64 % (len / ept) == 0; }
+// elements per thread under launch variant V (bit 1, the secondary schedule:
+// half, or else twice, as many where that has a plan; the tile shape has no
+// variant here, a workgroup always carries one wavefront of rows per field)
+template <typename T, int N, int V>
+constexpr int ezf_of() {
+  constexpr int prim = default_ezf<T, N>(), H = N / 2;
+  if ((V & 2) == 0) return prim;
+  return ezf_ok(H, prim / 2) ? prim / 2 : (ezf_ok(H, prim * 2) && prim * 2 <= 12) ? prim * 2 : prim;
+}
+
+template <typename T, int N, int EZ = default_ezf<T, N>()> struct GeoF {
+  static constexpr int H = N / 2;
+  static constexpr int EZF = EZ;
+  static constexpr int TZF = H / EZF;
+  static constexpr int RW = 64 / TZF;  // rows per workgroup
+  static constexpr int tiles = (N * N) / RW;
+  static constexpr int threads = 64 * kFields;
+  // padding of the LDS rows; with a factor 3 a gap that sets the rows of a
+  // wavefront side by side in the banks
+  static constexpr int SH = H % 3 != 0 ? 3 : 30, GAP = H % 3 != 0 ? 0 : TZF;
+  static_assert(ezf_ok(H, EZ) && (N * N) % RW == 0, "derivative pass: rows per wavefront");
+};
+
+
+template <typename T, int N, bool PHI = false, bool WB = false, int EZF = default_ezf<T, N>()>
+__global__ void __launch_bounds__((GeoF<T, N, EZF>::threads))
+    k_zderiv_fields(const EvalArgs* __restrict__ args) {
+  using D = GeoF<T, N, EZF>;
+  constexpr int H = D::H, TZ = D::TZF, EZ = D::EZF, RW = D::RW;
+  using Row = LdsRow<T, true, D::SH, D::GAP>;
+  constexpr int P0 = Row::pitch(H);
+  __shared__ cx<T> twH[H];  // FFT twiddles
+  __shared__ cx<T> twp[H];  // P_k = (1 - i W^k) / 2 of the r2c / c2r steps
+  __shared__ cx<T> val[kFields * RW * P0];
+  __shared__ LogEntry logt[kLogTable];
+  int tile;
+  const EvalArgs& a = args[inst_of(D::tiles, tile)];
+  if (!a.hs_on || (a.hs_wb != 0) != WB) return;  // uniform per block
+  const int f = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x & 63;
+  const int t = lane % TZ, r = lane / TZ;
+  const uint32_t row = (uint32_t)(tile * RW + r);
+  cx<T>* mine = val + (f * RW + r) * P0;
+  const Row lp{mine};
+  const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
+  // the z components of the vector densities are i s_z [6] and i s_z k0 [3]
+  const uint32_t so = (uint32_t)((f == kFieldZ2 ? kSlotN3 : f) * a.fstride * sizeof(cx<T>));
+  const bool zmul = f == kSlotZ || f == kFieldZ2;
+  const T zs = f == kFieldZ2 ? (T)a.kscale : (T)1;
+  cx<T> v[EZ], nyq;
+  c2r_load_k<T, N, TZ, EZ>(v, nyq, t, B, so, row);
+  // the tables while the loads are in flight, each made by threads of its own
+  for (int j = threadIdx.x; j < kLogTable + 2 * H; j += D::threads) {
+    if (j < kLogTable) {
+      logt[j] = log_table_entry(j);
+    } else {
+      const int i = (j - kLogTable) % H;
+      const bool p = j >= kLogTable + H;
+      double sn, cs;
+      sincospi((p ? 1.0 : 2.0) * (double)i / (double)H, &sn, &cs);
+      if (p) twp[i] = mk<T>((T)(0.5 - 0.5 * sn), (T)(-0.5 * cs));
+      else twH[i] = mk<T>((T)cs, (T)-sn);
+    }
+  }
+  __syncthreads();
+  {
+    cx<T> xm[EZ], P[EZ];
+    c2r_mirror<T, N, TZ, EZ>(xm, v, nyq, t, lp);
+#pragma unroll
+    for (int m = 0; m < EZ; ++m) P[m] = twp[t + TZ * m];
+    if (zmul) c2r_combine_p<T, N, TZ, EZ>(v, v, xm, t, P, true, zs);  // uniform
+    else c2r_combine_p<T, N, TZ, EZ>(v, v, xm, t, P);
+  }
+  fft_pencil<T, H, EZ, false>(v, t, (const cx<T>*)twH, lp);
+#pragma unroll
+  for (int m = 0; m < EZ; ++m) lp.st(t + TZ * m, v[m]);
+  __syncthreads();
+  uint32_t bad = 0u, badidx = 0xffffffffu;
+  double phi = 0.0;  // Phi_hs summed over this thread's grid points
+  {
+    using P = typename std::conditional<PHI, double, T>::type;  // as in k_zderiv
+    // points per LDS access: a pair in FP32; one in FP64, where the twenty
+    // doubles of a pair would not fit beside the arithmetic
+    constexpr int W = sizeof(T) == 4 ? 2 : 1;
+    using X = typename std::conditional<W == 2, cx<T>, T>::type;
+    for (int e = threadIdx.x; e < RW * (N / W); e += D::threads) {
+      const int er = e / (N / W), ez = e % (N / W) * W;  // the points z = ez .. ez + W - 1 of row er
+      X* q0 = (X*)((T*)(val + er * P0 + Row::at(ez / 2)) + ez % 2);
+      const uint32_t erow = (uint32_t)(tile * RW + er);
+      P w[W][kFields];
+#pragma unroll
+      for (int q = 0; q < kFields; ++q) {
+        const X x = q0[q * (RW * P0 * 2 / W)];
+        if constexpr (W == 2) { w[0][q] = (P)x.x; w[1][q] = (P)x.y; }
+        else w[0][q] = (P)x;
+      }
+      if (a.ext_n != 0) {  // aperiodic mode: no derivatives outside the domain, as in k_zderiv
+        const uint32_t nd = (uint32_t)a.ext_n;
+        if (!(erow / N < nd && erow % N < nd && (uint32_t)ez < nd)) {
+#pragma unroll
+          for (int h = 0; h < W; ++h)
+#pragma unroll
+            for (int q = 0; q < kFields; ++q) w[h][q] = (P)0;
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < W; ++h) {
+        P d[kFields];
+        const P n3 = w[h][kSlotN3];
+        if (!(n3 < (P)1)) {
+          bad |= isfinite(n3) ? kStPacking : kStNonFinite;
+          badidx = min(badidx, erow * N + ez + h);
+        }
+        phi += fmt_point<P, PHI, WB>(w[h], d, logt);
+#pragma unroll
+        for (int q = 0; q < kFields; ++q) w[h][q] = d[q];
+        __builtin_amdgcn_sched_barrier(0);  // one grid point at a time
+      }
+#pragma unroll
+      for (int q = 0; q < kFields; ++q) {
+        X x;
+        if constexpr (W == 2) x = mk<T>((T)w[0][q], (T)w[1][q]);
+        else x = (T)w[0][q];
+        q0[q * (RW * P0 * 2 / W)] = x;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < EZ; ++m) v[m] = lp.ld(t + TZ * m);
+  lds_sync<true>();
+  fft_pencil<T, H, EZ, true>(v, t, (const cx<T>*)twH, lp);
+  {
+    cx<T> P[EZ];
+#pragma unroll
+    for (int m = 0; m < EZ; ++m) P[m] = twp[t + TZ * m];
+    r2c_post_p<T, N, TZ, EZ>(v, nyq, t, P, lp);
+  }
+  // the z components of the vector derivatives leave as i s_z F_z
+  if (zmul) mul_isz<T, TZ, EZ>(v, nyq, t, f == kFieldZ2 ? -zs : zs);
+  if (f == kFieldZ2) {
+#pragma unroll
+    for (int m = 0; m < EZ; ++m) lp.st(t + TZ * m, v[m]);
+  } else if (f != kSlotN3) {
+    r2c_store<T, N, TZ, EZ>(v, nyq, t, B, so, row);
+  }
+  __syncthreads();
+  if (f == kSlotN3) {  // -i s_z k0 F_2z joins the spectrum of F_3
+    const Row z2{mine + (kFieldZ2 - kSlotN3) * RW * P0};
+#pragma unroll
+    for (int m = 0; m < EZ; ++m) v[m] = cadd<T>(v[m], z2.ld(t + TZ * m));
+    r2c_store<T, N, TZ, EZ>(v, nyq, t, B, so, row);
   }
   if (bad) raise_status(a.status, bad, badidx);
   if constexpr (PHI) {
@@ -1080,6 +1295,7 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
 // adds those components' derivatives to [6] and [3] and leaves [y] unused.
 // ---------------------------------------------------------------------------
 constexpr int kVecMode = -2;
+constexpr int kVecItems = 7;  // two vectors (two transforms each), n0..n2 and the x components
 
 template <typename T, int N, int EY, int TY>
 __device__ __forceinline__ void mul_isy(cx<T>* v, int t, T sc) {
@@ -1129,19 +1345,23 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
 #pragma unroll
   for (int m = 0; m < EY; ++m) eo[m] = (off + (uint32_t)(t + TY * m) * es) * (uint32_t)sizeof(cx<T>);
   const uint32_t fbytes = (uint32_t)(a.fstride * sizeof(cx<T>));
-  for (int f = 0; f < nf; ++f) {
-    if (vec && (f == kSlotN3 || (f > kSlotX && (f - kSlotX) % kVecStride != 0))) continue;  // [y], [z] below
-    const uint32_t so = (uint32_t)f * fbytes;
-    cx<T> v[EY];
-#pragma unroll
-    for (int m = 0; m < EY; ++m) v[m] = base.template ld<cx<T>>(eo[m], so);
-    fft_pencil<T, N, EY, FWD>(v, t, tw, lp);
-#pragma unroll
-    for (int m = 0; m < EY; ++m) base.template st<cx<T>>(v[m], eo[m], so);
-  }
-  if (!vec) return;
+  // work items: the fields, in the vector mode the two vectors first; each
+  // gridDim.y-th belongs to this workgroup
+  const int items = vec ? kVecItems : nf;
 #pragma unroll 1
-  for (int b = 0; b < 2; ++b) {
+  for (int it = blockIdx.y; it < items; it += gridDim.y) {
+    if (!vec || it >= 2) {
+      const int f = !vec ? it : it < 5 ? it - 2 : kSlotX + kVecStride * (it - 5);  // 0, 1, 2, 4, 7
+      const uint32_t so = (uint32_t)f * fbytes;
+      cx<T> v[EY];
+#pragma unroll
+      for (int m = 0; m < EY; ++m) v[m] = base.template ld<cx<T>>(eo[m], so);
+      fft_pencil<T, N, EY, FWD>(v, t, tw, lp);
+#pragma unroll
+      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(v[m], eo[m], so);
+      continue;
+    }
+    const int b = it;
     const uint32_t sy_off = (uint32_t)(kSlotY + kVecStride * b) * fbytes;
     const uint32_t sz_off = (uint32_t)(b == 0 ? kSlotZ : kSlotN3) * fbytes;
     // vector 2: k0 times the gradient of n3, and minus that on the way back

@@ -28,13 +28,13 @@ struct SpeciesMix {
 
 struct Ops {
   void (*tables)(const TableArgs*, int, int, int, hipStream_t);
-  void (*zfwd)(const EvalArgs*, int, hipStream_t);
-  void (*ystep)(const EvalArgs*, int, int, int, bool, int, hipStream_t);  // count, sel, nf, fwd, part
+  void (*zfwd)(const EvalArgs*, int, int, hipStream_t);  // count, most species
+  void (*ystep)(const EvalArgs*, int, int, int, int, bool, int, hipStream_t);  // count, sel, nf, most fields, fwd, part
   void (*xfwd)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);   // count, species, part
   void (*zderiv)(const EvalArgs*, int, bool, int, hipStream_t);
   void (*xback)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);  // count, species, part
   int zderiv_tiles;  // workgroups of the derivative pass per instance
-  void (*zinv)(const EvalArgs*, int, int, hipStream_t);
+  void (*zinv)(const EvalArgs*, int, int, int, hipStream_t);  // count, sel, most fields
   void (*xplain)(const EvalArgs*, int, int, bool, hipStream_t);
   void (*xport)(const EvalArgs*, int, double*, int, hipStream_t);
   uint32_t sched_alt;  // passes (bit p: pass p) whose secondary FFT schedule differs from the primary

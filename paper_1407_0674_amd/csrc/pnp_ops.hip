@@ -25,13 +25,28 @@ template <typename T, int N, int V = 0> struct Launch {
   using G = Geo<T, N, V>;
   static constexpr int EZD = ezd_of<T, N, V>();
   using GD = GeoD<T, N, EZD, V>;
+  // the derivative pass of small grids runs one wavefront per field
+  static constexpr bool kFieldWaves = N <= 96;
+  static constexpr int EZF = ezf_of<T, N, V>();
+  // Workgroups per tile of the y and z passes: on small grids the fields of a
+  // tile are spread over workgroups of their own, until the launch has about
+  // two wavefronts for each of the 1024 SIMDs; with more tiles than that, one
+  // workgroup walks all of a tile's fields and makes its tables once.  (Each
+  // field's arithmetic is the same.)  Three species, y inverse of the weighted
+  // densities: FP64 16^3 12.2 -> 6.6 us, 64^3 16.6 -> 9.9; mixed 32^3 12.7 -> 6.7,
+  // 96^3 24.5 -> 16.1; no change from 128^3 on.
+  static int split(int tiles, int threads, int fields) {
+    const int waves = tiles * ((threads + 63) / 64);
+    return std::max(1, std::min(fields, 2048 / std::max(1, waves)));
+  }
   // maxS: the largest species count among the launch's instances
   static void tables(const TableArgs* a, int count, int M, int maxS, hipStream_t s) {
     const int items = maxS * ((maxS + 3) / 4 * 4) + maxS;  // pair-table entries + hs species
     hipLaunchKernelGGL(k_tables<T>, dim3((M + 255) / 256, items, count), dim3(256), 0, s, a);
   }
-  static void zfwd(const EvalArgs* a, int count, hipStream_t s) {
-    hipLaunchKernelGGL((k_zfwd<T, N, V>), dim3(count * G::tiles_z), dim3(G::RZ * G::TZ), 0, s, a);
+  static void zfwd(const EvalArgs* a, int count, int maxS, hipStream_t s) {
+    const int b = G::RZ * G::TZ, g = count * G::tiles_z;
+    hipLaunchKernelGGL((k_zfwd<T, N, V>), dim3(g, split(g, b, maxS)), dim3(b), 0, s, a);
   }
   // part: kPartAll, kPartMain (main-array tiles) or kPartNyquist (Nyquist-plane tiles)
   static int tiles_y(int part) { return part == kPartAll ? G::tiles_y : part == kPartMain ? (N * G::H) / G::PY : N / G::PY; }
@@ -40,8 +55,10 @@ template <typename T, int N, int V = 0> struct Launch {
   static constexpr int TXG = N / G::EXG;
   static constexpr bool four = G::kXMax < 4;
   static constexpr int EX4 = G::EX > 8 ? 8 : G::EX > 4 ? 4 : G::EX;  // of four species where kXMax is three
-  static void ystep(const EvalArgs* a, int count, int sel, int nf, bool fwd, int part, hipStream_t s) {
-    const dim3 g(count * tiles_y(part)), b(G::PY * G::TY);
+  // maxf: the most fields of an instance (kVecItems in the vector mode)
+  static void ystep(const EvalArgs* a, int count, int sel, int nf, int maxf, bool fwd, int part, hipStream_t s) {
+    const int tiles = count * tiles_y(part);
+    const dim3 g(tiles, split(tiles, G::PY * G::TY, nf == kVecMode ? kVecItems : maxf)), b(G::PY * G::TY);
     if (fwd)
       hipLaunchKernelGGL((k_ystep<T, N, true, V>), g, b, 0, s, a, sel, nf, part);
     else
@@ -73,14 +90,27 @@ template <typename T, int N, int V = 0> struct Launch {
   // hard-sphere functionals among the instances (1 Rosenfeld, 2 White Bear),
   // one launch of the matching variant each
   static void zderiv(const EvalArgs* a, int count, bool phi, int fmask, hipStream_t s) {
-    const dim3 g(count * GD::tiles), b(GD::RDD * GD::TZD);
-    if (fmask & 1) {
-      if (phi) hipLaunchKernelGGL((k_zderiv<T, N, true, false, EZD, V>), g, b, 0, s, a);
-      else hipLaunchKernelGGL((k_zderiv<T, N, false, false, EZD, V>), g, b, 0, s, a);
-    }
-    if (fmask & 2) {
-      if (phi) hipLaunchKernelGGL((k_zderiv<T, N, true, true, EZD, V>), g, b, 0, s, a);
-      else hipLaunchKernelGGL((k_zderiv<T, N, false, true, EZD, V>), g, b, 0, s, a);
+    if constexpr (kFieldWaves) {
+      using GF = GeoF<T, N, EZF>;
+      const dim3 g(count * GF::tiles), b(GF::threads);
+      if (fmask & 1) {
+        if (phi) hipLaunchKernelGGL((k_zderiv_fields<T, N, true, false, EZF>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_zderiv_fields<T, N, false, false, EZF>), g, b, 0, s, a);
+      }
+      if (fmask & 2) {
+        if (phi) hipLaunchKernelGGL((k_zderiv_fields<T, N, true, true, EZF>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_zderiv_fields<T, N, false, true, EZF>), g, b, 0, s, a);
+      }
+    } else {
+      const dim3 g(count * GD::tiles), b(GD::RDD * GD::TZD);
+      if (fmask & 1) {
+        if (phi) hipLaunchKernelGGL((k_zderiv<T, N, true, false, EZD, V>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_zderiv<T, N, false, false, EZD, V>), g, b, 0, s, a);
+      }
+      if (fmask & 2) {
+        if (phi) hipLaunchKernelGGL((k_zderiv<T, N, true, true, EZD, V>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((k_zderiv<T, N, false, true, EZD, V>), g, b, 0, s, a);
+      }
     }
   }
   static void xback(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
@@ -97,8 +127,10 @@ template <typename T, int N, int V = 0> struct Launch {
     if (sm.maxS() > 4)
       hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EXG, G::PX>), g, dim3(G::PX * TXG), 0, s, a, 5, part);
   }
-  static void zinv(const EvalArgs* a, int count, int sel, hipStream_t s) {
-    hipLaunchKernelGGL((k_zinv<T, N, V>), dim3(count * G::tiles_z), dim3(G::RZ * G::TZ), 0, s, a, sel);
+  // maxf: the most fields of an instance
+  static void zinv(const EvalArgs* a, int count, int sel, int maxf, hipStream_t s) {
+    const int b = G::RZ * G::TZ, g = count * G::tiles_z;
+    hipLaunchKernelGGL((k_zinv<T, N, V>), dim3(g, split(g, b, maxf)), dim3(b), 0, s, a, sel);
   }
   static void xplain(const EvalArgs* a, int count, int nf, bool fwd, hipStream_t s) {
     if (fwd)
@@ -119,8 +151,8 @@ template <typename T, int N, int V = 0> struct Launch {
   static constexpr uint32_t sched_alt =
       (G0::EZ != G2::EZ ? (1u << 1) | (1u << 9) : 0u) |
       (G0::EY != G2::EY ? (1u << 2) | (1u << 4) | (1u << 6) | (1u << 8) : 0u) |
-      (G0::EX != G2::EX ? (1u << 3) | (1u << 7) : 0u) | (ezd_of<T, N, 0>() != ezd_of<T, N, 2>() ? 1u << 5 : 0u);
-  static constexpr Ops ops{tables, zfwd, ystep, xfwd, zderiv, xback, GD::tiles, zinv, xplain, xport, sched_alt};
+      (G0::EX != G2::EX ? (1u << 3) | (1u << 7) : 0u) | ((kFieldWaves ? ezf_of<T, N, 0>() != ezf_of<T, N, 2>() : ezd_of<T, N, 0>() != ezd_of<T, N, 2>()) ? 1u << 5 : 0u);
+  static constexpr Ops ops{tables, zfwd, ystep, xfwd, zderiv, xback, kFieldWaves ? GeoF<T, N, EZF>::tiles : GD::tiles, zinv, xplain, xport, sched_alt};
 };
 
 template <typename T, int N, int V> const Ops* ops_inst() { return &Launch<T, N, V>::ops; }
