@@ -30,6 +30,10 @@ struct pnp_ctx_s {
   char* arena = nullptr;      // device ring for argument tables
   size_t arena_bytes = 0;
   size_t arena_pos = 0;
+  // status blocks read back by the current call (pinned host memory, and its
+  // device address)
+  uint32_t* pin = nullptr;
+  void* pin_dev = nullptr;
   // pass timing
   bool prof = false;
   uint32_t prof_mask = ~0u;                        // passes that record events
@@ -354,7 +358,10 @@ void fill_eval_args(EvalArgs& e, const Derived& d, const pnp_species* sp, const 
   e.nreal = d.S;
 }
 
-// copy host bytes into the context's device ring (stream ordered)
+// Copy host bytes into the context's device ring (stream ordered).  The few
+// KB of a single call go as kernel parameters: a copy from pageable memory
+// costs a staging copy, a blit and its gaps (about 12 us before the first
+// pass).  Larger lists take the copy.
 void* upload(pnp_ctx c, const void* src, size_t bytes, hipStream_t s) {
   const size_t need = up(bytes);
   if (c->arena_pos + need > c->arena_bytes) {
@@ -365,8 +372,17 @@ void* upload(pnp_ctx c, const void* src, size_t bytes, hipStream_t s) {
   }
   void* dst = c->arena + c->arena_pos;
   c->arena_pos += need;
-  if (hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) != hipSuccess) return nullptr;
-  return dst;
+  if (bytes > 3 * (size_t)kPutBytes)
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess ? dst : nullptr;
+  for (size_t at = 0; at < bytes; at += kPutBytes) {
+    PutBlob b;
+    const size_t n = std::min(bytes - at, (size_t)kPutBytes);
+    const int words = (int)((n + 15) / 16);
+    b.w[words - 1] = uint4{0, 0, 0, 0};
+    std::memcpy(&b, (const char*)src + at, n);
+    hipLaunchKernelGGL(k_put, dim3(1), dim3(kPutBytes / 16), 0, s, b, (uint4*)((char*)dst + at), words);
+  }
+  return hipPeekAtLastError() == hipSuccess ? dst : nullptr;
 }
 
 // the table and evaluation records of a launch list in one copy (each copy
@@ -398,11 +414,41 @@ pnp_status status_of(pnp_ctx c, const uint32_t st[2]) {
   return fail(c, PNP_E_OVERFLOW, "exp(-beta mu_ex) overflows" + at);
 }
 
+// The 16-byte blocks src[0..count) (null: zeros), each 16-byte aligned device
+// memory, as they are once the work on `s` so far is done: gathered by a kernel
+// into the context's pinned block, one wait for all (a copy to pageable
+// memory for each took about 16 us after the last kernel).  False on a HIP
+// error.
+constexpr int kPinBlocks = 1024;
+
+bool read_blocks(pnp_ctx c, const void* const* src, int count, uint32_t* words, hipStream_t s) {
+  for (int at = 0; at < count; at += kPinBlocks) {
+    const int n = std::min(count - at, kPinBlocks);
+    for (int k = 0; k < n; k += kGather) {
+      GatherList g;
+      const int m = std::min(n - k, kGather);
+      int any = -1;
+      for (int i = 0; i < m; ++i) {
+        g.src[i] = (const uint4*)src[at + k + i];
+        if (g.src[i]) any = i;
+      }
+      if (any < 0) continue;
+      for (int i = 0; i < m; ++i)
+        if (!g.src[i]) g.src[i] = g.src[any];
+      hipLaunchKernelGGL(k_gather_status, dim3(1), dim3(kGather), 0, s, g, (uint4*)c->pin_dev + k, m);
+      if (hipPeekAtLastError() != hipSuccess) return false;
+    }
+    if (hipStreamSynchronize(s) != hipSuccess) return false;
+    std::memcpy(words + 4 * (size_t)at, c->pin, 16 * (size_t)n);
+  }
+  for (int i = 0; i < count; ++i)
+    if (!src[i]) std::memset(words + 4 * (size_t)i, 0, 16);
+  return true;
+}
+
 pnp_status read_status(pnp_ctx c, const void* status_dev, hipStream_t s) {
-  uint32_t st[2] = {0, 0};
-  if (hipMemcpyAsync(st, status_dev, sizeof(st), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return device_check(c, "status read");
+  uint32_t st[4] = {0, 0, 0, 0};
+  if (!read_blocks(c, &status_dev, 1, st, s)) return device_check(c, "status read");
   return status_of(c, st);
 }
 
@@ -780,6 +826,13 @@ pnp_status pnp_create(int device, pnp_ctx* out) {
     delete c;
     return PNP_E_DEVICE;
   }
+  if (hipHostMalloc((void**)&c->pin, 16 * (size_t)kPinBlocks, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(&c->pin_dev, c->pin, 0) != hipSuccess) {
+    if (c->pin) (void)hipHostFree(c->pin);
+    (void)hipFree(c->arena);
+    delete c;
+    return PNP_E_DEVICE;
+  }
   c->scratch = scratch_address(device);  // with `device` current; null: the no-alloc call reports it
   *out = c;
   return PNP_OK;
@@ -792,6 +845,7 @@ void pnp_destroy(pnp_ctx c) {
     hipDeviceSynchronize();
     hipFree(c->arena);
   }
+  if (c->pin) (void)hipHostFree(c->pin);
   if (c->side) (void)hipStreamDestroy(c->side);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
@@ -1022,9 +1076,11 @@ pnp_status pnp_free_energy(pnp_ctx ctx, const pnp_grid* g, int32_t S, const pnp_
                      d.hs ? op->zderiv_tiles : 0, (const double*)part, kEnergyBlocks, h3, el_scale, sh_scale, res);
   st = device_check(ctx, "energy launch");
   if (st != PNP_OK) return st;
-  if (hipMemcpyAsync(energies, res, 4 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess)
-    return device_check(ctx, "energy read");
-  return read_status(ctx, w + L.status, s);
+  const void* src[3] = {res, res + 2, w + L.status};
+  uint32_t words[12];
+  if (!read_blocks(ctx, src, 3, words, s)) return device_check(ctx, "energy read");
+  std::memcpy(energies, words, 4 * sizeof(double));
+  return status_of(ctx, words + 8);
 }
 
 pnp_status pnp_equilibrium(pnp_ctx ctx, const pnp_grid* g, int32_t S, const pnp_species* sp, double T,
@@ -1077,9 +1133,8 @@ pnp_status pnp_equilibrium(pnp_ctx ctx, const pnp_grid* g, int32_t S, const pnp_
     st = device_check(ctx, "picard launch");
     if (st != PNP_OK) return st;
     uint32_t stw[4] = {0, 0, 0, 0};
-    if (hipMemcpyAsync(stw, w + L.status, sizeof(stw), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return device_check(ctx, "residual read");
+    const void* src = w + L.status;
+    if (!read_blocks(ctx, &src, 1, stw, s)) return device_check(ctx, "residual read");
     st = status_of(ctx, stw);
     *iters = it;
     std::memcpy(residual, stw + 2, sizeof(double));
@@ -1260,15 +1315,13 @@ pnp_status pnp_batch_mu_ex(pnp_ctx ctx, int32_t count, pnp_request* reqs, void* 
     if (reqs[r].status == PNP_OK && (reqs[r].params->flags & PNP_FLAG_ASYNC)) async = true;
   if (async) return PNP_OK;
   // one synchronisation for the whole batch, then each request's own status
-  std::vector<uint32_t> words(2 * (size_t)count, 0u);
+  std::vector<const void*> src(count, nullptr);
   for (int r = 0; r < count; ++r)
-    if (reqs[r].status == PNP_OK)
-      if (hipMemcpyAsync(&words[2 * r], (char*)reqs[r].workspace + lay[r].status, 8, hipMemcpyDeviceToHost, s) !=
-          hipSuccess)
-        return device_check(ctx, "status read");
-  if (hipStreamSynchronize(s) != hipSuccess) return device_check(ctx, "batch sync");
+    if (reqs[r].status == PNP_OK) src[r] = (char*)reqs[r].workspace + lay[r].status;
+  std::vector<uint32_t> words(4 * (size_t)count, 0u);
+  if (!read_blocks(ctx, src.data(), count, words.data(), s)) return device_check(ctx, "batch sync");
   for (int r = 0; r < count; ++r)
-    if (reqs[r].status == PNP_OK) reqs[r].status = status_of(ctx, &words[2 * r]);
+    if (reqs[r].status == PNP_OK) reqs[r].status = status_of(ctx, &words[4 * r]);
   return PNP_OK;
 }
 
@@ -1416,14 +1469,10 @@ pnp_status pnp_plan_status(pnp_plan plan, void* stream, int32_t* status) {
   pnp_ctx ctx = plan->ctx;
   if (hipSetDevice(ctx->device) != hipSuccess) return device_check(ctx, "set device");
   hipStream_t s = (hipStream_t)stream;
-  std::vector<uint32_t> words(2 * (size_t)plan->count, 0u);
+  std::vector<uint32_t> words(4 * (size_t)plan->count, 0u);
+  if (!read_blocks(ctx, plan->status.data(), plan->count, words.data(), s)) return device_check(ctx, "plan sync");
   for (int r = 0; r < plan->count; ++r)
-    if (plan->status[r] &&
-        hipMemcpyAsync(&words[2 * r], plan->status[r], 8, hipMemcpyDeviceToHost, s) != hipSuccess)
-      return device_check(ctx, "status read");
-  if (hipStreamSynchronize(s) != hipSuccess) return device_check(ctx, "plan sync");
-  for (int r = 0; r < plan->count; ++r)
-    status[r] = plan->valid[r] != PNP_OK ? plan->valid[r] : status_of(ctx, &words[2 * r]);
+    status[r] = plan->valid[r] != PNP_OK ? plan->valid[r] : status_of(ctx, &words[4 * r]);
   return PNP_OK;
 }
 

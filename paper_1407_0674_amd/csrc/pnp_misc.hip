@@ -22,6 +22,26 @@ __global__ void __launch_bounds__(256) k_copy(const uint4* __restrict__ src, uin
   }
 }
 
+// Up to kPutBytes of host bytes, handed over as a kernel parameter, to device
+// memory (16-byte words).
+constexpr int kPutBytes = 3072;
+struct PutBlob {
+  uint4 w[kPutBytes / 16];
+};
+__global__ void __launch_bounds__(kPutBytes / 16) k_put(PutBlob b, uint4* dst, int words) {
+  if ((int)threadIdx.x < words) dst[threadIdx.x] = b.w[threadIdx.x];
+}
+
+// The status blocks (four words each) of up to kGather requests into pinned
+// host memory.
+constexpr int kGather = 64;
+struct GatherList {
+  const uint4* src[kGather];
+};
+__global__ void __launch_bounds__(kGather) k_gather_status(GatherList g, uint4* dst, int count) {
+  if ((int)threadIdx.x < count) dst[threadIdx.x] = *g.src[threadIdx.x];
+}
+
 // Grid of the density updates over [S][n3]: one species per blockIdx.y, so no
 // thread divides a flat index by n3 (a 64-bit division per element costs more
 // than its memory traffic).
