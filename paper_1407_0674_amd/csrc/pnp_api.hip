@@ -805,6 +805,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
     pt.begin(9); os.at(9)->zinv(dea + k, 1, 2, S, s); pt.end();
     if (k < 3) sq.fork();  // the next term's Nyquist tiles rewrite what this z pass read
   }
+  if (d.aperiodic) return device_check(ctx, "launch");  // only the domain part is written: the crop checks it
   const long sn3 = (long)S * n3;
   const int blocks = (int)std::min<long>((sn3 + 255) / 256, 4096);
   hipLaunchKernelGGL(k_sum_exp, dim3(blocks), dim3(256), 0, s, (const double*)mu, slot, sn3,

@@ -566,6 +566,23 @@ __device__ __forceinline__ uint64_t spec_bytes(const EvalArgs& a, int nf) {
   return (uint64_t)nf * a.fstride * sizeof(cx<T>);
 }
 
+// Aperiodic mode (a.ext_n = N / 2): every field is zero, or is not wanted, at
+// x >= ext_n, y >= ext_n or z >= ext_n in real space, so the passes take only
+// what lies inside: a z pass the rows, a y or x pass before its axis is
+// transformed the first half of each pencil, and the tiles of the other planes
+// are left alone.  What they would hold is never read: elements of the second
+// half are addressed past the end of the buffer (loads give zero, stores are
+// dropped).  Mixed 64^3 domain on 128^3, three species: see the last pass.
+constexpr uint32_t kPastEnd = 0x80000000u;  // beyond any spectral buffer (at most 1.4 GB)
+
+// whether no row of a z-pass tile of R rows lies inside
+template <int N, int R>
+__device__ __forceinline__ bool rows_outside(const EvalArgs& a, int tile) {
+  if (a.ext_n == 0) return false;
+  const int row = tile * R;
+  return row / N >= a.ext_n || ((N / 2) % R == 0 && row % N >= a.ext_n);
+}
+
 // P1: z r2c of the S input densities (float64) into specA (each gridDim.y-th
 // species per workgroup)
 template <typename T, int N, int V = 0>
@@ -588,6 +605,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
 #pragma unroll
     for (int s = 0; s < kMaxSpecies; ++s) gbl(a.dc)[s] = 0.0;
   }
+  if (rows_outside<N, RZ>(a, tile)) return;  // uniform per block
   __syncthreads();
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;
   const uint32_t row = (uint32_t)(tile * RZ + r);
@@ -644,6 +662,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
   __shared__ cx<T> xch[RZ * H];
   int tile;
   const EvalArgs& a = args[inst_of(G::tiles_z, tile)];
+  if (rows_outside<N, RZ>(a, tile)) return;  // uniform per block
   init_twiddles<T, H>(twH);
   init_twiddles<T, N>(twN);
   __syncthreads();
@@ -943,7 +962,7 @@ __global__ void __launch_bounds__((GeoD<T, N, EZD, V>::RDD * GeoD<T, N, EZD, V>:
   __shared__ LogEntry logt[kLogTable];
   int tile;
   const EvalArgs& a = args[inst_of(D::tiles, tile)];
-  if (!a.hs_on || (a.hs_wb != 0) != WB) return;  // uniform per block
+  if (!a.hs_on || (a.hs_wb != 0) != WB || rows_outside<N, RD>(a, tile)) return;  // uniform per block
   const int t = threadIdx.x % TZ, r = threadIdx.x / TZ;
   const uint32_t row = (uint32_t)(tile * RD + r);
   const Row lp{xch + r * P0};
@@ -1163,7 +1182,7 @@ __global__ void __launch_bounds__((GeoF<T, N, EZF>::threads))
   __shared__ LogEntry logt[kLogTable];
   int tile;
   const EvalArgs& a = args[inst_of(D::tiles, tile)];
-  if (!a.hs_on || (a.hs_wb != 0) != WB) return;  // uniform per block
+  if (!a.hs_on || (a.hs_wb != 0) != WB || rows_outside<N, RW>(a, tile)) return;  // uniform per block
   const int f = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x & 63;
   const int t = lane % TZ, r = lane / TZ;
   const uint32_t row = (uint32_t)(tile * RW + r);
@@ -1317,12 +1336,16 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
   int tile;
   const EvalArgs& a = args[inst_of_part((N * H) / PY, N / PY, part, tile)];
   if (sel == 1 && !a.hs_on) return;  // uniform per block
+  constexpr int tiles_main = (N * H) / PY;
+  // aperiodic mode: only planes x < ext_n, read (forward) or written (inverse)
+  // at y < ext_n
+  if (a.ext_n != 0 && (tile < tiles_main ? tile * PY / H : (tile - tiles_main) * PY) >= a.ext_n) return;
+  const uint32_t past = __builtin_amdgcn_readfirstlane(a.ext_n != 0 ? kPastEnd : 0u);
   init_twiddles<T, N>(tw);
   __syncthreads();
   const bool vec = nf_code == kVecMode;
   const int nf = nf_code == -1 ? a.S : vec ? kFields : nf_code;
   const BufN<N> base = make_buf<stream_policy<N>()>(sel == 0 ? a.specA : sel == 1 ? a.specB : a.specC, spec_bytes<T>(a, nf));
-  constexpr int tiles_main = (N * H) / PY;
   uint32_t off, es;
   int t;
   LdsPencil<T> lp;
@@ -1345,6 +1368,8 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
 #pragma unroll
   for (int m = 0; m < EY; ++m) eo[m] = (off + (uint32_t)(t + TY * m) * es) * (uint32_t)sizeof(cx<T>);
   const uint32_t fbytes = (uint32_t)(a.fstride * sizeof(cx<T>));
+  auto in = [&](int m) { return FWD && m >= EY / 2 ? eo[m] + past : eo[m]; };
+  auto to = [&](int m) { return !FWD && m >= EY / 2 ? eo[m] + past : eo[m]; };
   // work items: the fields, in the vector mode the two vectors first; each
   // gridDim.y-th belongs to this workgroup
   const int items = vec ? kVecItems : nf;
@@ -1355,10 +1380,10 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
       const uint32_t so = (uint32_t)f * fbytes;
       cx<T> v[EY];
 #pragma unroll
-      for (int m = 0; m < EY; ++m) v[m] = base.template ld<cx<T>>(eo[m], so);
+      for (int m = 0; m < EY; ++m) v[m] = base.template ld<cx<T>>(in(m), so);
       fft_pencil<T, N, EY, FWD>(v, t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(v[m], eo[m], so);
+      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(v[m], to(m), so);
       continue;
     }
     const int b = it;
@@ -1370,28 +1395,28 @@ __global__ void __launch_bounds__((Geo<T, N, V>::PY * Geo<T, N, V>::TY))
       // Q -> [y] = y-inverse of i s_y sc Q and [z] = y-inverse of Q
       cx<T> q[EY], w[EY];
 #pragma unroll
-      for (int m = 0; m < EY; ++m) q[m] = base.template ld<cx<T>>(eo[m], sz_off);
+      for (int m = 0; m < EY; ++m) q[m] = base.template ld<cx<T>>(in(m), sz_off);
 #pragma unroll
       for (int m = 0; m < EY; ++m) w[m] = q[m];
       mul_isy<T, N, EY, TY>(w, t, sc);
       fft_pencil<T, N, EY, false>(w, t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(w[m], eo[m], sy_off);
+      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(w[m], to(m), sy_off);
       fft_pencil<T, N, EY, false>(q, t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(q[m], eo[m], sz_off);
+      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(q[m], to(m), sz_off);
     } else {
       // [z] <- i s_y sc (y-forward of F_y) + y-forward of [z]
       cx<T> fy[EY], g[EY];
 #pragma unroll
-      for (int m = 0; m < EY; ++m) fy[m] = base.template ld<cx<T>>(eo[m], sy_off);
+      for (int m = 0; m < EY; ++m) fy[m] = base.template ld<cx<T>>(in(m), sy_off);
 #pragma unroll
-      for (int m = 0; m < EY; ++m) g[m] = base.template ld<cx<T>>(eo[m], sz_off);
+      for (int m = 0; m < EY; ++m) g[m] = base.template ld<cx<T>>(in(m), sz_off);
       fft_pencil<T, N, EY, true>(fy, t, tw, lp);
       mul_isy<T, N, EY, TY>(fy, t, sc);
       fft_pencil<T, N, EY, true>(g, t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(cadd<T>(g[m], fy[m]), eo[m], sz_off);
+      for (int m = 0; m < EY; ++m) base.template st<cx<T>>(cadd<T>(g[m], fy[m]), to(m), sz_off);
     }
   }
 }
@@ -1554,12 +1579,16 @@ static_assert(back_field(5) == kSlotN3, "the k = 0 sum of the streamed back pass
 // Per-lane addressing of an x tile: element m of the lane's pencil sits at
 // byte vo + m * mstride (+ the field offset).  Both strides are uniform over
 // the block, which keeps them in scalar registers.
+// In the aperiodic mode the second half of a pencil (x >= ext_n) is addressed
+// past the end of the buffer.
 template <typename T, int N, int EX, int PX>
 struct XAddr {
-  uint32_t vo, mstride;
-  __device__ __forceinline__ XAddr(const XPencil<T, N, PX>& pc, int t) {
+  uint32_t lo, hi, mstride;
+  __device__ __forceinline__ uint32_t vo(int m) const { return m >= EX / 2 ? hi : lo; }
+  __device__ __forceinline__ XAddr(const XPencil<T, N, PX>& pc, int t, const EvalArgs& a) {
     constexpr int TX = N / EX;
-    vo = (pc.off + (uint32_t)t * pc.es) * (uint32_t)sizeof(cx<T>);
+    lo = (pc.off + (uint32_t)t * pc.es) * (uint32_t)sizeof(cx<T>);
+    hi = lo + (a.ext_n != 0 ? kPastEnd : 0u);
     mstride = __builtin_amdgcn_readfirstlane((uint32_t)TX * pc.es * (uint32_t)sizeof(cx<T>));
   }
 };
@@ -1664,14 +1693,14 @@ __global__ void __launch_bounds__((PX * (N / EX)), 2)
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
-  const XAddr<T, N, EX, PX> xa(pc, t);
+  const XAddr<T, N, EX, PX> xa(pc, t, a);
   // the pencils of all species are in flight while the tables are made
   cx<T> r[CH][EX];
 #pragma unroll
   for (int c = 0; c < CH; ++c)
     if (c < S) {  // uniform
 #pragma unroll
-      for (int m = 0; m < EX; ++m) r[c][m] = A.template ld<cx<T>>(xa.vo, (uint32_t)c * fbytes + m * xa.mstride);
+      for (int m = 0; m < EX; ++m) r[c][m] = A.template ld<cx<T>>(xa.vo(m), (uint32_t)c * fbytes + m * xa.mstride);
     }
   XW::template fill<TX>(wl, a, hs, S, t, p, pc.ky, pc.kz);
   init_twiddles<T, N>(tw);
@@ -1706,7 +1735,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), 2)
     }
     fft_pencil<T, N, EX, false>(v, t, tw, lp);
 #pragma unroll
-    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)slots[o] * fbytes + m * xa.mstride);
+    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo(m), (uint32_t)slots[o] * fbytes + m * xa.mstride);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -1748,7 +1777,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   const BufN<N> A = make_buf<stream_policy<N>()>(a.specA, spec_bytes<T>(a, S));
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, spec_bytes<T>(a, kFields));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
-  const XAddr<T, N, EX, PX> xa(pc, t);
+  const XAddr<T, N, EX, PX> xa(pc, t, a);
   int mm[EX];
   {
     const int sy = sgn_idx(pc.ky, N), sz = pc.kz;
@@ -1762,7 +1791,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   cx<T> b0[EX], b1[EX];
   // the first species' pencil is in flight while the twiddle table is built
 #pragma unroll
-  for (int m = 0; m < EX; ++m) b0[m] = A.template ld<cx<T>>(xa.vo, m * xa.mstride);
+  for (int m = 0; m < EX; ++m) b0[m] = A.template ld<cx<T>>(xa.vo(m), m * xa.mstride);
   const bool pre = sizeof(T) == 4 && S <= 3;  // uniform
   if constexpr (sizeof(T) == 4) {
     if (pre) {
@@ -1794,7 +1823,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
       cx<T>* nxt = (i & 1) ? b0 : b1;
       if (i + 1 < S) {
 #pragma unroll
-        for (int m = 0; m < EX; ++m) nxt[m] = A.template ld<cx<T>>(xa.vo, (uint32_t)(i + 1) * fbytes + m * xa.mstride);
+        for (int m = 0; m < EX; ++m) nxt[m] = A.template ld<cx<T>>(xa.vo(m), (uint32_t)(i + 1) * fbytes + m * xa.mstride);
       }
       fft_pencil<T, N, EX, true>(cur, t, tw, lp);
       const T R = (T)a.R[i], ar = (T)a.area[i], i4 = (T)(a.inv4piR[i] * a.kscale);
@@ -1850,7 +1879,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
     for (int m = 0; m < EX; ++m) v[m] = cscale<T>(acc[o][m], sc);
     fft_pencil<T, N, EX, false>(v, t, tw, lp);
 #pragma unroll
-    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)o * fbytes + m * xa.mstride);
+    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo(m), (uint32_t)o * fbytes + m * xa.mstride);
   }
   // vector weighted densities: [4] = i s_x Q and [6] = Q, [7] = i s_x k0 n3
   // (the y and z components are formed by the y and z passes)
@@ -1865,7 +1894,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
     fft_pencil<T, N, EX, false>(v, t, tw, lp);
     const int slot = c == 0 ? kSlotX : c == 1 ? kSlotZ : kSlotX + kVecStride;
 #pragma unroll
-    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo, (uint32_t)slot * fbytes + m * xa.mstride);
+    for (int m = 0; m < EX; ++m) B.template st<cx<T>>(v[m], xa.vo(m), (uint32_t)slot * fbytes + m * xa.mstride);
   }
 }
 
@@ -1903,7 +1932,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
   const BufN<N> B = make_buf<stream_policy<N>()>(a.specB, hs_on ? spec_bytes<T>(a, kFields) : 0);
   const BufN<N> C = make_buf<stream_policy<N>()>(a.specC, spec_bytes<T>(a, S));
   const uint32_t fbytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.fstride * sizeof(cx<T>)));
-  const XAddr<T, N, EX, PX> xa(pc, t);
+  const XAddr<T, N, EX, PX> xa(pc, t, a);
   cx<T> out[CH][EX];
   cx<T> b0[EX], b1[EX];
   // FP32: the k = 0 coefficient of each result is summed in double by the
@@ -1926,11 +1955,11 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
   // the first pencil of the stream is in flight while the tables are made
   if (hs_on) {
 #pragma unroll
-    for (int m = 0; m < EX; ++m) b0[m] = B.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
+    for (int m = 0; m < EX; ++m) b0[m] = B.template ldnt<cx<T>>(xa.vo(m), m * xa.mstride);
     XW::template fill<TX>(wl, a, hs, S, t, p, pc.ky, pc.kz);
   } else if (pair_on) {
 #pragma unroll
-    for (int m = 0; m < EX; ++m) b1[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
+    for (int m = 0; m < EX; ++m) b1[m] = A.template ldnt<cx<T>>(xa.vo(m), m * xa.mstride);
   }
   init_twiddles<T, N>(tw);
   __syncthreads();
@@ -1955,11 +1984,11 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
       if (q + 1 < kBackFields) {
         const int f1 = back_field(q + 1);
 #pragma unroll
-        for (int m = 0; m < EX; ++m) nxt[m] = B.template ldnt<cx<T>>(xa.vo, (uint32_t)f1 * fbytes + m * xa.mstride);
+        for (int m = 0; m < EX; ++m) nxt[m] = B.template ldnt<cx<T>>(xa.vo(m), (uint32_t)f1 * fbytes + m * xa.mstride);
       } else if (pair_on) {
         // the first density pencil is in flight during the last transform
 #pragma unroll
-        for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, m * xa.mstride);
+        for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo(m), m * xa.mstride);
       }
       fft_pencil<T, N, EX, true>(cur, t, tw, lp);
       const int f = back_field(q);
@@ -1997,7 +2026,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
         cx<T>* nxt = (j & 1) ? b1 : b0;
         if (j + 1 < S) {
 #pragma unroll
-          for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo, (uint32_t)(j + 1) * fbytes + m * xa.mstride);
+          for (int m = 0; m < EX; ++m) nxt[m] = A.template ldnt<cx<T>>(xa.vo(m), (uint32_t)(j + 1) * fbytes + m * xa.mstride);
         }
         // G_{0..3, j} of row [m][j][.]: one gather per element, issued before
         // the transform where the registers hold them, else eight at a time
@@ -2054,7 +2083,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
       for (int m = 0; m < EX; ++m) out[c][m] = cscale<T>(out[c][m], sc);
       fft_pencil<T, N, EX, false>(out[c], t, tw, lp);
 #pragma unroll
-      for (int m = 0; m < EX; ++m) C.template st<cx<T>>(out[c][m], xa.vo, (uint32_t)c * fbytes + m * xa.mstride);
+      for (int m = 0; m < EX; ++m) C.template st<cx<T>>(out[c][m], xa.vo(m), (uint32_t)c * fbytes + m * xa.mstride);
     }
   }
 }
@@ -2097,7 +2126,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   }
   uint32_t eo[EX];
 #pragma unroll
-  for (int m = 0; m < EX; ++m) eo[m] = (pc.off + (uint32_t)(t + TX * m) * pc.es) * (uint32_t)sizeof(cx<T>);
+  for (int m = 0; m < EX; ++m)
+    eo[m] = (pc.off + (uint32_t)(t + TX * m) * pc.es) * (uint32_t)sizeof(cx<T>) + (m >= EX / 2 && a.ext_n != 0 ? kPastEnd : 0u);
   cx<T> F[5][EX];  // n0..n2, [3] - i s_x k0 [7], i s_x [4] + [6]
 #pragma unroll
   for (int q = 0; q < 5; ++q)
