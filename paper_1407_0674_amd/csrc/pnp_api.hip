@@ -215,13 +215,12 @@ Layout layout_of(int n, int S, int precision, bool hs, bool pairs, bool per_term
 // aperiodic_ok: the entry point accepts PNP_FLAG_APERIODIC (the evaluation
 // then runs on the doubled grid, and d.n is that grid's size)
 // The aperiodic mode adds, after the evaluation workspace of the doubled
-// grid n2: the doubled-grid output and the doubled-grid EC response to the
-// domain's bulk densities (EC only); float64 [S][n2^3], the output
-// [3][S][n2^3] in per-term mode.  (The zero extension itself is read on the
+// grid n2: the doubled-grid output, float64 [S][n2^3] ([3][S][n2^3] in per-term
+// mode), and the bulk table (EC only).  (The zero extension itself is read on the
 // fly by the first pass.)
 struct LayoutAp {
   Layout L;
-  size_t muA, muB, total;
+  size_t muA, bulk, total;
 };
 
 LayoutAp layout_aperiodic(int n2, int S, int precision, bool hs, bool pairs, bool ec, bool per_term) {
@@ -230,7 +229,7 @@ LayoutAp layout_aperiodic(int n2, int S, int precision, bool hs, bool pairs, boo
   const size_t f = sizeof(double) * (size_t)S * n2 * n2 * n2;
   size_t o = A.L.total;
   A.muA = o; o = up(o + (per_term ? 3 : 1) * f);
-  A.muB = o; if (ec) o = up(o + f);
+  A.bulk = o; if (ec) o = up(o + sizeof(double) * (size_t)A.L.M * padded_species(S));
   A.total = o;
   return A;
 }
@@ -327,6 +326,12 @@ void fill_table_args(TableArgs& t, const Derived& d, const pnp_species* sp, doub
     for (int j = 0; j < d.S; ++j) t.pidx[i][j] = (int8_t)d.pi[i][j];
   t.Sp = padded_species(d.S);
   t.hs_tab = hs; t.pair_tab = pair;
+}
+
+// the bulk table of the aperiodic mode (null: none)
+void set_bulk(TableArgs& t, const pnp_species* sp, void* bulk) {
+  t.bulk_tab = bulk;
+  for (int i = 0; i < t.S && bulk; ++i) t.rho_b[i] = sp[i].rho_bulk;
 }
 
 void fill_eval_args(EvalArgs& e, const Derived& d, const pnp_species* sp, const Layout& L, char* ws,
@@ -743,7 +748,7 @@ struct pnp_plan_s {
 // per-workgroup sums of Phi_hs.
 static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid* g, const pnp_species* sp,
                           const double* rho, const pnp_params* p, const Layout& L, char* w, double* mu,
-                          double* slot, double* phi_part, hipStream_t s) {
+                          double* slot, double* phi_part, hipStream_t s, void* bulk = nullptr) {
   const int S = d.S;
   const bool pairs = d.ec || d.sw;
   const OpsSel os = select_ops(ctx, d.precision, d.n, 1);
@@ -754,6 +759,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   fill_table_args(ta[0], d, sp, g->h, sw_c, d.ec, false, w + L.hs, pairs ? w + L.pair : nullptr, L.M);
   fill_table_args(ta[1], d, sp, g->h, sw_c, false, d.sw, w + L.hs, pairs ? w + L.pair2 : nullptr,
                   L.M);
+  set_bulk(ta[0], sp, bulk);  // aperiodic mode with EC
   // four argument records: forward half, hs-only, el-only, sh-only
   EvalArgs ea[4];
   for (int k = 0; k < 4; ++k) {
@@ -764,7 +770,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   ea[0].out = mu;
   ea[1].out = mu; ea[1].pair_on = 0;
   for (int i = 0; i < S; ++i) ea[1].cfin[i] = 0.0;
-  ea[2].out = mu + (long)S * n3; ea[2].hs_on = 0; ea[2].pair_on = d.ec;
+  ea[2].out = mu + (long)S * n3; ea[2].hs_on = 0; ea[2].pair_on = d.ec; ea[2].bulk_tab = bulk;
   ea[3].out = mu + 2L * S * n3; ea[3].hs_on = 0; ea[3].pair_on = d.sw; ea[3].pair_tab = w + L.pair2;
   for (int i = 0; i < S; ++i) ea[3].cfin[i] = 0.0;
   if (!d.ec) for (int i = 0; i < S; ++i) ea[2].cfin[i] = 0.0;
@@ -911,9 +917,10 @@ pnp_status pnp_workspace_bytes(pnp_ctx ctx, const pnp_grid* g, int32_t S, const 
   return PNP_OK;
 }
 
-// The aperiodic evaluation (Sec. 3.4): extend, the EC response to the
-// domain's bulk densities (EC only), the evaluation of the extended densities
-// on the doubled grid, and the domain part of their difference.
+// The aperiodic evaluation (Sec. 3.4): the evaluation of the extended
+// densities on the doubled grid, less the EC response to the domain's bulk
+// densities (-sum_j C_ij (*) rho_b,j chi_domain, which the back pass subtracts
+// in closed form), and the domain part of the result.
 static pnp_status enqueue_aperiodic(pnp_ctx ctx, const Derived& d, const pnp_grid* g, const pnp_species* sp,
                                     const double* rho, const pnp_params* p, const LayoutAp& A, char* w, double* mu,
                                     double* slot, hipStream_t s) {
@@ -921,35 +928,15 @@ static pnp_status enqueue_aperiodic(pnp_ctx ctx, const Derived& d, const pnp_gri
   const Layout& L = A.L;
   const bool pairs = d.ec || d.sw;
   double* muA = (double*)(w + A.muA);
-  double* muB = d.ec ? (double*)(w + A.muB) : nullptr;
+  void* bulk = d.ec ? w + A.bulk : nullptr;
   const OpsSel ops = select_ops(ctx, d.precision, d.n, 1);
-  if (d.ec) {
-    // -sum_j C_ij (*) rho_b,j chi_domain: the EC term alone, no constant
-    Derived dB = d;
-    dB.hs = dB.wb = dB.sw = false;
-    TableArgs ta;
-    fill_table_args(ta, dB, sp, g->h, p->sw_prefactor, true, false, w + L.hs, w + L.pair, L.M);
-    EvalArgs ea;
-    fill_eval_args(ea, dB, sp, L, w, nullptr);
-    ea.ext_bulk = 1;
-    for (int i = 0; i < S; ++i) {
-      ea.cfin[i] = 0.0;
-      ea.ext_val[i] = sp[i].rho_bulk;
-    }
-    ea.out = muB;
-    ea.slot = nullptr;
-    const TableArgs* dta = nullptr;
-    const EvalArgs* dea = nullptr;
-    upload_args(ctx, &ta, 1, &ea, 1, s, dta, dea);
-    if (!dta || !dea) return device_check(ctx, "argument upload");
-    run_sequence(ctx, ops, dea, dta, 1, L.M, 0, mix_of(S), s, d.n);
-  }
-  // the extended densities (their status word starts clean here)
   if (!p->per_term) {
     TableArgs ta;
     fill_table_args(ta, d, sp, g->h, p->sw_prefactor, d.ec, d.sw, w + L.hs, pairs ? w + L.pair : nullptr, L.M);
+    set_bulk(ta, sp, bulk);
     EvalArgs ea;
     fill_eval_args(ea, d, sp, L, w, rho);
+    ea.bulk_tab = bulk;
     ea.out = muA;
     ea.slot = nullptr;
     const TableArgs* dta = nullptr;
@@ -958,12 +945,12 @@ static pnp_status enqueue_aperiodic(pnp_ctx ctx, const Derived& d, const pnp_gri
     if (!dta || !dea) return device_check(ctx, "argument upload");
     run_sequence(ctx, ops, dea, dta, 1, L.M, hs_mask(d), mix_of(S), s, d.n);
   } else {
-    const pnp_status st = enqueue_per_term(ctx, d, g, sp, rho, p, L, w, muA, nullptr, nullptr, s);
+    const pnp_status st = enqueue_per_term(ctx, d, g, sp, rho, p, L, w, muA, nullptr, nullptr, s, bulk);
     if (st != PNP_OK) return st;
   }
   const long N = (long)d.n_dom * d.n_dom * d.n_dom;
   const int cb = (int)std::min<long>((S * N + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_crop, dim3(cb), dim3(256), 0, s, (const double*)muA, (const double*)muB,
+  hipLaunchKernelGGL(k_crop, dim3(cb), dim3(256), 0, s, (const double*)muA,
                      p->per_term ? 3 : 1, S, d.n_dom, mu, slot, (uint32_t*)(w + L.status));
   return device_check(ctx, "launch");
 }

@@ -341,8 +341,19 @@ __device__ inline double d_j1x(double x) {
   return d_j1x(x, sn, cs);
 }
 
-// hs table [m][S][2] = (j0(kR), 4 pi R^3 j1(kR)/(kR)) (FP64 path only); pair table [m][j][i] (row length Sp) = G_ij, the combined
-// pair kernel, zero for i >= S.  One thread per (m, table entry): blockIdx.y
+// MSA correlation kernel of pair p (Sec. 2.3.4): 2 B ball - B^2 (r-ball) -
+// (1/r-ball), from ball, the transform of the ball of radius sigma, and the
+// cosine of y = k sigma.
+__device__ __forceinline__ double ec_kernel(const TableArgs& a, int p, double y, double sn, double cs, double ball) {
+  const double s = a.sigma[p], b = a.Bsig[p];
+  const double rball = 4.0 * kPi * s * s * s * s * d_rb(y, sn, cs);
+  const double irball = 4.0 * kPi * s * s * d_irb(y, cs);
+  return a.ec_pref[p] * (2.0 * b * ball - b * b * rball - irball);
+}
+
+// hs table [m][S][2] = (j0(kR), 4 pi R^3 j1(kR)/(kR)) (FP64 path only); pair
+// table [m][j][i] (row length Sp) = G_ij, the combined pair kernel, zero for
+// i >= S; bulk table [m][i] (row length Sp, made with the hs species).  One thread per (m, table entry): blockIdx.y
 // picks the entry (pair-table entries first, then the hs species), blockIdx.z
 // the instance.  G is symmetric, so the thread of entry (j, i) with i <= j
 // writes both (j, i) and (i, j), and those with i > j have nothing to do.
@@ -370,13 +381,7 @@ __global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ ta
     if (fabs(y) >= 0.5) sincos(y, &sn, &cs);
     const double ball = 4.0 * kPi * s * s * s * d_j1x(y, sn, cs);
     double v = 0.0;
-    if (a.ec_pref[p] != 0.0) {
-      // MSA correlation (Sec. 2.3.4): 2 B ball - B^2 (r-ball) - (1/r-ball)
-      const double b = a.Bsig[p];
-      const double rball = 4.0 * kPi * s * s * s * s * d_rb(y, sn, cs);
-      const double irball = 4.0 * kPi * s * s * d_irb(y, cs);
-      v += a.ec_pref[p] * (2.0 * b * ball - b * b * rball - irball);
-    }
+    if (a.ec_pref[p] != 0.0) v += ec_kernel(a, p, y, sn, cs, ball);
     if (a.sw_pref[p] != 0.0) {
       // square well (Sec. 2.3.2): the shell between sigma and r_out
       const double ro = a.rout[p];
@@ -384,8 +389,21 @@ __global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ ta
     }
     pr.template st<T>((T)v, (uint32_t)(((m * a.S + j) * a.Sp + i) * sizeof(T)));
     if (i != j) pr.template st<T>((T)v, (uint32_t)(((m * a.S + i) * a.Sp + j) * sizeof(T)));
-  } else if (sizeof(T) == 8 && item < npair + a.S) {  // the FP32 path evaluates these in registers
+  } else if (item < npair + a.S) {
     const int i = item - npair;
+    if (a.bulk_tab) {  // a row's padding is not read into a result
+      double v = 0.0;
+      for (int j = 0; j < a.S; ++j) {
+        const int p = a.pidx[i][j];
+        const double s = a.sigma[p], y = k * s;
+        double sn = 0.0, cs = 1.0;
+        if (fabs(y) >= 0.5) sincos(y, &sn, &cs);
+        v += a.rho_b[j] * ec_kernel(a, p, y, sn, cs, 4.0 * kPi * s * s * s * d_j1x(y, sn, cs));
+      }
+      const Buf bt = make_buf(a.bulk_tab, (uint64_t)a.M * a.Sp * sizeof(T));
+      bt.template st<T>((T)v, (uint32_t)((m * a.Sp + i) * sizeof(T)));
+    }
+    if constexpr (sizeof(T) == 4) return;  // the FP32 path evaluates these in registers
     const double R = a.R[i];
     const double x = k * R;
     double sn, cs;
@@ -572,7 +590,8 @@ __device__ __forceinline__ uint64_t spec_bytes(const EvalArgs& a, int nf) {
 // transformed the first half of each pencil, and the tiles of the other planes
 // are left alone.  What they would hold is never read: elements of the second
 // half are addressed past the end of the buffer (loads give zero, stores are
-// dropped).  Mixed 64^3 domain on 128^3, three species: see the last pass.
+// dropped).  Mixed 64^3 domain on 128^3, three species, all terms: 385 us a call
+// without, 304 us with.
 constexpr uint32_t kPastEnd = 0x80000000u;  // beyond any spectral buffer (at most 1.4 GB)
 
 // whether no row of a z-pass tile of R rows lies inside
@@ -630,17 +649,15 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     const uint32_t nd = (uint32_t)a.ext_n, x = row / N, y = row % N;
     const bool row_in = x < nd && y < nd;
     const uint32_t d3b = nd * nd * nd * (uint32_t)sizeof(double);
-    const BufN<N> rho = make_buf<stream_policy<N>()>(a.rho, a.ext_bulk ? 0 : (uint64_t)a.S * d3b);
+    const BufN<N> rho = make_buf<stream_policy<N>()>(a.rho, (uint64_t)a.S * d3b);
     for (int s = blockIdx.y; s < a.S; s += gridDim.y) {
       cx<T> v[EZ];
 #pragma unroll
       for (int m = 0; m < EZ; ++m) {
         const uint32_t j = t + TZ * m;
         cf64 p{0.0, 0.0};
-        if (row_in && 2 * j < nd) {
-          if (a.ext_bulk) p = cf64{a.ext_val[s], a.ext_val[s]};
-          else p = rho.template ldnt<cf64>(((x * nd + y) * nd + 2 * j) * (uint32_t)sizeof(double), (uint32_t)s * d3b);
-        }
+        if (row_in && 2 * j < nd)
+          p = rho.template ldnt<cf64>(((x * nd + y) * nd + 2 * j) * (uint32_t)sizeof(double), (uint32_t)s * d3b);
         v[m] = mk<T>((T)p.x, (T)p.y);
       }
       fft_pencil<T, H, EZ, true>(v, t, twH, lp);
@@ -1519,6 +1536,23 @@ __device__ __forceinline__ void hs_weights(const EvalArgs& a, const Buf& hs, int
   }
 }
 
+// The EC response to the domain's bulk densities (aperiodic mode) is a product
+// of known factors in k space: the bulk table times the transform of the
+// domain's indicator, a product over the axes.  Subtracting it in the back pass
+// costs one table row an element; evaluating it like a density took six more
+// passes (mixed 64^3 domain, three species: 304 us a call with them, 237 without).
+// The indicator's transform along one axis:
+// D_k = sum_{j < N/2} exp(-2 pi i k j / N) = N/2 at k = 0, 0 at the other even k
+// and 1 - i cot(pi k / N) at odd k; table for k in [0, N), made in double.
+template <typename T, int N>
+__device__ __forceinline__ void init_indicator(cx<T>* d) {
+  for (int k = threadIdx.x; k < N; k += blockDim.x) {
+    double s, c;
+    sincospi((double)k / (double)N, &s, &c);
+    d[k] = k == 0 ? mk<T>((T)(N / 2), (T)0) : k % 2 == 0 ? mk<T>((T)0, (T)0) : mk<T>((T)1, (T)(-c / s));
+  }
+}
+
 // FP32 weights of a thread's EX elements of one x pencil (element e at
 // kx = t + TX e), shared with the mirror thread.  |k| depends on kx only
 // through |sx|, and element e >= EX/2 of thread t has the |sx| of element
@@ -1952,6 +1986,8 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
     if constexpr (kDc && kFree) dcv[own0 ? q : kBackFields + CH] = x;
     else if (own0) dcv[q] = x;
   };
+  __shared__ cx<T> ind[N];
+  if (a.bulk_tab) init_indicator<T, N>(ind);
   // the first pencil of the stream is in flight while the tables are made
   if (hs_on) {
 #pragma unroll
@@ -2055,6 +2091,21 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
       }
     }
   }
+  if (a.bulk_tab) {  // uniform
+    const int sy = sgn_idx(pc.ky, N), m0 = sy * sy + pc.kz * pc.kz;
+    const cx<T> dyz = cmul<T>(ind[pc.ky], ind[pc.kz]);
+    const Buf bt = make_buf(a.bulk_tab, table_m<T, N>(0) * a.Sp * sizeof(T));
+#pragma unroll
+    for (int m = 0; m < EX; ++m) {
+      const int sx = sgn_idx(t + TX * m, N);
+      const v4<T> g = bt.template ld<v4<T>>((uint32_t)((sx * sx + m0) * a.Sp) * (uint32_t)sizeof(T));
+      const cx<T> chi = cmul<T>(dyz, ind[t + TX * m]);
+      cfma<T>(out[0][m], chi, -g.x);
+      if constexpr (CH > 1) cfma<T>(out[1][m], chi, -g.y);
+      if constexpr (CH > 2) cfma<T>(out[2][m], chi, -g.z);
+      if constexpr (CH > 3) cfma<T>(out[3][m], chi, -g.w);
+    }
+  }
   if (own0) {
     // j0 = 1, w3 = 4 pi R^3 / 3 and the pair rows at k = 0; the vector fields
     // have no part there (s = 0)
@@ -2070,6 +2121,9 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
 #pragma unroll 1
         for (int j = 0; j < S; ++j)
           d += (double)pt.template ld<T>((uint32_t)(j * a.Sp + c) * (uint32_t)sizeof(T)) * (double)dcv[kBackFields + j];
+      if (a.bulk_tab)
+        d -= (double)make_buf(a.bulk_tab, a.Sp * sizeof(T)).template ld<T>((uint32_t)c * (uint32_t)sizeof(T)) *
+             ((double)(N / 2) * (N / 2) * (N / 2));
       g[c] = d * a.inv_n3;
     }
 #pragma unroll
@@ -2103,6 +2157,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
   if (a.S < min_s) return;  // uniform per block
+  __shared__ cx<T> ind[N];
+  if (a.bulk_tab) init_indicator<T, N>(ind);
   init_twiddles<T, N>(tw);
   __syncthreads();
   const int p = threadIdx.x % PX, t = threadIdx.x / PX;
@@ -2189,6 +2245,19 @@ __global__ void __launch_bounds__((PX * (N / EX)))
           if constexpr (CH > 2) cfma<T>(out[2][m], v[m], g.z);
           if constexpr (CH > 3) cfma<T>(out[3][m], v[m], g.w);
         }
+      }
+    }
+    if (a.bulk_tab) {  // as in k_xback
+      const cx<T> dyz = cmul<T>(ind[pc.ky], ind[pc.kz]);
+      const Buf bt = make_buf(a.bulk_tab, table_m<T, N>(0) * a.Sp * sizeof(T));
+#pragma unroll
+      for (int m = 0; m < EX; ++m) {
+        const v4<T> g = bt.template ld<v4<T>>((uint32_t)(mm[m] * a.Sp + i0) * (uint32_t)sizeof(T));
+        const cx<T> chi = cmul<T>(dyz, ind[t + TX * m]);
+        cfma<T>(out[0][m], chi, -g.x);
+        if constexpr (CH > 1) cfma<T>(out[1][m], chi, -g.y);
+        if constexpr (CH > 2) cfma<T>(out[2][m], chi, -g.z);
+        if constexpr (CH > 3) cfma<T>(out[3][m], chi, -g.w);
       }
     }
 #pragma unroll

@@ -91,11 +91,12 @@ struct EvalArgs {
                       // double (FP32, up to four species); cleared by the first pass
   double* phi_part;   // per-workgroup sums of Phi_hs from the derivative pass, or null
   // aperiodic mode: the first pass reads an ext_n^3 domain [S][ext_n]^3 and
-  // treats it as zero-extended onto the n^3 grid (domain at the corner); with
-  // ext_bulk the domain holds ext_val[s] everywhere instead of rho
+  // treats it as zero-extended onto the n^3 grid (domain at the corner)
   int32_t ext_n;
-  int32_t ext_bulk;
-  double ext_val[kMaxSpecies];
+  // aperiodic mode with EC: [M][Sp] sum_j G^EC_ij rho_b,j per |k|^2 class, or
+  // null; the back pass subtracts it times the transform of the domain's
+  // indicator (the response to the domain's bulk densities)
+  const void* bulk_tab;
 };
 
 // Per-instance arguments of the radial table builder.
@@ -112,6 +113,8 @@ struct TableArgs {
   int32_t Sp;
   void* hs_tab;
   void* pair_tab;
+  void* bulk_tab;                // [M][Sp] or null (EvalArgs)
+  double rho_b[kMaxSpecies];     // bulk densities (bulk_tab only)
 };
 
 }  // namespace pnp

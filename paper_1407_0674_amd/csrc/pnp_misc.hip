@@ -170,12 +170,10 @@ __global__ void k_sum_exp(const double* mu3, double* slot, long sn3, uint32_t* s
 // Aperiodic mode: the domain part of the doubled-grid result.
 //   muA  [nterm][S][(2n)^3]: the evaluation of the extended densities
 //        (nterm = 3: hs, el, sh; 1: the total)
-//   muB  [S][(2n)^3] or null: the EC response to the extended bulk densities,
-//        subtracted from the EC term (from the total when nterm = 1)
 //   out  [nterm][S][n^3]; slot [S][n^3] = exp(-total) or null
 // Status as the final pass: non-finite totals, and exp(-mu) overflow when
 // slot is requested.
-__global__ void k_crop(const double* muA, const double* muB, int nterm, int S, int n, double* out, double* slot,
+__global__ void k_crop(const double* muA, int nterm, int S, int n, double* out, double* slot,
                        uint32_t* status) {
   const long n2 = 2L * n, N2 = n2 * n2 * n2, N = (long)n * n * n, total = (long)S * N;
   uint32_t bad = 0u, badidx = 0xffffffffu;
@@ -188,8 +186,7 @@ __global__ void k_crop(const double* muA, const double* muB, int nterm, int S, i
     const long e2 = (long)s * N2 + (x * n2 + y) * n2 + z;
     double tot = 0.0;
     for (int t = 0; t < nterm; ++t) {
-      double v = muA[(long)t * S * N2 + e2];
-      if (muB && (nterm == 1 || t == 1)) v -= muB[e2];
+      const double v = muA[(long)t * S * N2 + e2];
       out[(long)t * total + e] = v;
       tot += v;
     }
