@@ -1193,15 +1193,17 @@ pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* g, int32_t F, cons
     if (!(radius[i] > 0.0) || !std::isfinite(radius[i]) || radius[i] / g->h > 16.0)
       return fail(ctx, PNP_E_ARG, "field " + std::to_string(i) + ": radius must be in (0, 16 h]");
   std::vector<QuadStencil> st;
-  int H = 0;
+  int H = 0, span = 0;
   for (int i = 0; i < F; ++i) {
     st.push_back(build_quad_stencil(radius[i] / g->h, radius[i], order, (flags & PNP_FLAG_CUBIC) != 0));
     H = std::max(H, st.back().reach);
+    span = std::max(span, st.back().span);
   }
   H = std::max(H, 1);
   const int max_reach = precision == PNP_FP64 ? quad_max_reach<double>() : quad_max_reach<float>();
-  if (H > max_reach)
-    return fail(ctx, PNP_E_UNSUPPORTED_SIZE, "sphere reach " + std::to_string(H) +
+  span = std::max(span, 1);
+  if (span > max_reach)
+    return fail(ctx, PNP_E_UNSUPPORTED_SIZE, "sphere reach " + std::to_string(span) +
                                                  " grid points does not fit the LDS tile (R / h too large)");
   QuadArgs a;
   a.f = f;

@@ -52,7 +52,7 @@ struct QuadArgs {
   const double* f;        // [F][N]
   double* out;            // [F][4][N]
   const int32_t* begin;   // [2F + 1]: field f's pairs are [begin[2f], begin[2f+1]), its singles
-                          // [begin[2f+1], begin[2f+2])
+                          // [begin[2f+1], begin[2f+2]); then the reach of each field [F]
   const void* entries;
   int32_t nx, ny, nz;
   int32_t H;              // stencil reach (max |offset| over all fields and axes); selects
@@ -89,9 +89,16 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   constexpr int TX = quad_tx(H, sizeof(T));
   constexpr int LY = kQuadTY + 2 * H, LZ = kQuadTZ + 2 * H, LX = TX + 2 * H;
   constexpr int PLANE = LY * LZ;
+  const int F = (int)gridDim.y;
   __shared__ T tile[LX * PLANE];
+  __shared__ int32_t at[LX + LY + LZ];
+  static_assert(LX + LY + LZ <= kQuadThreads, "one thread per table entry");
   const int field = blockIdx.y;
-  int t = blockIdx.x;
+  // neighbouring tiles on one XCD (workgroups go round the eight in turn), so
+  // that they find each other's halos in its L2
+  const int per = (int)gridDim.x / 8, rest = (int)gridDim.x % 8;
+  const int xcd = (int)blockIdx.x % 8, nth = (int)blockIdx.x / 8;
+  int t = xcd * per + (xcd < rest ? xcd : rest) + nth;
   const int tz = t % a.tiles_z;
   t /= a.tiles_z;
   const int ty = t % a.tiles_y;
@@ -100,25 +107,36 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   const size_t N = (size_t)a.nx * a.ny * a.nz;
   const double* src = a.f + (size_t)field * N;
 
-  // tile element (i, j, l) holds f at grid point (x0 - H + i, y0 - H + j, z0 - H + l):
-  // its periodic image, or zero outside the grid in the aperiodic mode
+  // Tile element (i, j, l) holds f at grid point (x0 - H + i, y0 - H + j,
+  // z0 - H + l): its periodic image, or zero outside the grid in the aperiodic
+  // mode.  The image is found once per plane, row and column of the tile (three
+  // remainders an element were most of the staging), -1 for none; a field of
+  // smaller reach than the launch's leaves out what its stencil does not touch.
+  const int reach = a.begin[2 * F + 1 + field];
+  if (threadIdx.x < LX + LY + LZ) {
+    const int q = threadIdx.x;
+    const int axis = q < LX ? 0 : q < LX + LY ? 1 : 2;
+    const int i = axis == 0 ? q : axis == 1 ? q - LX : q - LX - LY;
+    const int n = axis == 0 ? a.nx : axis == 1 ? a.ny : a.nz;
+    const int g = (axis == 0 ? x0 : axis == 1 ? y0 : z0) - H + i;
+    const int len = axis == 0 ? LX : axis == 1 ? LY : LZ;
+    const bool used = i >= H - reach && i < len - H + reach;
+    int v = a.aperiodic ? (g >= 0 && g < n ? g : -1) : quad_wrap(g, n);
+    if (!used) v = -1;
+    // grid extents multiply to less than 2^31 points
+    at[q] = v < 0 ? -1 : axis == 0 ? v * a.ny * a.nz : axis == 1 ? v * a.nz : v;
+  }
+  __syncthreads();
+#pragma unroll 8
   for (int e = threadIdx.x; e < LX * PLANE; e += kQuadThreads) {
     const int i = e / PLANE;
     const int rem = e - i * PLANE;
     const int j = rem / LZ;
     const int l = rem - j * LZ;
-    int gx = x0 - H + i, gy = y0 - H + j, gz = z0 - H + l;
-    T v = T(0);
-    if (a.aperiodic) {
-      if (gx >= 0 && gx < a.nx && gy >= 0 && gy < a.ny && gz >= 0 && gz < a.nz)
-        v = (T)src[((size_t)gx * a.ny + gy) * a.nz + gz];
-    } else {
-      gx = quad_wrap(gx, a.nx);
-      gy = quad_wrap(gy, a.ny);
-      gz = quad_wrap(gz, a.nz);
-      v = (T)src[((size_t)gx * a.ny + gy) * a.nz + gz];
-    }
-    tile[e] = v;
+    const int ox = at[i], oy = at[LX + j], oz = at[LX + LY + l];
+    const bool in = (ox | oy | oz) >= 0;
+    const double v = src[(uint32_t)(in ? ox + oy + oz : 0)];
+    tile[e] = in ? (T)v : T(0);
   }
   __syncthreads();
 
@@ -218,6 +236,7 @@ struct QuadStencil {
   std::vector<double> c;  // 4 per record
   std::vector<char> paired;
   int reach = 0;          // max |offset|
+  int span = 0;           // the same over every cell that a node touches, if only by rounding
 };
 
 // Interpolation points along one axis at fraction t of a cell (the node at
@@ -284,7 +303,19 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
     if (hit[cell])
       for (int q = 0; q < 4; ++q) cmax = std::max(cmax, std::fabs(acc[cell * 4 + q]));
   const double tol = 1e-14 * cmax;
+  // A node on a grid plane up to rounding (every rule has some: cos(pi / 2) is
+  // 6e-17) also touches the cell beyond with weights of the rounding's size.
+  // Cells with no weight above the same 1e-14 are left out: at order
+  // 8 and R = 1.5, 3 and 4 h, 106 -> 100, 218 -> 188 and 248 -> 212 offsets.
   QuadStencil s;
+  for (size_t cell = 0; cell < cells; ++cell) {
+    if (!hit[cell]) continue;
+    const int ox = (int)(cell / ((size_t)side * side)), oy = (int)(cell / side % side), oz = (int)(cell % side);
+    s.span = std::max(s.span, std::max(std::abs(ox - Hc), std::max(std::abs(oy - Hc), std::abs(oz - Hc))));
+    double m = 0.0;
+    for (int q = 0; q < 4; ++q) m = std::max(m, std::fabs(acc[cell * 4 + q]));
+    if (!(m > tol)) hit[cell] = 0;
+  }
   std::vector<size_t> singles;
   auto push = [&](size_t cell, const double* c, bool paired) {
     const int ox = (int)(cell / ((size_t)side * side)), oy = (int)(cell / side % side), oz = (int)(cell % side);
@@ -323,13 +354,13 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
   return s;
 }
 
-// The packed upload: begin[2F + 1] (padded to 16 bytes), then per field its
+// The packed upload: begin[2F + 1] and the reaches [F] (padded to 16 bytes), then per field its
 // paired records followed by its single ones.
 template <typename T>
 inline std::vector<unsigned char> pack_quad(const std::vector<QuadStencil>& st, int ly, int lz,
                                             size_t& entries_at) {
   const int F = (int)st.size();
-  size_t head = ((size_t)(2 * F + 1) * sizeof(int32_t) + 15) / 16 * 16;
+  size_t head = ((size_t)(3 * F + 1) * sizeof(int32_t) + 15) / 16 * 16;
   size_t count = 0;
   for (const auto& s : st) count += s.dx.size();
   std::vector<unsigned char> buf(head + count * sizeof(QuadEntry<T>), 0);
@@ -350,6 +381,7 @@ inline std::vector<unsigned char> pack_quad(const std::vector<QuadStencil>& st, 
     }
   }
   begin[2 * F] = (int32_t)e;
+  for (int f = 0; f < F; ++f) begin[2 * F + 1 + f] = st[f].reach;
   entries_at = head;
   return buf;
 }
