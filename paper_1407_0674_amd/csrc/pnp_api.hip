@@ -1212,14 +1212,12 @@ pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* g, int32_t F, cons
   a.ny = g->ny;
   a.nz = g->nz;
   a.H = H;
-  const int ly = kQuadTY + 2 * H, lz = kQuadTZ + 2 * H;  // the kernel's tile pitches
+  const int lz = kQuadTZ + 2 * H;  // the kernel's tile pitch
   a.tiles_y = (g->ny + kQuadTY - 1) / kQuadTY;
   a.tiles_z = (g->nz + kQuadTZ - 1) / kQuadTZ;
   a.aperiodic = (flags & PNP_FLAG_APERIODIC) ? 1 : 0;
-  size_t entries_at = 0;
-  std::vector<unsigned char> buf = precision == PNP_FP64 ? pack_quad<double>(st, ly, lz, entries_at)
-                                                         : pack_quad<float>(st, ly, lz, entries_at);
-  if (buf.size() > ctx->arena_bytes / 2)
+  const QuadPack pack = precision == PNP_FP64 ? pack_quad<double>(st, lz) : pack_quad<float>(st, lz);
+  if (pack.bytes.size() > ctx->arena_bytes / 2)
     return fail(ctx, PNP_E_UNSUPPORTED_SIZE, "stencils too large for one call: pass fewer fields");
   if (hipSetDevice(ctx->device) != hipSuccess) return device_check(ctx, "set device");
   hipStream_t s = (hipStream_t)stream;
@@ -1229,10 +1227,11 @@ pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* g, int32_t F, cons
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) return device_check(ctx, "capture query");
   if (capture != hipStreamCaptureStatusNone)
     return fail(ctx, PNP_E_ARG, "pnp_sphere_quadrature cannot be recorded into a graph");
-  const char* dev = (const char*)upload(ctx, buf.data(), buf.size(), s);
+  const char* dev = (const char*)upload(ctx, pack.bytes.data(), pack.bytes.size(), s);
   if (!dev) return device_check(ctx, "stencil upload");
   a.begin = (const int32_t*)dev;
-  a.entries = dev + entries_at;
+  a.columns = (const QuadColumn*)(dev + pack.columns_at);
+  a.weights = dev + pack.weights_at;
   const hipError_t e = precision == PNP_FP64 ? launch_sphere_quad<double>(a, F, s)
                                              : launch_sphere_quad<float>(a, F, s);
   if (e != hipSuccess) return fail(ctx, PNP_E_DEVICE, std::string("sphere quadrature launch: ") + hipGetErrorString(e));

@@ -18,9 +18,16 @@
 // integer offsets with four weights each (scalar, x, y, z), merged on the
 // host in double.  The kernel is then a 3D stencil: a workgroup stages a
 // tile of f with a halo of the stencil reach in LDS and every thread sums
-// the stencil for a column of TX outputs along x, so each LDS value fetched
-// feeds four FMAs and each stencil record (read through the scalar cache,
-// uniform across the workgroup) feeds 4 TX of them.
+// the stencil for TX outputs along x.
+//
+// It is bound by the vector ALU (three fields at 192^3 move 850 MB, 130 us at
+// 6.6 TB/s).  The rule's symmetry in y and z lets a thread fold the four mirror
+// columns of a (|dy|, |dz|) into three sums once per tile plane, and all the
+// offsets along x of those columns share them: 4 multiply-adds and a share of
+// the folding per four offsets, against 12 operations and four LDS reads when
+// each offset was paired with its antipode alone.  192^3, order 8, mixed,
+// R = 1.4, 2.6 and 3.9 h: 82, 140 and 192 us with pairs, 73, 92 and 134 with
+// columns (FP64 88, 179 and 289; 81, 132 and 218).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -31,29 +38,32 @@ namespace pnp {
 
 constexpr int kQuadTY = 8;       // outputs per workgroup along y
 constexpr int kQuadTZ = 32;      // outputs per workgroup along z (the fastest axis)
-constexpr int kQuadThreads = kQuadTY * kQuadTZ;
+constexpr int kQuadCols = kQuadTY * kQuadTZ;  // output columns per workgroup
 constexpr int kQuadMaxFields = 64;
-constexpr size_t kQuadFastLds = 65536;   // tiles up to this size keep several workgroups per CU
 constexpr size_t kQuadMaxLds = 163840;   // the most LDS one workgroup can hold on gfx950
 
-// One record of the merged stencil: an integer offset (its position in the
-// LDS tile relative to the output point) and the weights of the scalar and
-// the three vector integrals there.  A paired record also names the mirror
-// offset, whose weights are the same for the scalar and opposite for the
-// vector integrals.
-template <typename T>
-struct QuadEntry {
-  int32_t lds;
-  int32_t lds_mirror;  // paired records only
-  T c[4];
+// A column of the merged stencil: the offsets (dx, +-dy, +-dz) of one (|dy|, |dz|)
+// over all dx.  The rule is even in y and in z (theta and 2 pi - theta, phi and
+// pi - phi are nodes together), so the four mirror images share their weights up
+// to sign: with a, b, c, d the values at (+dy, +dz), (+dy, -dz), (-dy, +dz),
+// (-dy, -dz), the scalar and x weights multiply ss = a + b + c + d, the y weight
+// ds = a + b - c - d and the z weight sd = a - b + c - d.
+struct QuadColumn {
+  int32_t near_lds, far_lds;  // tile positions of (dy, dz) and (dy, -dz) relative to the output's
+  int32_t dx;                 // bit k: any weight at dx = +-k
+  int32_t w;                  // first weight, in units of four: dx = 0, then +1, -1, +2, -2, ...
 };
+
+// Kinds of columns: bit 0 dy = 0 (two images, ds = 0), bit 1 dz = 0 (sd = 0).
+constexpr int kQuadKinds = 4;
 
 struct QuadArgs {
   const double* f;        // [F][N]
   double* out;            // [F][4][N]
-  const int32_t* begin;   // [2F + 1]: field f's pairs are [begin[2f], begin[2f+1]), its singles
-                          // [begin[2f+1], begin[2f+2]); then the reach of each field [F]
-  const void* entries;
+  const int32_t* begin;   // [4F + 1]: field f's columns of kind k are [begin[4f+k], begin[4f+k+1]);
+                          // then the reach of each field [F]
+  const QuadColumn* columns;
+  const void* weights;    // four T each: scalar, x, y, z
   int32_t nx, ny, nz;
   int32_t H;              // stencil reach (max |offset| over all fields and axes); selects
                           // the kernel, whose tile extents follow from it
@@ -66,33 +76,102 @@ __device__ __forceinline__ int quad_wrap(int i, int n) {
   return r < 0 ? r + n : r;
 }
 
-// Outputs per thread along x for a stencil reach H: the largest of 8, 4, 2, 1
-// whose tile fits 64 KB (at least two workgroups per compute unit); for
-// spheres too wide for that, the largest whose tile fits the 160 KB a
-// workgroup can hold; 0 if none does.
+// Tile height along x for a stencil reach H: 8 or 4 outputs if two workgroups
+// then share a compute unit's 160 KB, else the most that fits one workgroup
+// (fewer than four outputs a column share its folding too thinly: FP64 reach 5,
+// order 8, two groups of two outputs 415 us, one group of eight 282); 0 if
+// nothing fits.
 constexpr size_t quad_tile_bytes(int tx, int H, size_t elem) {
   return (size_t)(tx + 2 * H) * (kQuadTY + 2 * H) * (kQuadTZ + 2 * H) * elem;
 }
+constexpr size_t quad_table_bytes(int tx, int H) { return (size_t)(tx + kQuadTY + kQuadTZ + 6 * H) * sizeof(int32_t); }
 constexpr int quad_tx(int H, size_t elem) {
+  for (int tx = 8; tx >= 4; tx /= 2)
+    if (quad_tile_bytes(tx, H, elem) + quad_table_bytes(tx, H) <= kQuadMaxLds / 2) return tx;
   for (int tx = 8; tx >= 1; tx /= 2)
-    if (quad_tile_bytes(tx, H, elem) <= kQuadFastLds) return tx;
-  for (int tx = 8; tx >= 1; tx /= 2)
-    if (quad_tile_bytes(tx, H, elem) <= kQuadMaxLds) return tx;
+    if (quad_tile_bytes(tx, H, elem) + quad_table_bytes(tx, H) <= kQuadMaxLds) return tx;
   return 0;
+}
+// A tile that has the compute unit to itself is taken by two threads per
+// column of outputs, so that two wavefronts a SIMD cover each other's LDS reads
+// (FP32 reach 9: 1206 us with one, 831 with two, 1376 with four).
+constexpr int quad_split(int H, size_t elem) {
+  const int tx = quad_tx(H, elem);
+  if (quad_tile_bytes(tx, H, elem) + quad_table_bytes(tx, H) <= kQuadMaxLds / 2) return 1;
+  return tx < 2 ? 1 : 2;
+}
+
+// Sum the columns [c0, c1) of one kind into a thread's TX outputs.  A column's
+// values are read and folded once per tile plane, at most TX + 2H of them, and
+// serve all its dx: level k reads the two planes that dx = +-k adds.
+template <typename T, int H, int TX, int KIND>
+__device__ __forceinline__ void quad_columns(const QuadColumn* columns, int c0, int c1, const T* weights, const T* col,
+                                             T (&acc)[TX][4]) {
+  constexpr int PLANE = (kQuadTY + 2 * H) * (kQuadTZ + 2 * H);
+  constexpr bool Y = !(KIND & 1), Z = !(KIND & 2);
+#pragma unroll 1
+  for (int e = c0; e < c1; ++e) {
+    const QuadColumn q = columns[e];
+    const T* w = weights + 4 * (size_t)q.w;
+    T ss[TX + 2 * H], ds[TX + 2 * H], sd[TX + 2 * H];
+    auto read = [&](int i) {  // plane i - H relative to the first output's
+      const T* p = col + (i - H) * PLANE;
+      if constexpr (Y && Z) {
+        const T va = p[q.near_lds], vb = p[q.far_lds], vc = p[-q.far_lds], vd = p[-q.near_lds];
+        const T ab = va + vb, cd = vc + vd;
+        ss[i] = ab + cd;
+        ds[i] = ab - cd;
+        sd[i] = (va - vb) + (vc - vd);
+      } else if constexpr (Y) {
+        const T va = p[q.near_lds], vd = p[-q.near_lds];
+        ss[i] = va + vd;
+        ds[i] = va - vd;
+      } else if constexpr (Z) {
+        const T va = p[q.near_lds], vd = p[-q.near_lds];
+        ss[i] = va + vd;
+        sd[i] = va - vd;
+      } else {
+        ss[i] = p[0];
+      }
+    };
+    auto add = [&](int dx, const T* c) {
+#pragma unroll
+      for (int x = 0; x < TX; ++x) {
+        acc[x][0] += c[0] * ss[x + H + dx];
+        acc[x][1] += c[1] * ss[x + H + dx];
+        if constexpr (Y) acc[x][2] += c[2] * ds[x + H + dx];
+        if constexpr (Z) acc[x][3] += c[3] * sd[x + H + dx];
+      }
+    };
+#pragma unroll
+    for (int i = H; i < H + TX; ++i) read(i);
+    if (q.dx & 1) add(0, w);
+#pragma unroll
+    for (int k = 1; k <= H; ++k) {
+      if ((q.dx >> k) == 0) break;
+      read(H - k);
+      read(H + TX - 1 + k);
+      if (q.dx >> k & 1) {
+        add(k, w + 4 * (2 * k - 1));
+        add(-k, w + 4 * (2 * k));
+      }
+    }
+  }
 }
 
 // H (the stencil reach) is a template parameter so that the tile pitches are
 // constants: the TX reads of one stencil offset then share one address and
 // differ by immediate offsets.
 template <typename T, int H>
-__global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
-  constexpr int TX = quad_tx(H, sizeof(T));
-  constexpr int LY = kQuadTY + 2 * H, LZ = kQuadTZ + 2 * H, LX = TX + 2 * H;
+__global__ __launch_bounds__((kQuadCols * quad_split(H, sizeof(T)))) void k_sphere_quad(QuadArgs a) {
+  constexpr int HX = quad_tx(H, sizeof(T)), TX = HX / quad_split(H, sizeof(T));  // outputs per tile, per thread
+  constexpr int LY = kQuadTY + 2 * H, LZ = kQuadTZ + 2 * H, LX = HX + 2 * H;
+  constexpr int kThreads = kQuadCols * quad_split(H, sizeof(T));
   constexpr int PLANE = LY * LZ;
   const int F = (int)gridDim.y;
   __shared__ T tile[LX * PLANE];
   __shared__ int32_t at[LX + LY + LZ];
-  static_assert(LX + LY + LZ <= kQuadThreads, "one thread per table entry");
+  static_assert(LX + LY + LZ <= kThreads, "one thread per table entry");
   const int field = blockIdx.y;
   // neighbouring tiles on one XCD (workgroups go round the eight in turn), so
   // that they find each other's halos in its L2
@@ -103,7 +182,7 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   t /= a.tiles_z;
   const int ty = t % a.tiles_y;
   const int tx = t / a.tiles_y;
-  const int x0 = tx * TX, y0 = ty * kQuadTY, z0 = tz * kQuadTZ;
+  const int x0 = tx * HX, y0 = ty * kQuadTY, z0 = tz * kQuadTZ;
   const size_t N = (size_t)a.nx * a.ny * a.nz;
   const double* src = a.f + (size_t)field * N;
 
@@ -112,7 +191,7 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   // mode.  The image is found once per plane, row and column of the tile (three
   // remainders an element were most of the staging), -1 for none; a field of
   // smaller reach than the launch's leaves out what its stencil does not touch.
-  const int reach = a.begin[2 * F + 1 + field];
+  const int reach = a.begin[kQuadKinds * F + 1 + field];
   if (threadIdx.x < LX + LY + LZ) {
     const int q = threadIdx.x;
     const int axis = q < LX ? 0 : q < LX + LY ? 1 : 2;
@@ -128,7 +207,7 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   }
   __syncthreads();
 #pragma unroll 8
-  for (int e = threadIdx.x; e < LX * PLANE; e += kQuadThreads) {
+  for (int e = threadIdx.x; e < LX * PLANE; e += kThreads) {
     const int i = e / PLANE;
     const int rem = e - i * PLANE;
     const int j = rem / LZ;
@@ -140,52 +219,28 @@ __global__ __launch_bounds__(kQuadThreads) void k_sphere_quad(QuadArgs a) {
   }
   __syncthreads();
 
-  const int yl = threadIdx.x / kQuadTZ, zl = threadIdx.x % kQuadTZ;
-  const T* col = tile + (H * LY + (H + yl)) * LZ + (H + zl);
+  const int yl = threadIdx.x / kQuadTZ % kQuadTY, zl = threadIdx.x % kQuadTZ;
+  const int xl = threadIdx.x / kQuadCols * TX;  // the thread's first output along x
+  const T* col = tile + ((H + xl) * LY + (H + yl)) * LZ + (H + zl);
   T acc[TX][4];
 #pragma unroll
   for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[x][c] = T(0);
 
-  const QuadEntry<T>* E = reinterpret_cast<const QuadEntry<T>*>(a.entries);
-  const int e0 = a.begin[2 * field], e1 = a.begin[2 * field + 1], e2 = a.begin[2 * field + 2];
-  // mirror pairs d, -d: the scalar weight multiplies the sum of the two
-  // values and the vector weights their difference
-#pragma unroll 4
-  for (int e = e0; e < e1; ++e) {
-    const T c0 = E[e].c[0], c1 = E[e].c[1], c2 = E[e].c[2], c3 = E[e].c[3];
-    const T* p = col + E[e].lds;
-    const T* m = col + E[e].lds_mirror;
-#pragma unroll
-    for (int x = 0; x < TX; ++x) {
-      const T vp = p[x * PLANE], vm = m[x * PLANE];
-      const T sum = vp + vm, dif = vp - vm;
-      acc[x][0] += c0 * sum;
-      acc[x][1] += c1 * dif;
-      acc[x][2] += c2 * dif;
-      acc[x][3] += c3 * dif;
-    }
-  }
-  for (int e = e1; e < e2; ++e) {
-    const T c0 = E[e].c[0], c1 = E[e].c[1], c2 = E[e].c[2], c3 = E[e].c[3];
-    const T* p = col + E[e].lds;
-#pragma unroll
-    for (int x = 0; x < TX; ++x) {
-      const T v = p[x * PLANE];
-      acc[x][0] += c0 * v;
-      acc[x][1] += c1 * v;
-      acc[x][2] += c2 * v;
-      acc[x][3] += c3 * v;
-    }
-  }
+  const int32_t* begin = a.begin + kQuadKinds * field;
+  const T* w = static_cast<const T*>(a.weights);
+  quad_columns<T, H, TX, 0>(a.columns, begin[0], begin[1], w, col, acc);
+  quad_columns<T, H, TX, 1>(a.columns, begin[1], begin[2], w, col, acc);
+  quad_columns<T, H, TX, 2>(a.columns, begin[2], begin[3], w, col, acc);
+  quad_columns<T, H, TX, 3>(a.columns, begin[3], begin[4], w, col, acc);
 
   const int gy = y0 + yl, gz = z0 + zl;
   if (gy >= a.ny || gz >= a.nz) return;
   double* dst = a.out + (size_t)field * 4 * N;
 #pragma unroll
   for (int x = 0; x < TX; ++x) {
-    const int gx = x0 + x;
+    const int gx = x0 + xl + x;
     if (gx < a.nx) {
       const size_t idx = ((size_t)gx * a.ny + gy) * a.nz + gz;
 #pragma unroll
@@ -231,10 +286,12 @@ inline void gauss_legendre(int k, std::vector<double>& x, std::vector<double>& w
 }
 
 struct QuadStencil {
-  // pairs: offset (dx, dy, dz) and its mirror; singles: offset alone
-  std::vector<int32_t> dx, dy, dz;
-  std::vector<double> c;  // 4 per record
-  std::vector<char> paired;
+  struct Column {
+    int dy, dz;             // >= 0
+    std::vector<double> c;  // [2 hx + 1][4], the order of QuadColumn::w
+    uint32_t dx = 0;
+  };
+  std::vector<Column> columns[kQuadKinds];
   int reach = 0;          // max |offset|
   int span = 0;           // the same over every cell that a node touches, if only by rounding
 };
@@ -292,11 +349,6 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
           }
     }
   }
-  // A rule with even k holds every node together with its antipode, so the
-  // merged weights are even in the offset for the scalar integral and odd for
-  // the vector ones (in exact arithmetic; the node coordinates differ in the
-  // last bits).  Offsets whose mirror agrees to 1e-14 of the largest weight
-  // become one record with the mean weights; the rest stay single.
   const size_t cells = (size_t)side * side * side;
   double cmax = 0.0;
   for (size_t cell = 0; cell < cells; ++cell)
@@ -312,87 +364,91 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
     if (!hit[cell]) continue;
     const int ox = (int)(cell / ((size_t)side * side)), oy = (int)(cell / side % side), oz = (int)(cell % side);
     s.span = std::max(s.span, std::max(std::abs(ox - Hc), std::max(std::abs(oy - Hc), std::abs(oz - Hc))));
-    double m = 0.0;
-    for (int q = 0; q < 4; ++q) m = std::max(m, std::fabs(acc[cell * 4 + q]));
-    if (!(m > tol)) hit[cell] = 0;
   }
-  std::vector<size_t> singles;
-  auto push = [&](size_t cell, const double* c, bool paired) {
-    const int ox = (int)(cell / ((size_t)side * side)), oy = (int)(cell / side % side), oz = (int)(cell % side);
-    s.dx.push_back(ox - Hc);
-    s.dy.push_back(oy - Hc);
-    s.dz.push_back(oz - Hc);
-    for (int q = 0; q < 4; ++q) s.c.push_back(c[q]);
-    s.paired.push_back(paired ? 1 : 0);
-    const int m = std::max(std::abs(ox - Hc), std::max(std::abs(oy - Hc), std::abs(oz - Hc)));
-    s.reach = std::max(s.reach, m);
-  };
-  for (size_t cell = 0; cell < cells; ++cell) {
-    if (!hit[cell]) continue;
-    const size_t mirror = cells - 1 - cell;  // offset -d
-    if (mirror == cell || !hit[mirror]) {
-      singles.push_back(cell);
-      continue;
+  // The merged weights are even in y and z (odd for that axis' vector weight)
+  // in exact arithmetic; the node coordinates differ in the last bits, and the
+  // mean over the images is taken.
+  for (int dy = 0; dy <= Hc; ++dy)
+    for (int dz = 0; dz <= Hc; ++dz) {
+      QuadStencil::Column col;
+      col.dy = dy;
+      col.dz = dz;
+      col.c.assign((size_t)(2 * Hc + 1) * 4, 0.0);
+      int hx = -1;
+      for (int dx = -Hc; dx <= Hc; ++dx) {
+        double m[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int iy = 0; iy < 2; ++iy)
+          for (int iz = 0; iz < 2; ++iz) {
+            const int oy = Hc + (iy ? -dy : dy), oz = Hc + (iz ? -dz : dz);
+            const double* v = &acc[(((size_t)(dx + Hc) * side + oy) * side + oz) * 4];
+            m[0] += 0.25 * v[0];
+            m[1] += 0.25 * v[1];
+            m[2] += (iy ? -0.25 : 0.25) * v[2];
+            m[3] += (iz ? -0.25 : 0.25) * v[3];
+          }
+        double big = 0.0;
+        for (int q = 0; q < 4; ++q) big = std::max(big, std::fabs(m[q]));
+        if (!(big > tol)) continue;
+        const int k = std::abs(dx);
+        double* c = &col.c[(dx == 0 ? 0 : dx > 0 ? 2 * k - 1 : 2 * k) * 4];
+        for (int q = 0; q < 4; ++q) c[q] = m[q];
+        col.dx |= 1u << k;
+        hx = std::max(hx, k);
+      }
+      if (hx < 0) continue;
+      col.c.resize((size_t)(2 * hx + 1) * 4);
+      s.reach = std::max(s.reach, std::max(hx, std::max(dy, dz)));
+      s.columns[(dy == 0 ? 1 : 0) + (dz == 0 ? 2 : 0)].push_back(std::move(col));
     }
-    if (mirror < cell) continue;  // handled with its partner
-    const double* a = &acc[cell * 4];
-    const double* b = &acc[mirror * 4];
-    bool even = std::fabs(a[0] - b[0]) <= tol;
-    for (int q = 1; q < 4; ++q) even = even && std::fabs(a[q] + b[q]) <= tol;
-    if (!even) {
-      singles.push_back(cell);
-      singles.push_back(mirror);
-      continue;
-    }
-    const double mean[4] = {0.5 * (a[0] + b[0]), 0.5 * (a[1] - b[1]), 0.5 * (a[2] - b[2]), 0.5 * (a[3] - b[3])};
-    push(cell, mean, true);
-    const int m = std::max(std::abs((int)(mirror / ((size_t)side * side)) - Hc),
-                           std::max(std::abs((int)(mirror / side % side) - Hc), std::abs((int)(mirror % side) - Hc)));
-    s.reach = std::max(s.reach, m);
-  }
-  for (size_t cell : singles) push(cell, &acc[cell * 4], false);
   return s;
 }
 
-// The packed upload: begin[2F + 1] and the reaches [F] (padded to 16 bytes), then per field its
-// paired records followed by its single ones.
+// The packed upload, each part padded to 16 bytes: begin[4F + 1] and the
+// reaches [F], the columns of each field by kind, the weights.
+struct QuadPack {
+  std::vector<unsigned char> bytes;
+  size_t columns_at, weights_at;
+};
+
 template <typename T>
-inline std::vector<unsigned char> pack_quad(const std::vector<QuadStencil>& st, int ly, int lz,
-                                            size_t& entries_at) {
+inline QuadPack pack_quad(const std::vector<QuadStencil>& st, int lz) {
   const int F = (int)st.size();
-  size_t head = ((size_t)(3 * F + 1) * sizeof(int32_t) + 15) / 16 * 16;
-  size_t count = 0;
-  for (const auto& s : st) count += s.dx.size();
-  std::vector<unsigned char> buf(head + count * sizeof(QuadEntry<T>), 0);
-  int32_t* begin = reinterpret_cast<int32_t*>(buf.data());
-  QuadEntry<T>* E = reinterpret_cast<QuadEntry<T>*>(buf.data() + head);
-  size_t e = 0;
+  size_t columns = 0, weights = 0;
+  for (const auto& s : st)
+    for (const auto& kind : s.columns)
+      for (const auto& q : kind) {
+        ++columns;
+        weights += q.c.size();
+      }
+  QuadPack p;
+  p.columns_at = ((size_t)(kQuadKinds * F + 1 + F) * sizeof(int32_t) + 15) / 16 * 16;
+  p.weights_at = p.columns_at + columns * sizeof(QuadColumn);
+  p.bytes.assign(p.weights_at + weights * sizeof(T), 0);
+  int32_t* begin = reinterpret_cast<int32_t*>(p.bytes.data());
+  QuadColumn* C = reinterpret_cast<QuadColumn*>(p.bytes.data() + p.columns_at);
+  T* W = reinterpret_cast<T*>(p.bytes.data() + p.weights_at);
+  int32_t e = 0, w = 0;
   for (int f = 0; f < F; ++f) {
-    const QuadStencil& q = st[f];
-    for (int pass = 0; pass < 2; ++pass) {
-      begin[2 * f + pass] = (int32_t)e;
-      for (size_t r = 0; r < q.dx.size(); ++r) {
-        if ((q.paired[r] != 0) != (pass == 0)) continue;
-        E[e].lds = (q.dx[r] * ly + q.dy[r]) * lz + q.dz[r];
-        E[e].lds_mirror = pass == 0 ? -E[e].lds : 0;
-        for (int c = 0; c < 4; ++c) E[e].c[c] = (T)q.c[r * 4 + c];
-        ++e;
+    for (int k = 0; k < kQuadKinds; ++k) {
+      begin[kQuadKinds * f + k] = e;
+      for (const auto& q : st[f].columns[k]) {
+        C[e++] = {q.dy * lz + q.dz, q.dy * lz - q.dz, (int32_t)q.dx, w / 4};
+        for (double v : q.c) W[w++] = (T)v;
       }
     }
+    begin[kQuadKinds * F + 1 + f] = st[f].reach;
   }
-  begin[2 * F] = (int32_t)e;
-  for (int f = 0; f < F; ++f) begin[2 * F + 1 + f] = st[f].reach;
-  entries_at = head;
-  return buf;
+  begin[kQuadKinds * F] = e;
+  return p;
 }
 
 template <typename T, int H>
 inline void launch_sphere_quad_h(const QuadArgs& a, int F, hipStream_t s) {
-  constexpr int TX = quad_tx(H, sizeof(T));
-  static_assert(TX > 0, "tile does not fit the LDS budget");
-  const int tiles_x = (a.nx + TX - 1) / TX;
+  constexpr int HX = quad_tx(H, sizeof(T));
+  static_assert(HX > 0, "tile does not fit the LDS budget");
+  const int tiles_x = (a.nx + HX - 1) / HX;
   const dim3 grid((unsigned)(tiles_x * a.tiles_y * a.tiles_z), (unsigned)F);
-  hipLaunchKernelGGL((k_sphere_quad<T, H>), grid, dim3(kQuadThreads), 0, s, a);
+  hipLaunchKernelGGL((k_sphere_quad<T, H>), grid, dim3(kQuadCols * quad_split(H, sizeof(T))), 0, s, a);
 }
 
 // The largest reach each precision's tile takes.
