@@ -1,0 +1,149 @@
+"""The kernel variants that a rule on sizes, species counts or request counts
+selects, at the edges of each rule, against the oracle (FP64 1e-10, mixed 1e-5
+infinity-norm relative per species, the bars of the paths' other tests; sphere
+quadrature 1e-12 and 1e-5 of the largest scalar integral)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import pnp_inputs as P
+from conftest import relerr, to_dev
+from oracle.aperiodic import mu_ex_aperiodic
+from oracle.sphere_quad import shell_integrals
+from paper_1407_0674_amd import FLAG_APERIODIC, FP64, MIXED, Evaluator
+
+pytestmark = pytest.mark.gpu
+
+TOL = {FP64: 1e-10, MIXED: 1e-5}
+PACKING = -4
+
+
+def _close(mu, slot, ref, tol):
+    mu = mu.cpu().numpy()
+    for i in range(mu.shape[0]):
+        assert relerr(mu[i], ref["total"][i]) < tol, (i, relerr(mu[i], ref["total"][i]))
+    stol = tol * max(1.0, float(np.max(np.abs(ref["total"]))))
+    assert float(np.max(np.abs(slot.cpu().numpy() / ref["slotboom"] - 1.0))) < stol
+
+
+# the x passes pick their form by species count and, in mixed precision, by
+# size: streamed up to four species, accumulators beyond; the z and y passes
+# split the fields over workgroups on small grids only
+@pytest.mark.parametrize("n,S", [(8, 1), (8, 8), (24, 5), (32, 4), (64, 1), (64, 8), (96, 2), (96, 5), (128, 1), (128, 4),
+                                 (128, 5)])
+def test_species_counts(ev, n, S):
+    prob, rho = P.many_species(n, S, 4100 + 10 * n + S)
+    print(f"oracle n={n} S={S}", flush=True)
+    ref = oracle.mu_ex(prob, rho, "fft")
+    rd = to_dev(rho)
+    for precision in (FP64, MIXED):
+        mu, slot = ev.mu_ex(prob.with_(precision=precision), rd)
+        _close(mu, slot, ref, TOL[precision])
+
+
+# four species at 256^3 mixed have an x pass of their own shape; the FP64 route
+# of the same grid, held to the oracle elsewhere, is the reference
+@pytest.mark.parametrize("S", [4, 5])
+def test_species_counts_256(ev, S):
+    n = 256
+    gen = torch.Generator(device="cuda").manual_seed(4200 + S)
+    prob, _ = P.many_species(8, S, 4200 + S)
+    prob = prob.with_(n=n)
+    rho = torch.rand((S, n, n, n), generator=gen, device="cuda", dtype=torch.float64)
+    for i, s in enumerate(prob.species):
+        rho[i] = s.rho_bulk * (0.9 + 0.2 * rho[i])
+    ref, _ = ev.mu_ex(prob.with_(precision=FP64), rho)
+    ref = ref.clone()
+    mu, _ = ev.mu_ex(prob.with_(precision=MIXED), rho)
+    for i in range(S):
+        assert float((mu[i] - ref[i]).abs().max() / ref[i].abs().max()) < TOL[MIXED], i
+    del rho, ref, mu
+    torch.cuda.empty_cache()
+
+
+# the derivative pass with a wavefront per field (up to 96^3) and the one that
+# walks the fields, in both functionals and with the free energy
+@pytest.mark.parametrize("n", [8, 24, 48, 64, 96, 128])
+def test_derivative_pass_forms(ev, n):
+    for terms in (P.TERMS_ALL, P.TERM_HS_WB | P.TERM_EC | P.TERM_SW):
+        prob, rho = P.channel_problem(n, 4300 + n, terms=terms)
+        print(f"oracle n={n} terms={terms}", flush=True)
+        ref = oracle.mu_ex(prob, rho, "fft")
+        rd = to_dev(rho)
+        for precision in (FP64, MIXED):
+            mu, slot = ev.mu_ex(prob.with_(precision=precision), rd)
+            _close(mu, slot, ref, TOL[precision])
+        if n <= 48:
+            F, _ = ev.free_energy(prob, rd)
+            want = oracle.free_energy(prob, rho, "fft")
+            for name in ("hs", "el", "sh"):
+                assert abs(F[name] - want[name]) <= 1e-10 * abs(want[name]), name
+
+
+# aperiodic mode: tiles of rows that end at, before and after the domain's
+# edge, both forms of the back pass, the bulk response with one and with padded
+# species rows, per term and summed, wide and narrow tiles, both schedules
+@pytest.mark.parametrize("n,S,precision", [(4, 1, FP64), (8, 5, MIXED), (12, 4, FP64), (16, 2, MIXED), (24, 5, FP64),
+                                           (32, 3, MIXED), (48, 1, MIXED), (48, 2, FP64), (64, 4, MIXED)])
+def test_aperiodic_forms(ev, n, S, precision):
+    prob, rho = P.many_species(n, S, 4400 + 10 * n + S, precision=precision)
+    print(f"oracle domain {n} S={S}", flush=True)
+    ref = mu_ex_aperiodic(prob, rho, "fft")
+    rd = to_dev(rho)
+    other = Evaluator(0)
+    other.tune_import(f"{precision} {2 * n} s {sum(1 << p for p in range(1, 10))}\n")
+    try:
+        for e in (ev, other):
+            mu, slot = e.mu_ex(prob, rd, flags=FLAG_APERIODIC)
+            _close(mu, slot, ref, TOL[precision])
+            mu3, _ = e.mu_ex(prob, rd, per_term=True, flags=FLAG_APERIODIC)
+            mu3 = mu3.cpu().numpy()
+            for k, name in enumerate(("hs", "el", "sh")):
+                for i in range(S):
+                    assert relerr(mu3[k, i], ref[name][i]) < TOL[precision], (name, i)
+    finally:
+        other.close()
+
+
+# argument records go as kernel parameters up to three launches' worth and by a
+# copy beyond; statuses are read back in blocks
+@pytest.mark.parametrize("count", [1, 2, 3, 9, 10, 65, 130])
+def test_batch_request_counts(ev, count):
+    inst = [P.many_species(8, 1 + k % 3, 4500 + k) for k in range(count)]
+    rhos = [to_dev(r) for _, r in inst]
+    # the last of several is dense; it alone fails if its weighted density n3
+    # reaches one (all but one of these counts)
+    bad = -1
+    if count > 1:
+        p, r = inst[-1]
+        r = r * (1.5 / P.local_packing_max(r, p.species))
+        rhos[-1] = to_dev(r)
+        if float(np.max(oracle.weighted_densities(p, r, "fft")["n3"])) >= 1.0:
+            bad = count - 1
+    mus, slots, st = ev.batch([p for p, _ in inst], rhos)
+    for k, ((p, _), rd) in enumerate(zip(inst, rhos)):
+        if k == bad:
+            assert st[k] == PACKING
+            continue
+        assert st[k] == 0, k
+        mu, slot = ev.mu_ex(p, rd)
+        assert torch.equal(mus[k], mu) and torch.equal(slots[k], slot), k
+
+
+# every stencil reach of the sphere quadrature (the tile height and the threads
+# per column follow from it), rules without mirror nodes in x, ragged tiles
+@pytest.mark.parametrize("precision,reach", [(MIXED, H) for H in range(1, 12)] + [(FP64, H) for H in range(1, 9)])
+def test_sphere_quadrature_reach(ev, precision, reach):
+    h, shape, k = 0.05, (19, 11, 37), 7 if reach % 2 else 6
+    f = 1.0 + np.random.default_rng(4600 + reach).random((2,) + shape)
+    radii = [(reach - 0.45) * h, max(0.3, reach - 2.7) * h]  # the second stages less than the tile
+    for flags in (0, FLAG_APERIODIC):
+        got = ev.sphere_quadrature(to_dev(f), radii, h, k, precision=precision, flags=flags).cpu().numpy()
+        for i, R in enumerate(radii):
+            I, Iv = shell_integrals(f[i], R, h, k, aperiodic=flags != 0)
+            scale = float(np.max(np.abs(I)))
+            tol = 1e-12 if precision == FP64 else 1e-5
+            assert np.max(np.abs(got[i, 0] - I)) / scale < tol, i
+            for a in range(3):
+                assert np.max(np.abs(got[i, 1 + a] - Iv[a])) / scale < tol, (i, a)
