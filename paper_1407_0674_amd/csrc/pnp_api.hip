@@ -544,8 +544,9 @@ uint32_t default_sched(int precision, int n) {
   return 0u;
 }
 
-inline SpeciesMix mix_of(int S) {
+inline SpeciesMix mix_of(int S, bool bulk = false) {
   SpeciesMix m;
+  m.bulk = bulk;
   m.add(S);
   return m;
 }
@@ -785,7 +786,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   if (d.sw) os.at(0)->tables(dta + 1, 1, L.M, S, s);
   pt.end();
   Split sq(ctx, s, d.n);
-  const SpeciesMix sm = mix_of(S);
+  const SpeciesMix sm = mix_of(S, bulk != nullptr);
   const int mp = sq.main_part();
   pt.begin(1); os.at(1)->zfwd(dea, 1, S, s); pt.end();
   sq.fork();
@@ -943,7 +944,7 @@ static pnp_status enqueue_aperiodic(pnp_ctx ctx, const Derived& d, const pnp_gri
     const EvalArgs* dea = nullptr;
     upload_args(ctx, &ta, 1, &ea, 1, s, dta, dea);
     if (!dta || !dea) return device_check(ctx, "argument upload");
-    run_sequence(ctx, ops, dea, dta, 1, L.M, hs_mask(d), mix_of(S), s, d.n);
+    run_sequence(ctx, ops, dea, dta, 1, L.M, hs_mask(d), mix_of(S, bulk != nullptr), s, d.n);
   } else {
     const pnp_status st = enqueue_per_term(ctx, d, g, sp, rho, p, L, w, muA, nullptr, nullptr, s, bulk);
     if (st != PNP_OK) return st;

@@ -108,10 +108,15 @@ template <typename T, int N, int V = 0> struct Geo {
   static constexpr int EX0 = default_ex<T, N>();
   static constexpr int EX = SEC ? alt_ept(N, EX0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EX0;
   static constexpr int TX = N / EX;
-  // the x passes that hold accumulators in registers (k_xfwd_acc and the
-  // chunked back pass), which leave less room
+  // the forward x pass that holds accumulators in registers (k_xfwd_acc),
+  // which leave less room
   static constexpr int EXG0 = R3 ? 6 : (sizeof(T) == 4 ? 8 : 4);
   static constexpr int EXG = SEC ? alt_ept(N, EXG0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EXG0;
+  // the chunked back pass, more accumulators still, whichever schedule: five
+  // species, us a pass with 8 | 4 elements per thread: FP32 64^3 42 | 32, 128^3
+  // 124 | 103; FP64 (4 | 8) 64^3 31 | 38, 128^3 157 | 178; with 6 | 12: FP32 48^3
+  // 34 | 55, 96^3 58 | 73, FP64 48^3 41 | 71, 96^3 118 | 109, 192^3 753 | 676.
+  static constexpr int EXC = R3 ? (sizeof(T) == 8 && N >= 96 ? 12 : 6) : 4;
   // whether the forward pass is the streamed kernel (see k_xfwd_acc)
   static constexpr bool kXStream = sizeof(T) == 4 && N >= 128;
   // the streamed x passes: the largest species count on EX elements per
@@ -1942,7 +1947,9 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 // into the results.
 // lo: instances with fewer than lo or more than CH species belong to another
 // kernel of the same launch list and are skipped here.
-template <typename T, int N, int CH, int EX, int PX>
+// BULK: the instances have bulk tables (aperiodic mode with EC; a test of
+// a.bulk_tab alone took 128^3 of the chunked kernel from 102 to 132 us).
+template <typename T, int N, int CH, int EX, int PX, bool BULK = false>
 __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <= 3 ? 4 : 2)
     k_xback(const EvalArgs* __restrict__ args, int lo, int part) {
   static_assert(CH >= 1 && CH <= 4, "output chunk");
@@ -1986,8 +1993,8 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
     if constexpr (kDc && kFree) dcv[own0 ? q : kBackFields + CH] = x;
     else if (own0) dcv[q] = x;
   };
-  __shared__ cx<T> ind[N];
-  if (a.bulk_tab) init_indicator<T, N>(ind);
+  __shared__ cx<T> ind[BULK ? N : 1];
+  if (BULK && a.bulk_tab) init_indicator<T, N>(ind);
   // the first pencil of the stream is in flight while the tables are made
   if (hs_on) {
 #pragma unroll
@@ -2091,7 +2098,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
       }
     }
   }
-  if (a.bulk_tab) {  // uniform
+  if (BULK && a.bulk_tab) {  // uniform
     const int sy = sgn_idx(pc.ky, N), m0 = sy * sy + pc.kz * pc.kz;
     const cx<T> dyz = cmul<T>(ind[pc.ky], ind[pc.kz]);
     const Buf bt = make_buf(a.bulk_tab, table_m<T, N>(0) * a.Sp * sizeof(T));
@@ -2121,7 +2128,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
 #pragma unroll 1
         for (int j = 0; j < S; ++j)
           d += (double)pt.template ld<T>((uint32_t)(j * a.Sp + c) * (uint32_t)sizeof(T)) * (double)dcv[kBackFields + j];
-      if (a.bulk_tab)
+      if (BULK && a.bulk_tab)
         d -= (double)make_buf(a.bulk_tab, a.Sp * sizeof(T)).template ld<T>((uint32_t)c * (uint32_t)sizeof(T)) *
              ((double)(N / 2) * (N / 2) * (N / 2));
       g[c] = d * a.inv_n3;
@@ -2147,7 +2154,7 @@ __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <=
 // density pencils).
 // min_s: instances with fewer species run the streamed kernel of the same
 // launch list and are skipped here.
-template <typename T, int N, int CH, int EX, int PX>
+template <typename T, int N, int CH, int EX, int PX, bool BULK = false>
 __global__ void __launch_bounds__((PX * (N / EX)))
     k_xback_chunked(const EvalArgs* __restrict__ args, int min_s, int part) {
   static_assert(CH >= 1 && CH <= 4, "output chunk");
@@ -2157,8 +2164,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
   if (a.S < min_s) return;  // uniform per block
-  __shared__ cx<T> ind[N];
-  if (a.bulk_tab) init_indicator<T, N>(ind);
+  __shared__ cx<T> ind[BULK ? N : 1];
+  if (BULK && a.bulk_tab) init_indicator<T, N>(ind);
   init_twiddles<T, N>(tw);
   __syncthreads();
   const int p = threadIdx.x % PX, t = threadIdx.x / PX;
@@ -2247,7 +2254,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
         }
       }
     }
-    if (a.bulk_tab) {  // as in k_xback
+    if (BULK && a.bulk_tab) {  // as in k_xback
       const cx<T> dyz = cmul<T>(ind[pc.ky], ind[pc.kz]);
       const Buf bt = make_buf(a.bulk_tab, table_m<T, N>(0) * a.Sp * sizeof(T));
 #pragma unroll

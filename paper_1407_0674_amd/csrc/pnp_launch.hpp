@@ -13,6 +13,7 @@ namespace pnp {
 
 // The species counts of a launch list (they select the x-pass kernels).
 struct SpeciesMix {
+  bool bulk = false;  // the instances have bulk tables (EvalArgs::bulk_tab)
   uint32_t mask = 0;  // bit S set: some instance has S species
   void add(int S) { mask |= 1u << S; }
   bool has(int S) const { return (mask >> S) & 1u; }

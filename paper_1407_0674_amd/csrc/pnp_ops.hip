@@ -52,7 +52,7 @@ template <typename T, int N, int V = 0> struct Launch {
   static int tiles_y(int part) { return part == kPartAll ? G::tiles_y : part == kPartMain ? (N * G::H) / G::PY : N / G::PY; }
   static int tiles_x(int part) { return part == kPartAll ? G::tiles_x : part == kPartMain ? (N * G::H) / G::PX : N / G::PX; }
   // the general x passes keep the same pencils per workgroup
-  static constexpr int TXG = N / G::EXG;
+  static constexpr int TXG = N / G::EXG, TXC = N / G::EXC;
   static constexpr bool four = G::kXMax < 4;
   static constexpr int EX4 = G::EX > 8 ? 8 : G::EX > 4 ? 4 : G::EX;  // of four species where kXMax is three
   // maxf: the most fields of an instance (kVecItems in the vector mode)
@@ -113,19 +113,23 @@ template <typename T, int N, int V = 0> struct Launch {
       }
     }
   }
-  static void xback(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
+  template <bool BULK> static void xback_of(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
     const dim3 g(count * tiles_x(part)), b(G::PX * G::TX);
     switch (sm.upto(G::kXMax)) {
-      case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
-      case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
-      case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
-      case 4: if constexpr (!four) hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX>), g, b, 0, s, a, 1, part); break;
+      case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
+      case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
+      case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
+      case 4: if constexpr (!four) hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
       default: break;
     }
     if constexpr (four)
-      if (sm.has(4)) hipLaunchKernelGGL((k_xback<T, N, 4, EX4, G::PX>), g, dim3(G::PX * (N / EX4)), 0, s, a, 4, part);
+      if (sm.has(4)) hipLaunchKernelGGL((k_xback<T, N, 4, EX4, G::PX, BULK>), g, dim3(G::PX * (N / EX4)), 0, s, a, 4, part);
     if (sm.maxS() > 4)
-      hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EXG, G::PX>), g, dim3(G::PX * TXG), 0, s, a, 5, part);
+      hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EXC, G::PX, BULK>), g, dim3(G::PX * TXC), 0, s, a, 5, part);
+  }
+  static void xback(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
+    if (sm.bulk) xback_of<true>(a, count, sm, part, s);
+    else xback_of<false>(a, count, sm, part, s);
   }
   // maxf: the most fields of an instance
   static void zinv(const EvalArgs* a, int count, int sel, int maxf, hipStream_t s) {
