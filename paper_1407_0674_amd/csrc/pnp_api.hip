@@ -171,8 +171,9 @@ struct Derived {
 // 2 White Bear, 0 no hard-sphere term
 inline int hs_mask(const Derived& d) { return d.hs ? (d.wb ? 2 : 1) : 0; }
 
-// The status region: four words, the k = 0 parts of the results at 64 bytes.
-constexpr size_t kDcOffset = 64, kStatusBytes = kDcOffset + kMaxSpecies * sizeof(double);
+// The status region: four words, the k = 0 parts of the results at 64 bytes
+// (of up to three results: the terms of a per-term call).
+constexpr size_t kDcOffset = 64, kStatusBytes = kDcOffset + 3 * kMaxSpecies * sizeof(double);
 
 struct Layout {
   size_t status, energy, hs, pair, pair2, A, B, C, total;
@@ -776,14 +777,26 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   for (int i = 0; i < S; ++i) ea[3].cfin[i] = 0.0;
   if (!d.ec) for (int i = 0; i < S; ++i) ea[2].cfin[i] = 0.0;
   if (!d.hs) ea[1].hs_on = 0;
+  // Up to four species, each term's spectra get an array of their own, and the
+  // inverse y and z passes of the three run as one launch each: hs in the
+  // derivative spectra and sh in the density spectra they came from (a back-pass
+  // workgroup has read its pencils when it writes them; more species take two
+  // rounds of reads), el in specC.  sh follows el, which reads the same densities.
+  // Mixed, three species: 64^3 157 -> 134 us a call, 96^3 274 -> 230, 192^3 1208 ->
+  // 1155; at 256^3, where a term at a time leaves more in the cache, 2391 -> 2432.
+  const bool joint = d.hs && S <= 4 && d.n <= 192;
+  if (joint) {
+    ea[1].specC = ea[1].specB;
+    ea[3].specC = ea[3].specA;
+    for (int k = 2; k < 4; ++k) ea[k].dc += (k - 1) * kMaxSpecies;
+  }
   const TableArgs* dta = nullptr;
   const EvalArgs* dea = nullptr;
   upload_args(ctx, ta, sizeof(ta) / sizeof(TableArgs), ea, sizeof(ea) / sizeof(EvalArgs), s, dta, dea);
   if (!dta || !dea) return device_check(ctx, "argument upload");
   PassTimer pt{ctx, s};
   pt.begin(0);
-  os.at(0)->tables(dta, 1, L.M, S, s);
-  if (d.sw) os.at(0)->tables(dta + 1, 1, L.M, S, s);
+  os.at(0)->tables(dta, d.sw ? 2 : 1, L.M, S, s);  // both write the same hs table
   pt.end();
   Split sq(ctx, s, d.n);
   const SpeciesMix sm = mix_of(S, bulk != nullptr);
@@ -803,7 +816,21 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
     pt.begin(6); os.at(6)->ystep(dea, 1, 1, kVecMode, S, true, mp, s); pt.end();
     if (sq.on) os.at(6)->ystep(dea, 1, 1, kVecMode, S, true, kPartNyquist, sq.nyq());
   }
-  for (int k = 1; k < 4; ++k) {
+  if (joint) {
+    pt.begin(7);
+    os.at(7)->xback(dea + 1, 2, sm, mp, s);
+    os.at(7)->xback(dea + 3, 1, sm, mp, s);
+    pt.end();
+    if (sq.on) {
+      os.at(7)->xback(dea + 1, 2, sm, kPartNyquist, sq.nyq());
+      os.at(7)->xback(dea + 3, 1, sm, kPartNyquist, sq.nyq());
+    }
+    pt.begin(8); os.at(8)->ystep(dea + 1, 3, 2, -1, S, false, mp, s); pt.end();
+    if (sq.on) os.at(8)->ystep(dea + 1, 3, 2, -1, S, false, kPartNyquist, sq.nyq());
+    sq.join();
+    pt.begin(9); os.at(9)->zinv(dea + 1, 3, 2, S, s); pt.end();
+  }
+  for (int k = 1; k < 4 && !joint; ++k) {
     pt.begin(7); os.at(7)->xback(dea + k, 1, sm, mp, s); pt.end();
     if (sq.on) os.at(7)->xback(dea + k, 1, sm, kPartNyquist, sq.nyq());
     pt.begin(8); os.at(8)->ystep(dea + k, 1, 2, -1, S, false, mp, s); pt.end();

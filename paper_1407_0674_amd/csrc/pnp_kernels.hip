@@ -627,7 +627,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     st[1] = 0xffffffffu;
     st[2] = st[3] = 0u;
 #pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) gbl(a.dc)[s] = 0.0;
+    for (int s = 0; s < 3 * kMaxSpecies; ++s) gbl(a.dc)[s] = 0.0;
   }
   if (rows_outside<N, RZ>(a, tile)) return;  // uniform per block
   __syncthreads();

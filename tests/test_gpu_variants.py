@@ -147,3 +147,26 @@ def test_sphere_quadrature_reach(ev, precision, reach):
             assert np.max(np.abs(got[i, 0] - I)) / scale < tol, i
             for a in range(3):
                 assert np.max(np.abs(got[i, 1 + a] - Iv[a])) / scale < tol, (i, a)
+
+
+# per-term calls: one launch for the three terms' inverse passes (up to four
+# species and 192^3) and a term at a time, without a hard-sphere term too
+@pytest.mark.parametrize("n,S,terms", [(8, 4, P.TERMS_ALL), (24, 2, P.TERM_HS | P.TERM_EC), (32, 4, P.TERMS_ALL),
+                                       (32, 5, P.TERMS_ALL), (48, 3, P.TERM_EC | P.TERM_SW), (64, 1, P.TERMS_ALL),
+                                       (192, 2, P.TERMS_ALL)])
+def test_per_term_forms(ev, n, S, terms):
+    prob, rho = P.many_species(n, S, 4700 + 10 * n + S, terms=terms)
+    print(f"oracle n={n} S={S}", flush=True)
+    ref = oracle.mu_ex(prob, rho, "fft")
+    rd = to_dev(rho)
+    for precision in (FP64, MIXED):
+        mu3, slot = ev.mu_ex(prob.with_(precision=precision), rd, per_term=True)
+        _close(mu3.sum(dim=0), slot, ref, TOL[precision])
+        mu3 = mu3.cpu().numpy()
+        for k, name in enumerate(("hs", "el", "sh")):
+            for i in range(S):
+                want = ref[name][i]
+                err = float(np.max(np.abs(mu3[k, i] - want)))
+                assert err <= TOL[precision] * float(np.max(np.abs(want))), (name, i, err)
+    del rd, mu3, slot
+    torch.cuda.empty_cache()
