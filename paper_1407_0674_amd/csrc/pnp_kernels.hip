@@ -358,16 +358,13 @@ __device__ __forceinline__ double ec_kernel(const TableArgs& a, int p, double y,
 
 // hs table [m][S][2] = (j0(kR), 4 pi R^3 j1(kR)/(kR)) (FP64 path only); pair
 // table [m][j][i] (row length Sp) = G_ij, the combined pair kernel, zero for
-// i >= S; bulk table [m][i] (row length Sp, made with the hs species).  One thread per (m, table entry): blockIdx.y
-// picks the entry (pair-table entries first, then the hs species), blockIdx.z
-// the instance.  G is symmetric, so the thread of entry (j, i) with i <= j
-// writes both (j, i) and (i, j), and those with i > j have nothing to do.
+// i >= S; bulk table [m][i] (row length Sp, made with the hs species).  One
+// thread per (m, item): pair-table entries first, then the hs species.  G is
+// symmetric, so the thread of entry (j, i) with i <= j writes both (j, i) and
+// (i, j), and those with i > j have nothing to do.
 template <typename T>
-__global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ targs) {
-  const TableArgs& a = targs[blockIdx.z];
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void table_entry(const TableArgs& a, int item, int m) {
   if (m >= a.M) return;
-  const int item = blockIdx.y;
   const int npair = a.S * a.Sp;
   const double k = a.kscale * sqrt((double)m);
   if (item < npair) {
@@ -418,6 +415,12 @@ __global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ ta
     const Buf hs = make_buf(a.hs_tab, (uint64_t)a.M * a.S * sizeof(cx<T>));
     hs.template st<cx<T>>(mk<T>((T)j0, (T)(4.0 * kPi * R * R * R * j1x)), (uint32_t)((m * a.S + i) * sizeof(cx<T>)));
   }
+}
+
+// blockIdx.y the item, blockIdx.z the instance
+template <typename T>
+__global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ targs) {
+  table_entry<T>(targs[blockIdx.z], blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -609,10 +612,23 @@ __device__ __forceinline__ bool rows_outside(const EvalArgs& a, int tile) {
 
 // P1: z r2c of the S input densities (float64) into specA (each gridDim.y-th
 // species per workgroup)
-template <typename T, int N, int V = 0>
+// TAB: workgroups past the first `nz` of a row build the radial tables of tcount
+// instances (items of `chunks` workgroups each), which this pass does not read:
+// beside it they cost next to nothing, as a launch of their own 4 to 7 us a call.
+// Grids that fill the chip build them beside the y pass instead.
+template <typename T, int N, int V = 0, bool TAB = false>
 __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
-    k_zfwd(const EvalArgs* __restrict__ args) {
+    k_zfwd(const EvalArgs* __restrict__ args, const TableArgs* __restrict__ targs, int nz, int tcount, int items,
+           int chunks) {
   using G = Geo<T, N, V>;
+  if constexpr (TAB) {
+    if ((int)blockIdx.x >= nz) {  // uniform per block
+      const int id = ((int)blockIdx.x - nz) * gridDim.y + blockIdx.y, item = id / chunks;
+      if (item < tcount * items)
+        table_entry<T>(targs[item / items], item % items, (id % chunks) * blockDim.x + threadIdx.x);
+      return;
+    }
+  }
   constexpr int H = G::H, TZ = G::TZ, EZ = G::EZ, RZ = G::RZ;
   __shared__ cx<T> twH[H];
   __shared__ cx<T> twN[N];

@@ -40,13 +40,25 @@ template <typename T, int N, int V = 0> struct Launch {
     return std::max(1, std::min(fields, 2048 / std::max(1, waves)));
   }
   // maxS: the largest species count among the launch's instances
+  static int table_items(int maxS) { return maxS * ((maxS + 3) / 4 * 4) + maxS; }  // pair-table entries + hs species
   static void tables(const TableArgs* a, int count, int M, int maxS, hipStream_t s) {
-    const int items = maxS * ((maxS + 3) / 4 * 4) + maxS;  // pair-table entries + hs species
-    hipLaunchKernelGGL(k_tables<T>, dim3((M + 255) / 256, items, count), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_tables<T>, dim3((M + 255) / 256, table_items(maxS), count), dim3(256), 0, s, a);
   }
   static void zfwd(const EvalArgs* a, int count, int maxS, hipStream_t s) {
     const int b = G::RZ * G::TZ, g = count * G::tiles_z;
-    hipLaunchKernelGGL((k_zfwd<T, N, V>), dim3(g, split(g, b, maxS)), dim3(b), 0, s, a);
+    hipLaunchKernelGGL((k_zfwd<T, N, V>), dim3(g, split(g, b, maxS)), dim3(b), 0, s, a, nullptr, g, 0, 0, 1);
+  }
+  // the first pass and the tables of tcount instances (M: their most classes)
+  static void zfwd_tables(const EvalArgs* a, int count, const TableArgs* ta, int tcount, int M, int maxS, hipStream_t s) {
+    if constexpr (N < 192) {
+      const int b = G::RZ * G::TZ, g = count * G::tiles_z, y = split(g, b, maxS);
+      const int items = table_items(maxS), chunks = (M + b - 1) / b;
+      const int extra = (int)(((long)tcount * items * chunks + y - 1) / y);
+      hipLaunchKernelGGL((k_zfwd<T, N, V, true>), dim3(g + extra, y), dim3(b), 0, s, a, ta, g, tcount, items, chunks);
+    } else {
+      tables(ta, tcount, M, maxS, s);
+      zfwd(a, count, maxS, s);
+    }
   }
   // part: kPartAll, kPartMain (main-array tiles) or kPartNyquist (Nyquist-plane tiles)
   static int tiles_y(int part) { return part == kPartAll ? G::tiles_y : part == kPartMain ? (N * G::H) / G::PY : N / G::PY; }
@@ -156,7 +168,7 @@ template <typename T, int N, int V = 0> struct Launch {
       (G0::EZ != G2::EZ ? (1u << 1) | (1u << 9) : 0u) |
       (G0::EY != G2::EY ? (1u << 2) | (1u << 4) | (1u << 6) | (1u << 8) : 0u) |
       (G0::EX != G2::EX ? (1u << 3) | (1u << 7) : 0u) | ((kFieldWaves ? ezf_of<T, N, 0>() != ezf_of<T, N, 2>() : ezd_of<T, N, 0>() != ezd_of<T, N, 2>()) ? 1u << 5 : 0u);
-  static constexpr Ops ops{tables, zfwd, ystep, xfwd, zderiv, xback, kFieldWaves ? GeoF<T, N, EZF>::tiles : GD::tiles, zinv, xplain, xport, sched_alt};
+  static constexpr Ops ops{tables, zfwd, zfwd_tables, ystep, xfwd, zderiv, xback, kFieldWaves ? GeoF<T, N, EZF>::tiles : GD::tiles, zinv, xplain, xport, sched_alt};
 };
 
 template <typename T, int N, int V> const Ops* ops_inst() { return &Launch<T, N, V>::ops; }
