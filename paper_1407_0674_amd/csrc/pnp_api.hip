@@ -799,7 +799,9 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   // Mixed, three species: 64^3 157 -> 134 us a call, 96^3 274 -> 230, 192^3 1208 ->
   // 1155; at 256^3, where a term at a time leaves more in the cache, 2391 -> 2432.
   const bool joint = d.hs && S <= 4 && d.n <= 192;
+  const bool fused = joint && !d.aperiodic;
   if (joint) {
+    if (fused) ea[1].slot = slot;
     ea[1].specC = ea[1].specB;
     ea[3].specC = ea[3].specA;
     for (int k = 2; k < 4; ++k) ea[k].dc += (k - 1) * kMaxSpecies;
@@ -839,7 +841,10 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
     pt.begin(8); os.at(8)->ystep(dea + 1, 3, 2, -1, S, false, mp, s); pt.end();
     if (sq.on) os.at(8)->ystep(dea + 1, 3, 2, -1, S, false, kPartNyquist, sq.nyq());
     sq.join();
-    pt.begin(9); os.at(9)->zinv(dea + 1, 3, 2, S, s); pt.end();
+    pt.begin(9);
+    if (fused) os.at(9)->zinv_terms(dea + 1, S, s);
+    else os.at(9)->zinv(dea + 1, 3, 2, S, s);
+    pt.end();
   }
   for (int k = 1; k < 4 && !joint; ++k) {
     pt.begin(7); os.at(7)->xback(dea + k, 1, sm, mp, s); pt.end();
@@ -850,6 +855,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
     pt.begin(9); os.at(9)->zinv(dea + k, 1, 2, S, s); pt.end();
     if (k < 3) sq.fork();  // the next term's Nyquist tiles rewrite what this z pass read
   }
+  if (fused) return device_check(ctx, "launch");
   if (d.aperiodic) return device_check(ctx, "launch");  // only the domain part is written: the crop checks it
   const long sn3 = (long)S * n3;
   const int blocks = (int)std::min<long>((sn3 + 255) / 256, 4096);

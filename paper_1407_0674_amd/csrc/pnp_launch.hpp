@@ -37,6 +37,7 @@ struct Ops {
   void (*xback)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);  // count, species, part
   int zderiv_tiles;  // workgroups of the derivative pass per instance
   void (*zinv)(const EvalArgs*, int, int, int, hipStream_t);  // count, sel, most fields
+  void (*zinv_terms)(const EvalArgs*, int, hipStream_t);  // species
   void (*xplain)(const EvalArgs*, int, int, bool, hipStream_t);
   void (*xport)(const EvalArgs*, int, double*, int, hipStream_t);
   uint32_t sched_alt;  // passes (bit p: pass p) whose secondary FFT schedule differs from the primary

@@ -148,6 +148,11 @@ template <typename T, int N, int V = 0> struct Launch {
     const int b = G::RZ * G::TZ, g = count * G::tiles_z;
     hipLaunchKernelGGL((k_zinv<T, N, V>), dim3(g, split(g, b, maxf)), dim3(b), 0, s, a, sel);
   }
+  // the three terms of a per-term call
+  static void zinv_terms(const EvalArgs* a, int S, hipStream_t s) {
+    const int b = G::RZ * G::TZ;
+    hipLaunchKernelGGL((k_zinv<T, N, V, true>), dim3(G::tiles_z, split(G::tiles_z, b, S)), dim3(b), 0, s, a, 2);
+  }
   static void xplain(const EvalArgs* a, int count, int nf, bool fwd, hipStream_t s) {
     if (fwd)
       hipLaunchKernelGGL((k_xplain<T, N, true, G::EX, G::PX>), dim3(count * G::tiles_x), dim3(G::PX * G::TX), 0, s,
@@ -168,7 +173,7 @@ template <typename T, int N, int V = 0> struct Launch {
       (G0::EZ != G2::EZ ? (1u << 1) | (1u << 9) : 0u) |
       (G0::EY != G2::EY ? (1u << 2) | (1u << 4) | (1u << 6) | (1u << 8) : 0u) |
       (G0::EX != G2::EX ? (1u << 3) | (1u << 7) : 0u) | ((kFieldWaves ? ezf_of<T, N, 0>() != ezf_of<T, N, 2>() : ezd_of<T, N, 0>() != ezd_of<T, N, 2>()) ? 1u << 5 : 0u);
-  static constexpr Ops ops{tables, zfwd, zfwd_tables, ystep, xfwd, zderiv, xback, kFieldWaves ? GeoF<T, N, EZF>::tiles : GD::tiles, zinv, xplain, xport, sched_alt};
+  static constexpr Ops ops{tables, zfwd, zfwd_tables, ystep, xfwd, zderiv, xback, kFieldWaves ? GeoF<T, N, EZF>::tiles : GD::tiles, zinv, zinv_terms, xplain, xport, sched_alt};
 };
 
 template <typename T, int N, int V> const Ops* ops_inst() { return &Launch<T, N, V>::ops; }
