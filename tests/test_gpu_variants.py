@@ -11,12 +11,12 @@ import pnp_inputs as P
 from conftest import relerr, to_dev
 from oracle.aperiodic import mu_ex_aperiodic
 from oracle.sphere_quad import shell_integrals
-from paper_1407_0674_amd import FLAG_APERIODIC, FP64, MIXED, Evaluator
+from paper_1407_0674_amd import FLAG_APERIODIC, FP64, MIXED, Evaluator, PnpError
 
 pytestmark = pytest.mark.gpu
 
 TOL = {FP64: 1e-10, MIXED: 1e-5}
-PACKING = -4
+PACKING, NON_FINITE = -4, -6
 
 
 def _close(mu, slot, ref, tol):
@@ -170,3 +170,22 @@ def test_per_term_forms(ev, n, S, terms):
                 assert err <= TOL[precision] * float(np.max(np.abs(want))), (name, i, err)
     del rd, mu3, slot
     torch.cuda.empty_cache()
+
+
+# the total's checks of per-term calls: exp(-total) past the double range is an
+# error only where the factor is asked for, a non-finite total always
+@pytest.mark.parametrize("S", [3, 5])
+def test_per_term_total_checks(ev, S):
+    prob, rho = P.many_species(16, S, 4800 + S)
+    eps, rout = P.uniform_well(prob.species, 240.0, 0.3)  # mu below -2000 k_B T
+    deep = prob.with_(sw_eps=eps, sw_rout=rout)
+    rd = to_dev(rho)
+    with pytest.raises(PnpError) as e:
+        ev.mu_ex(deep, rd, per_term=True)
+    assert e.value.status == -5
+    mu3, _ = ev.mu_ex(deep, rd, per_term=True, slotboom=False)
+    assert torch.isfinite(mu3).all()
+    rho[S - 1, 3, 4, 5] = np.nan
+    with pytest.raises(PnpError) as e:
+        ev.mu_ex(prob, to_dev(rho), per_term=True)
+    assert e.value.status == NON_FINITE
