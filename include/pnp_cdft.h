@@ -411,15 +411,12 @@ void pnp_plan_destroy(pnp_plan plan);
 
 /*
  * Autotuner of FFT schedules and tile shapes.  Each pass of the evaluation
- * has two FFT schedules: the primary one (16 elements per thread for the z
- * and y transforms, 12 on sizes with a factor 3; 8 for the x transforms in
- * mixed precision, 4 in FP64, 6 with a factor 3; 4, 2 or 6 for the
- * derivative pass) and a secondary one with half as many elements per
- * thread, twice the threads per pencil and smaller radices, where such a
- * radix plan exists; for the x transforms of sizes with a factor 3, twice
- * as many (12: fewer, larger radix stages); elsewhere the two are the
- * same.  Every pass also has a
- * default tile shape (workgroups carrying 16 pencils or rows, for
+ * has two FFT schedules: a primary one and a secondary one with half as many
+ * elements per thread, twice the threads per pencil and smaller radices,
+ * where such a radix plan exists, or twice as many and fewer, larger stages
+ * for some x transforms; elsewhere the two are the same.  (The back pass of
+ * more than four species has one schedule.)  Every pass but the derivative
+ * pass also has a default tile shape (workgroups carrying 16 pencils or rows, for
  * full-width HBM bursts on large grids) and, for grids up to 128^3, a
  * narrow one with a quarter of the pencils per workgroup and four times the
  * workgroups (small grids otherwise leave most of the 256 compute units
@@ -438,10 +435,8 @@ void pnp_plan_destroy(pnp_plan plan);
  * that size (single calls, batches of any composition, plans, sessions, the
  * equilibrium solve, free energies, weighted densities), so an instance gets
  * the same arithmetic alone and in any batch.  Before any tuning the
- * schedule is a built-in table of the autotuner's choices measured on an
- * MI355X for each supported size and precision (at 256^3: the secondary
- * schedule for the two z passes; at 192^3 also for the two x passes in
- * mixed precision).  The two schedules order the floating-point
+ * schedule is a built-in table measured on an MI355X for each supported size
+ * and precision.  The two schedules order the floating-point
  * operations differently: results agree to rounding, not bit for bit.  The
  * tile shape is stored under (precision, n, instance-count class of the
  * launch: 1, 2-3, 4-15, >= 16); it does not change the arithmetic.  The

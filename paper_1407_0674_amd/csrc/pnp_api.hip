@@ -512,9 +512,10 @@ uint64_t tune_key(int precision, int n, int cls) { return ((uint64_t)precision <
 uint64_t sched_key(int precision, int n) { return ((uint64_t)precision << 40) | (uint64_t)n; }
 
 // The FFT schedule of (precision, n) before any tuning: the passes (numbered
-// as pnp_profile_read orders them) on which the autotuner, run twice on an
-// MI355X for one three-species instance with every term, chose the
-// secondary schedule both times.
+// as pnp_profile_read orders them) whose secondary schedule was the faster one
+// on an MI355X for one three-species instance with every term: the x passes and
+// the derivative pass timed pass by pass under both, the z and y passes as the
+// autotuner chose them twice in a row.
 constexpr uint32_t passes(std::initializer_list<int> l) {
   uint32_t m = 0;
   for (int p : l) m |= 1u << p;

@@ -1734,7 +1734,7 @@ struct XWeights {
 // Exchange buffers of a streamed x pass: two in turn (one barrier per
 // exchange) up to 96^3, whose launches leave room for them beside the few
 // groups that each compute unit gets and whose time is the latency of the
-// barriers (S = 3 mixed back pass at 64^3: 18.2 us with one buffer, 15.2 us
+// barriers (S = 3 mixed back pass at 64^3: 18.2 us with one buffer, 16.5 us
 // with two); above, one, of real parts only (kXSplit) where two groups per
 // compute unit need that.
 enum : int { kXSplit = 0, kXOne = 1, kXTwo = 2 };

@@ -125,7 +125,7 @@ __global__ void __launch_bounds__(256) k_energy_final(const double* phi_part, in
 // *res starts at 0 (the evaluation's first pass clears it).  Atomics on one
 // word take about 12 ns each, one after the other: a workgroup reduces first,
 // and leaves its atomic out when the word already holds as much (two species
-// at 48^3: 43 us with one atomic per wavefront, 6 us so).
+// at 48^3: 43 us with one atomic per wavefront, 6 to 9 us so).
 __global__ void __launch_bounds__(256) k_picard(double* rho, const double* mu, const double* beta_v, long n3,
                                                 const double* rb_mb, double lambda, unsigned long long* res,
                                                 uint32_t fixed) {
