@@ -1995,7 +1995,7 @@ __global__ void __launch_bounds__((PX * (N / EX)))
 // into the results.
 // lo: instances with fewer than lo or more than CH species belong to another
 // kernel of the same launch list and are skipped here.
-// BULK: the instances have bulk tables (aperiodic mode with EC; a test of
+// BULK: instances may have bulk tables (aperiodic mode with EC; the test of
 // a.bulk_tab alone took 128^3 of the chunked kernel from 102 to 132 us).
 template <typename T, int N, int CH, int EX, int PX, bool BULK = false>
 __global__ void __launch_bounds__((PX * (N / EX)), PX * (N / EX) >= 512 && CH <= 3 ? 4 : 2)

@@ -127,15 +127,20 @@ template <typename T, int N, int V = 0> struct Launch {
   }
   template <bool BULK> static void xback_of(const EvalArgs* a, int count, const SpeciesMix& sm, int part, hipStream_t s) {
     const dim3 g(count * tiles_x(part)), b(G::PX * G::TX);
+    // The streamed FP64 kernels always carry the test for a bulk table: its block
+    // ends the density phase, without it the compiler holds values of that phase
+    // across the last transforms (three species: 188 B of spills at 128^3, 81
+    // against 66 us; 256^3 508 against 462; other counts the same).
+    constexpr bool TEST = BULK || sizeof(T) == 8;
     switch (sm.upto(G::kXMax)) {
-      case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
-      case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
-      case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
-      case 4: if constexpr (!four) hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX, BULK>), g, b, 0, s, a, 1, part); break;
+      case 1: hipLaunchKernelGGL((k_xback<T, N, 1, G::EX, G::PX, TEST>), g, b, 0, s, a, 1, part); break;
+      case 2: hipLaunchKernelGGL((k_xback<T, N, 2, G::EX, G::PX, TEST>), g, b, 0, s, a, 1, part); break;
+      case 3: hipLaunchKernelGGL((k_xback<T, N, 3, G::EX, G::PX, TEST>), g, b, 0, s, a, 1, part); break;
+      case 4: if constexpr (!four) hipLaunchKernelGGL((k_xback<T, N, 4, G::EX, G::PX, TEST>), g, b, 0, s, a, 1, part); break;
       default: break;
     }
     if constexpr (four)
-      if (sm.has(4)) hipLaunchKernelGGL((k_xback<T, N, 4, EX4, G::PX, BULK>), g, dim3(G::PX * (N / EX4)), 0, s, a, 4, part);
+      if (sm.has(4)) hipLaunchKernelGGL((k_xback<T, N, 4, EX4, G::PX, TEST>), g, dim3(G::PX * (N / EX4)), 0, s, a, 4, part);
     if (sm.maxS() > 4)
       hipLaunchKernelGGL((k_xback_chunked<T, N, 4, G::EXC, G::PX, BULK>), g, dim3(G::PX * TXC), 0, s, a, 5, part);
   }
