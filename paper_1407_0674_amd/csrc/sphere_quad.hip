@@ -51,7 +51,7 @@ constexpr size_t kQuadMaxLds = 163840;   // the most LDS one workgroup can hold 
 struct QuadColumn {
   int32_t near_lds, far_lds;  // tile positions of (dy, dz) and (dy, -dz) relative to the output's
   int32_t dx;                 // bit k: any weight at dx = +-k
-  int32_t w;                  // first weight, in units of four: dx = 0, then +1, -1, +2, -2, ...
+  int32_t w;                  // first weight, in units of four: of each bit set, dx = k, then -k
 };
 
 // Kinds of columns: bit 0 dy = 0 (two images, ds = 0), bit 1 dz = 0 (sd = 0).
@@ -145,15 +145,19 @@ __device__ __forceinline__ void quad_columns(const QuadColumn* columns, int c0, 
     };
 #pragma unroll
     for (int i = H; i < H + TX; ++i) read(i);
-    if (q.dx & 1) add(0, w);
+    if (q.dx & 1) {
+      add(0, w);
+      w += 4;
+    }
 #pragma unroll
     for (int k = 1; k <= H; ++k) {
       if ((q.dx >> k) == 0) break;
       read(H - k);
       read(H + TX - 1 + k);
       if (q.dx >> k & 1) {
-        add(k, w + 4 * (2 * k - 1));
-        add(-k, w + 4 * (2 * k));
+        add(k, w);
+        add(-k, w + 4);
+        w += 8;
       }
     }
   }
@@ -288,7 +292,7 @@ inline void gauss_legendre(int k, std::vector<double>& x, std::vector<double>& w
 struct QuadStencil {
   struct Column {
     int dy, dz;             // >= 0
-    std::vector<double> c;  // [2 hx + 1][4], the order of QuadColumn::w
+    std::vector<double> c;  // [..][4], the order of QuadColumn::w
     uint32_t dx = 0;
   };
   std::vector<Column> columns[kQuadKinds];
@@ -373,10 +377,10 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
       QuadStencil::Column col;
       col.dy = dy;
       col.dz = dz;
-      col.c.assign((size_t)(2 * Hc + 1) * 4, 0.0);
       int hx = -1;
-      for (int dx = -Hc; dx <= Hc; ++dx) {
-        double m[4] = {0.0, 0.0, 0.0, 0.0};
+      // the mean weights at dx; false if none is above tol
+      auto weights = [&](int dx, double* m) {
+        for (int q = 0; q < 4; ++q) m[q] = 0.0;
         for (int iy = 0; iy < 2; ++iy)
           for (int iz = 0; iz < 2; ++iz) {
             const int oy = Hc + (iy ? -dy : dy), oz = Hc + (iz ? -dz : dz);
@@ -388,15 +392,19 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
           }
         double big = 0.0;
         for (int q = 0; q < 4; ++q) big = std::max(big, std::fabs(m[q]));
-        if (!(big > tol)) continue;
-        const int k = std::abs(dx);
-        double* c = &col.c[(dx == 0 ? 0 : dx > 0 ? 2 * k - 1 : 2 * k) * 4];
-        for (int q = 0; q < 4; ++q) c[q] = m[q];
+        if (big > tol) return true;
+        for (int q = 0; q < 4; ++q) m[q] = 0.0;
+        return false;
+      };
+      for (int k = 0; k <= Hc; ++k) {
+        double m[8];
+        const bool up = weights(k, m), down = weights(-k, m + 4);
+        if (!up && !down) continue;
+        col.c.insert(col.c.end(), m, m + (k == 0 ? 4 : 8));
         col.dx |= 1u << k;
-        hx = std::max(hx, k);
+        hx = k;
       }
       if (hx < 0) continue;
-      col.c.resize((size_t)(2 * hx + 1) * 4);
       s.reach = std::max(s.reach, std::max(hx, std::max(dy, dz)));
       s.columns[(dy == 0 ? 1 : 0) + (dz == 0 ? 2 : 0)].push_back(std::move(col));
     }
