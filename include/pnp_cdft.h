@@ -43,10 +43,11 @@
  *
  * Memory: every pointer marked "device" is caller-owned device memory (for
  * example allocated by PyTorch) on the context's device; the library never
- * allocates, frees or retains caller memory.  The context owns a 4 MiB
- * device ring for per-call argument records (allocated by pnp_create) and a
- * few host records; when the ring wraps (after thousands of calls) the call
- * that wraps it waits for the device to drain.  A captured plan owns a small
+ * allocates, frees or retains caller memory.  The context owns a device
+ * ring of a little over 4 MiB for per-call argument records, 16 KiB of pinned
+ * host memory for status words (both allocated by pnp_create) and a few host
+ * records; when the ring wraps (after thousands of calls) the call that wraps
+ * it waits for the device to drain.  A captured plan owns a small
  * device block for its argument records (allocated by pnp_plan_create, freed
  * by pnp_plan_destroy).  Scratch space comes in through `workspace`, sized by
  * pnp_workspace_bytes().
@@ -362,6 +363,7 @@ typedef struct {
  * request that fails (bad packing, overflow, ...) reports its own status and
  * does not affect the others.  Returns PNP_OK when the batch ran (check each
  * status).
+ * More than 2048 requests of one size and precision: PNP_E_NOMEM.
  */
 pnp_status pnp_batch_mu_ex(pnp_ctx ctx, int32_t count, pnp_request* reqs, void* stream);
 

@@ -364,6 +364,15 @@ void fill_eval_args(EvalArgs& e, const Derived& d, const pnp_species* sp, const 
   e.nreal = d.S;
 }
 
+// The device ring: the records of 2048 requests of one size and precision in a
+// batch, 2112 bytes each; and the most a call's sphere stencils take of it.
+constexpr size_t kRingBytes = (4u << 20) + (128u << 10), kStencilBytes = 2u << 20;
+
+// whether the argument records of `count` instances fit the ring
+bool records_fit(size_t count) {
+  return up(up(sizeof(TableArgs) * count) + sizeof(EvalArgs) * count) <= kRingBytes;
+}
+
 // Copy host bytes into the context's device ring (stream ordered).  The few
 // KB of a single call go as kernel parameters: a copy from pageable memory
 // costs a staging copy, a blit and its gaps (about 12 us before the first
@@ -874,7 +883,7 @@ pnp_status pnp_create(int device, pnp_ctx* out) {
   if (hipGetDeviceCount(&count) != hipSuccess || device < 0 || device >= count) return PNP_E_DEVICE;
   pnp_ctx c = new pnp_ctx_s();
   c->device = device;
-  c->arena_bytes = 4u << 20;
+  c->arena_bytes = kRingBytes;
   if (hipSetDevice(device) != hipSuccess || hipMalloc((void**)&c->arena, c->arena_bytes) != hipSuccess) {
     delete c;
     return PNP_E_DEVICE;
@@ -1263,7 +1272,7 @@ pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* g, int32_t F, cons
   a.tiles_z = (g->nz + kQuadTZ - 1) / kQuadTZ;
   a.aperiodic = (flags & PNP_FLAG_APERIODIC) ? 1 : 0;
   const QuadPack pack = precision == PNP_FP64 ? pack_quad<double>(st, lz) : pack_quad<float>(st, lz);
-  if (pack.bytes.size() > ctx->arena_bytes / 2)
+  if (pack.bytes.size() > kStencilBytes)
     return fail(ctx, PNP_E_UNSUPPORTED_SIZE, "stencils too large for one call: pass fewer fields");
   if (hipSetDevice(ctx->device) != hipSuccess) return device_check(ctx, "set device");
   hipStream_t s = (hipStream_t)stream;
@@ -1315,6 +1324,8 @@ pnp_status pnp_batch_mu_ex(pnp_ctx ctx, int32_t count, pnp_request* reqs, void* 
   std::vector<Layout> lay;
   std::vector<Group> groups;
   prepare_batch(ctx, count, reqs, lay, groups);
+  for (const Group& g : groups)
+    if (!records_fit(g.ids.size())) return fail(ctx, PNP_E_NOMEM, "too many requests of one size for one batch");
   // Grid sizes below kSplitMinN leave most of the chip idle in their
   // launches: with two or more of them each runs on a branch stream of its
   // own, forked from the caller's stream and joined back before the status
@@ -1531,6 +1542,8 @@ pnp_status pnp_autotune(pnp_ctx ctx, int32_t count, pnp_request* reqs, int32_t r
   std::vector<Layout> lay;
   std::vector<Group> groups;
   prepare_batch(ctx, count, reqs, lay, groups);
+  for (const Group& g : groups)
+    if (!records_fit(g.ids.size())) return fail(ctx, PNP_E_NOMEM, "too many requests of one size for one batch");
   // the pass timers are borrowed: keep the caller's accumulated figures
   const bool prof0 = ctx->prof;
   const uint32_t mask0 = ctx->prof_mask;

@@ -189,3 +189,17 @@ def test_per_term_total_checks(ev, S):
     with pytest.raises(PnpError) as e:
         ev.mu_ex(prob, to_dev(rho), per_term=True)
     assert e.value.status == NON_FINITE
+
+
+# the argument ring holds the records of 2048 requests of one size
+def test_batch_ring_limit(ev):
+    prob, rho = P.many_species(8, 1, 4900)
+    rd = to_dev(rho)
+    mu, slot = ev.mu_ex(prob, rd)
+    mu, slot = mu.clone(), slot.clone()
+    mus, slots, st = ev.batch([prob] * 2048, [rd] * 2048)
+    assert st == [0] * 2048
+    for k in (0, 1, 1023, 2047):
+        assert torch.equal(mus[k], mu) and torch.equal(slots[k], slot), k
+    with pytest.raises(PnpError):
+        ev.batch([prob] * 2049, [rd] * 2049)
