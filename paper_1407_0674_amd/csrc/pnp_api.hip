@@ -1271,6 +1271,7 @@ pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* g, int32_t F, cons
   a.tiles_y = (g->ny + kQuadTY - 1) / kQuadTY;
   a.tiles_z = (g->nz + kQuadTZ - 1) / kQuadTZ;
   a.aperiodic = (flags & PNP_FLAG_APERIODIC) ? 1 : 0;
+  a.even = order % 2 == 0 ? 1 : 0;
   const QuadPack pack = precision == PNP_FP64 ? pack_quad<double>(st, lz) : pack_quad<float>(st, lz);
   if (pack.bytes.size() > kStencilBytes)
     return fail(ctx, PNP_E_UNSUPPORTED_SIZE, "stencils too large for one call: pass fewer fields");
