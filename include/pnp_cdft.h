@@ -417,8 +417,10 @@ void pnp_plan_destroy(pnp_plan plan);
  * elements per thread, twice the threads per pencil and smaller radices,
  * where such a radix plan exists, or twice as many and fewer, larger stages
  * for some x transforms; elsewhere the two are the same.  (The back pass of
- * more than four species has one schedule.)  Every pass but the derivative
- * pass also has a default tile shape (workgroups carrying 16 pencils or rows, for
+ * more than four species has one schedule; in mixed precision so has the
+ * forward x pass of more than four from 128^3 on, and both x passes of four
+ * species at 256^3.)  Every pass but the derivative pass up to 96^3 also has
+ * a default tile shape (workgroups carrying 16 pencils or rows, for
  * full-width HBM bursts on large grids) and, for grids up to 128^3, a
  * narrow one with a quarter of the pencils per workgroup and four times the
  * workgroups (small grids otherwise leave most of the 256 compute units

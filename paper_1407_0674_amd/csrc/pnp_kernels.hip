@@ -108,17 +108,25 @@ template <typename T, int N, int V = 0> struct Geo {
   static constexpr int EX0 = default_ex<T, N>();
   static constexpr int EX = SEC ? alt_ept(N, EX0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EX0;
   static constexpr int TX = N / EX;
-  // the forward x pass that holds accumulators in registers (k_xfwd_acc),
-  // which leave less room
+  // whether the forward pass is the streamed kernel (see k_xfwd_acc)
+  static constexpr bool kXStream = sizeof(T) == 4 && N >= 128;
+  // the forward x pass that holds accumulators in registers (k_xfwd_acc), which
+  // leave less room.  Beside the streamed kernel it takes the species counts that
+  // one does not, whichever schedule (the schedule's choice is the streamed
+  // kernel's); mixed, us a pass: 128^3 five species 42 with 4, 48 with 8; 192^3
+  // five 150 with 6, 145 with 12, eight 199 and 203; 256^3 four 225 with 4, 212
+  // with 8, five 239 and 227, eight 333 and 320.
   static constexpr int EXG0 = R3 ? 6 : (sizeof(T) == 4 ? 8 : 4);
-  static constexpr int EXG = SEC ? alt_ept(N, EXG0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true) : EXG0;
+  static constexpr int EXG = kXStream ? (R3 ? 6 : N >= 256 ? 8 : 4)
+                             : SEC    ? alt_ept(N, EXG0, pow2_divisor_le(N, sizeof(T) == 4 ? 16 : 8), true)
+                                      : EXG0;
   // the chunked back pass, more accumulators still, whichever schedule: five
   // species, us a pass with 8 | 4 elements per thread: FP32 64^3 42 | 32, 128^3
   // 124 | 103; FP64 (4 | 8) 64^3 31 | 38, 128^3 157 | 178; with 6 | 12: FP32 48^3
-  // 34 | 55, 96^3 58 | 73, FP64 48^3 41 | 71, 96^3 118 | 109, 192^3 753 | 676.
-  static constexpr int EXC = R3 ? (sizeof(T) == 8 && N >= 96 ? 12 : 6) : 4;
-  // whether the forward pass is the streamed kernel (see k_xfwd_acc)
-  static constexpr bool kXStream = sizeof(T) == 4 && N >= 128;
+  // 34 | 55, 96^3 58 | 73, 192^3 379 | 388, FP64 48^3 41 | 71, 96^3 118 | 109, 192^3
+  // 753 | 676.  At 256^3 FP32 four a thread are 1024 threads: 704 | 704 with hard
+  // spheres, 510 | 486 without, eight species 1041 | 1028 and 822 | 788.
+  static constexpr int EXC = R3 ? (sizeof(T) == 8 && N >= 96 ? 12 : 6) : (sizeof(T) == 4 && N >= 256 ? 8 : 4);
   // the streamed x passes: the largest species count on EX elements per
   // thread, and the elements per thread of four species where that is three
   static constexpr int kXMax = N >= 256 ? 3 : 4;
@@ -1738,13 +1746,17 @@ struct XWeights {
 // exchange) up to 96^3, whose launches leave room for them beside the few
 // groups that each compute unit gets and whose time is the latency of the
 // barriers (S = 3 mixed back pass at 64^3: 18.2 us with one buffer, 16.5 us
-// with two); above, one, of real parts only (kXSplit) where two groups per
-// compute unit need that.
+// with two), and where two groups would not fit a compute unit with half a
+// buffer either (four species at 256^3: mixed 390 -> 374 us, FP64 739 -> 693);
+// above, one, of real parts only (kXSplit) where two groups per compute unit
+// need that.
 enum : int { kXSplit = 0, kXOne = 1, kXTwo = 2 };
 template <typename T, int N, int PX, int CH>
 constexpr int x_buffers() {
   constexpr size_t w = sizeof(cx<T>) * (size_t)(CH * (N / 2 + 1) * PX + N), x = sizeof(cx<T>) * (size_t)PX * N;
-  return N <= 96 ? kXTwo : w + x > 81920 && w + x / 2 <= 81920 ? kXSplit : kXOne;
+  constexpr size_t half = 81920;  // of a compute unit's LDS
+  if (N <= 96 || (w + x / 2 > half && w + 2 * x <= 2 * half)) return kXTwo;
+  return w + x > half && w + x / 2 <= half ? kXSplit : kXOne;
 }
 template <typename T, int N, int PX, int B> struct XView {
   static constexpr int size = B == kXTwo ? 4 * PX * N : B == kXOne ? 2 * PX * N : PX * N;  // values of T

@@ -66,7 +66,9 @@ template <typename T, int N, int V = 0> struct Launch {
   // the general x passes keep the same pencils per workgroup
   static constexpr int TXG = N / G::EXG, TXC = N / G::EXC;
   static constexpr bool four = G::kXMax < 4;
-  static constexpr int EX4 = G::EX > 8 ? 8 : G::EX > 4 ? 4 : G::EX;  // of four species where kXMax is three
+  // of four species where kXMax is three, whichever schedule (mixed back pass at
+  // 256^3: 390 us with 8, 408 with the 4 that half of the streamed 8 would be)
+  static constexpr int EX4 = sizeof(T) == 4 ? 8 : 4;
   // maxf: the most fields of an instance (kVecItems in the vector mode)
   static void ystep(const EvalArgs* a, int count, int sel, int nf, int maxf, bool fwd, int part, hipStream_t s) {
     const int tiles = count * tiles_y(part);
