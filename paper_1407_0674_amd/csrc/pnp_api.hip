@@ -613,16 +613,16 @@ struct Split {
 // Three species, a call: mixed 32^3 92 -> 87 us, 64^3 115 -> 109, 128^3 275 -> 269;
 // FP64 64^3 131 -> 127.
 void first_pass(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, int count, const TableArgs* ta, int tcount, int M,
-                int maxS, hipStream_t s) {
+                const SpeciesMix& sm, hipStream_t s) {
   PassTimer pt{c, s};
   if (ta && !(c->prof && !c->capturing)) {
-    op.at(1)->zfwd_tables(ea, count, ta, tcount, M, maxS, s);
+    op.at(1)->zfwd_tables(ea, count, ta, tcount, M, sm, s);
     return;
   }
   if (ta) {
-    pt.begin(0); op.at(0)->tables(ta, tcount, M, maxS, s); pt.end();
+    pt.begin(0); op.at(0)->tables(ta, tcount, M, sm, s); pt.end();
   }
-  pt.begin(1); op.at(1)->zfwd(ea, count, maxS, s); pt.end();
+  pt.begin(1); op.at(1)->zfwd(ea, count, sm.maxS(), s); pt.end();
 }
 
 // ea: device arg tables; fmask: the hard-sphere functionals among the
@@ -644,11 +644,11 @@ void run_sequence(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, const TableAr
   // run: 1.657 ms per evaluation beside the y pass, 1.666 ms beside the z
   // pass).
   bool tab_pending = false;
-  first_pass(c, op, ea, count, sp.on || !tables ? nullptr : ta, count, M, sm.maxS(), s);
+  first_pass(c, op, ea, count, sp.on || !tables ? nullptr : ta, count, M, sm, s);
   sp.fork();
   if (sp.on && tables) {
     PassTimer ps{c, sp.nyq()};
-    ps.begin(0); op.at(0)->tables(ta, count, M, sm.maxS(), sp.nyq()); ps.end();
+    ps.begin(0); op.at(0)->tables(ta, count, M, sm, sp.nyq()); ps.end();
     tab_pending = true;
   }
   pt.begin(2); op.at(2)->ystep(ea, count, 0, -1, sm.maxS(), true, mp, s); pt.end();
@@ -824,7 +824,7 @@ static pnp_status enqueue_per_term(pnp_ctx ctx, const Derived& d, const pnp_grid
   Split sq(ctx, s, d.n);
   const SpeciesMix sm = mix_of(S, bulk != nullptr);
   const int mp = sq.main_part();
-  first_pass(ctx, os, dea, 1, dta, d.sw ? 2 : 1, L.M, S, s);  // both write the same hs table
+  first_pass(ctx, os, dea, 1, dta, d.sw ? 2 : 1, L.M, sm, s);  // both write the same hs table
   sq.fork();
   pt.begin(2); os.at(2)->ystep(dea, 1, 0, -1, S, true, mp, s); pt.end();
   if (sq.on) os.at(2)->ystep(dea, 1, 0, -1, S, true, kPartNyquist, sq.nyq());
@@ -1218,7 +1218,7 @@ pnp_status pnp_weighted_densities(pnp_ctx ctx, const pnp_grid* g, int32_t S, con
   const EvalArgs* dea = nullptr;
   upload_args(ctx, &ta, 1, &ea, 1, s, dta, dea);
   if (!dta || !dea) return device_check(ctx, "argument upload");
-  os.at(0)->tables(dta, 1, L.M, S, s);
+  os.at(0)->tables(dta, 1, L.M, mix_of(S), s);
   os.at(1)->zfwd(dea, 1, S, s);
   os.at(2)->ystep(dea, 1, 0, -1, S, true, kPartAll, s);
   os.at(3)->xfwd(dea, 1, mix_of(S), kPartAll, s);

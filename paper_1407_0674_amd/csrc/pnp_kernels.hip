@@ -370,7 +370,10 @@ __device__ __forceinline__ double ec_kernel(const TableArgs& a, int p, double y,
 // thread per (m, item): pair-table entries first, then the hs species.  G is
 // symmetric, so the thread of entry (j, i) with i <= j writes both (j, i) and
 // (i, j), and those with i > j have nothing to do.
-template <typename T>
+// BULK: instances may have bulk tables (without the code for them 32 registers
+// a thread instead of 56: five species without HS at 256^3 mixed 64 -> 58 us; in
+// the first pass's launch, which has its own registers, no difference).
+template <typename T, bool BULK>
 __device__ __forceinline__ void table_entry(const TableArgs& a, int item, int m) {
   if (m >= a.M) return;
   const int npair = a.S * a.Sp;
@@ -401,7 +404,7 @@ __device__ __forceinline__ void table_entry(const TableArgs& a, int item, int m)
     if (i != j) pr.template st<T>((T)v, (uint32_t)(((m * a.S + i) * a.Sp + j) * sizeof(T)));
   } else if (item < npair + a.S) {
     const int i = item - npair;
-    if (a.bulk_tab) {  // a row's padding is not read into a result
+    if (BULK && a.bulk_tab) {  // a row's padding is not read into a result
       double v = 0.0;
       for (int j = 0; j < a.S; ++j) {
         const int p = a.pidx[i][j];
@@ -426,9 +429,9 @@ __device__ __forceinline__ void table_entry(const TableArgs& a, int item, int m)
 }
 
 // blockIdx.y the item, blockIdx.z the instance
-template <typename T>
+template <typename T, bool BULK>
 __global__ void __launch_bounds__(256) k_tables(const TableArgs* __restrict__ targs) {
-  table_entry<T>(targs[blockIdx.z], blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
+  table_entry<T, BULK>(targs[blockIdx.z], blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -633,7 +636,7 @@ __global__ void __launch_bounds__((Geo<T, N, V>::RZ * Geo<T, N, V>::TZ))
     if ((int)blockIdx.x >= nz) {  // uniform per block
       const int id = ((int)blockIdx.x - nz) * gridDim.y + blockIdx.y, item = id / chunks;
       if (item < tcount * items)
-        table_entry<T>(targs[item / items], item % items, (id % chunks) * blockDim.x + threadIdx.x);
+        table_entry<T, true>(targs[item / items], item % items, (id % chunks) * blockDim.x + threadIdx.x);
       return;
     }
   }

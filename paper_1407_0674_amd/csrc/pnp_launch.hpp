@@ -28,9 +28,9 @@ struct SpeciesMix {
 };
 
 struct Ops {
-  void (*tables)(const TableArgs*, int, int, int, hipStream_t);
+  void (*tables)(const TableArgs*, int, int, const SpeciesMix&, hipStream_t);  // count, M, species
   void (*zfwd)(const EvalArgs*, int, int, hipStream_t);  // count, most species
-  void (*zfwd_tables)(const EvalArgs*, int, const TableArgs*, int, int, int, hipStream_t);  // count, tables, their count, M, most species
+  void (*zfwd_tables)(const EvalArgs*, int, const TableArgs*, int, int, const SpeciesMix&, hipStream_t);  // count, tables, their count, M, species
   void (*ystep)(const EvalArgs*, int, int, int, int, bool, int, hipStream_t);  // count, sel, nf, most fields, fwd, part
   void (*xfwd)(const EvalArgs*, int, const SpeciesMix&, int, hipStream_t);   // count, species, part
   void (*zderiv)(const EvalArgs*, int, bool, int, hipStream_t);

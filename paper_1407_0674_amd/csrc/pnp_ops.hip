@@ -41,23 +41,26 @@ template <typename T, int N, int V = 0> struct Launch {
   }
   // maxS: the largest species count among the launch's instances
   static int table_items(int maxS) { return maxS * ((maxS + 3) / 4 * 4) + maxS; }  // pair-table entries + hs species
-  static void tables(const TableArgs* a, int count, int M, int maxS, hipStream_t s) {
-    hipLaunchKernelGGL(k_tables<T>, dim3((M + 255) / 256, table_items(maxS), count), dim3(256), 0, s, a);
+  static void tables(const TableArgs* a, int count, int M, const SpeciesMix& sm, hipStream_t s) {
+    const dim3 g((M + 255) / 256, table_items(sm.maxS()), count);
+    if (sm.bulk) hipLaunchKernelGGL((k_tables<T, true>), g, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_tables<T, false>), g, dim3(256), 0, s, a);
   }
   static void zfwd(const EvalArgs* a, int count, int maxS, hipStream_t s) {
     const int b = G::RZ * G::TZ, g = count * G::tiles_z;
     hipLaunchKernelGGL((k_zfwd<T, N, V>), dim3(g, split(g, b, maxS)), dim3(b), 0, s, a, nullptr, g, 0, 0, 1);
   }
   // the first pass and the tables of tcount instances (M: their most classes)
-  static void zfwd_tables(const EvalArgs* a, int count, const TableArgs* ta, int tcount, int M, int maxS, hipStream_t s) {
+  static void zfwd_tables(const EvalArgs* a, int count, const TableArgs* ta, int tcount, int M, const SpeciesMix& sm,
+                          hipStream_t s) {
     if constexpr (N < 192) {
-      const int b = G::RZ * G::TZ, g = count * G::tiles_z, y = split(g, b, maxS);
-      const int items = table_items(maxS), chunks = (M + b - 1) / b;
+      const int b = G::RZ * G::TZ, g = count * G::tiles_z, y = split(g, b, sm.maxS());
+      const int items = table_items(sm.maxS()), chunks = (M + b - 1) / b;
       const int extra = (int)(((long)tcount * items * chunks + y - 1) / y);
       hipLaunchKernelGGL((k_zfwd<T, N, V, true>), dim3(g + extra, y), dim3(b), 0, s, a, ta, g, tcount, items, chunks);
     } else {
-      tables(ta, tcount, M, maxS, s);
-      zfwd(a, count, maxS, s);
+      tables(ta, tcount, M, sm, s);
+      zfwd(a, count, sm.maxS(), s);
     }
   }
   // part: kPartAll, kPartMain (main-array tiles) or kPartNyquist (Nyquist-plane tiles)
