@@ -1847,7 +1847,8 @@ __global__ void __launch_bounds__((PX * (N / EX)), 2)
 
 // P3 with the five spectra (n0..n3, Q) as accumulators in registers; the
 // species pencils stream through two register buffers (the loads of species
-// i + 1 are in flight while species i is transformed).  Any species count.
+// i + 1 are in flight while species i is transformed).  Any species count; where
+// the streamed kernel takes up to three or four (kXStream), those beyond.
 // Against the streamed kernel, which reads the weights once per output
 // instead of once per species but needs fewer elements per compute unit in
 // registers (three species): better in FP64 (128^3: 45 against 56 us; 192^3:
@@ -1862,15 +1863,16 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   constexpr int TX = N / EX;
   __shared__ cx<T> tw[N];
   __shared__ cx<T> xch[2 * PX * N];
-  // FP32 weights.  With at most three species: every species' weights for
-  // the first half of each thread's elements (and the column kx = N/2 of
-  // thread 0), evaluated while the first pencil loads are in flight; an
-  // element's other half is its mirror's.  With more species the first two
-  // regions serve as the two buffers of x_weights_shared, one species at a
-  // time.
+  // FP32 weights.  With at most three species (kPre: where such instances come
+  // here): every species' weights for the first half of each thread's elements
+  // (and the column kx = N/2 of thread 0), evaluated while the first pencil loads
+  // are in flight; an element's other half is its mirror's.  With more species
+  // the first two regions serve as the two buffers of x_weights_shared, one
+  // species at a time.
   constexpr int EH = EX / 2;
   constexpr int kRegion = EH * TX * PX;
-  __shared__ WPair wall[sizeof(T) == 4 ? 3 * kRegion + 3 * PX : 1];
+  constexpr bool kPre = sizeof(T) == 4 && !Geo<T, N>::kXStream;
+  __shared__ WPair wall[kPre ? 3 * kRegion + 3 * PX : sizeof(T) == 4 ? 2 * kRegion : 1];
   int tile;
   const EvalArgs& a = args[inst_of_part((N * (N / 2)) / PX, N / PX, part, tile)];
   if (!a.hs_on || a.S < min_s) return;  // uniform per block
@@ -1897,8 +1899,8 @@ __global__ void __launch_bounds__((PX * (N / EX)))
   // the first species' pencil is in flight while the twiddle table is built
 #pragma unroll
   for (int m = 0; m < EX; ++m) b0[m] = A.template ld<cx<T>>(xa.vo(m), m * xa.mstride);
-  const bool pre = sizeof(T) == 4 && S <= 3;  // uniform
-  if constexpr (sizeof(T) == 4) {
+  const bool pre = kPre && S <= 3;  // uniform
+  if constexpr (kPre) {
     if (pre) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
