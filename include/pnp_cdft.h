@@ -363,7 +363,8 @@ typedef struct {
  * request that fails (bad packing, overflow, ...) reports its own status and
  * does not affect the others.  Returns PNP_OK when the batch ran (check each
  * status).
- * More than 2048 requests of one size and precision: PNP_E_NOMEM.
+ * More than 2048 requests of one size and precision: PNP_E_NOMEM, also as the
+ * status of every request that was valid; none of them runs.
  */
 pnp_status pnp_batch_mu_ex(pnp_ctx ctx, int32_t count, pnp_request* reqs, void* stream);
 

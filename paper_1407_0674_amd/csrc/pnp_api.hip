@@ -102,7 +102,7 @@ const double kCoulombEvNm = kElementaryCharge / (4.0 * M_PI * kVacuumPermittivit
 
 constexpr size_t kAlign = 256;
 constexpr int kEnergyBlocks = 1024;  // workgroups of the pair-energy reduction
-inline size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
+constexpr size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 pnp_status fail(pnp_ctx c, pnp_status s, const std::string& m) {
   if (c) c->err = m;
@@ -364,14 +364,11 @@ void fill_eval_args(EvalArgs& e, const Derived& d, const pnp_species* sp, const 
   e.nreal = d.S;
 }
 
-// The device ring: the records of 2048 requests of one size and precision in a
-// batch, 2112 bytes each; and the most a call's sphere stencils take of it.
-constexpr size_t kRingBytes = (4u << 20) + (128u << 10), kStencilBytes = 2u << 20;
-
-// whether the argument records of `count` instances fit the ring
-bool records_fit(size_t count) {
-  return up(up(sizeof(TableArgs) * count) + sizeof(EvalArgs) * count) <= kRingBytes;
-}
+// The device ring: the records of kMaxGroup requests of one size and precision
+// in a batch (the header's limit); and the most a call's sphere stencils take of it.
+constexpr size_t kMaxGroup = 2048, kStencilBytes = 2u << 20;
+constexpr size_t kRingBytes = up(up(sizeof(TableArgs) * kMaxGroup) + sizeof(EvalArgs) * kMaxGroup);
+static_assert(kRingBytes >= 2 * kStencilBytes && kRingBytes <= (5u << 20), "ring: two sets of stencils, a little over 4 MiB");
 
 // Copy host bytes into the context's device ring (stream ordered).  The few
 // KB of a single call go as kernel parameters: a copy from pageable memory
@@ -749,6 +746,18 @@ void prepare_batch(pnp_ctx ctx, int count, pnp_request* reqs, std::vector<Layout
     }
     out.push_back(std::move(g));
   }
+}
+
+// PNP_E_NOMEM, also as the status of every valid request (none of them runs), if
+// the records of some group do not fit the ring.
+pnp_status check_groups(pnp_ctx ctx, const std::vector<Group>& groups, pnp_request* reqs) {
+  for (const Group& big : groups)
+    if (big.ids.size() > kMaxGroup) {
+      for (const Group& g : groups)
+        for (int r : g.ids) reqs[r].status = PNP_E_NOMEM;
+      return fail(ctx, PNP_E_NOMEM, "too many requests of one size for one batch");
+    }
+  return PNP_OK;
 }
 
 }  // namespace
@@ -1325,8 +1334,7 @@ pnp_status pnp_batch_mu_ex(pnp_ctx ctx, int32_t count, pnp_request* reqs, void* 
   std::vector<Layout> lay;
   std::vector<Group> groups;
   prepare_batch(ctx, count, reqs, lay, groups);
-  for (const Group& g : groups)
-    if (!records_fit(g.ids.size())) return fail(ctx, PNP_E_NOMEM, "too many requests of one size for one batch");
+  if (const pnp_status st = check_groups(ctx, groups, reqs); st != PNP_OK) return st;
   // Grid sizes below kSplitMinN leave most of the chip idle in their
   // launches: with two or more of them each runs on a branch stream of its
   // own, forked from the caller's stream and joined back before the status
@@ -1543,8 +1551,7 @@ pnp_status pnp_autotune(pnp_ctx ctx, int32_t count, pnp_request* reqs, int32_t r
   std::vector<Layout> lay;
   std::vector<Group> groups;
   prepare_batch(ctx, count, reqs, lay, groups);
-  for (const Group& g : groups)
-    if (!records_fit(g.ids.size())) return fail(ctx, PNP_E_NOMEM, "too many requests of one size for one batch");
+  if (const pnp_status st = check_groups(ctx, groups, reqs); st != PNP_OK) return st;
   // the pass timers are borrowed: keep the caller's accumulated figures
   const bool prof0 = ctx->prof;
   const uint32_t mask0 = ctx->prof_mask;
