@@ -42,6 +42,7 @@ struct pnp_ctx_s {
   double prof_ms[PNP_NUM_PASSES] = {0};
   int32_t prof_n[PNP_NUM_PASSES] = {0};
   bool capturing = false;  // a plan is being captured: no pass events
+  bool tuning = false;     // the autotuner is timing: the launches that untimed calls make
   // autotuned tile shapes: (precision, n, count class) -> narrow-pass mask
   std::map<uint64_t, uint32_t> tune;
   // autotuned or imported FFT schedules: (precision, n) -> secondary-pass mask
@@ -606,14 +607,15 @@ struct Split {
 };
 
 // The first z pass with, where `ta` is given, the radial tables of tcount
-// instances: in one launch, or in two where the passes are timed one by one.
+// instances: in one launch, or in two where the passes are timed one by one (but
+// for the autotuner, which has to time the launch that calls make).
 // Three species, a call: mixed 32^3 92 -> 87 us, 64^3 115 -> 109, 128^3 275 -> 269;
 // FP64 64^3 131 -> 127.
 void first_pass(pnp_ctx c, const OpsSel& op, const EvalArgs* ea, int count, const TableArgs* ta, int tcount, int M,
                 const SpeciesMix& sm, hipStream_t s) {
   PassTimer pt{c, s};
-  if (ta && !(c->prof && !c->capturing)) {
-    op.at(1)->zfwd_tables(ea, count, ta, tcount, M, sm, s);
+  if (ta && (!c->prof || c->capturing || c->tuning)) {
+    pt.begin(1); op.at(1)->zfwd_tables(ea, count, ta, tcount, M, sm, s); pt.end();
     return;
   }
   if (ta) {
@@ -1559,7 +1561,7 @@ pnp_status pnp_autotune(pnp_ctx ctx, int32_t count, pnp_request* reqs, int32_t r
   int32_t n0[PNP_NUM_PASSES];
   pnp_status st = pnp_profile_read(ctx, ms0, n0, PNP_NUM_PASSES, 1);
   if (st != PNP_OK) return st;
-  ctx->prof = true;
+  ctx->prof = ctx->tuning = true;
   ctx->prof_mask = ~0u;
   for (const Group& g : groups) {
     const int cnt = (int)g.ids.size();
@@ -1634,6 +1636,7 @@ pnp_status pnp_autotune(pnp_ctx ctx, int32_t count, pnp_request* reqs, int32_t r
     ctx->tune[tune_key(g.precision, g.n, count_class(cnt))] = tmask;
   }
   ctx->prof = prof0;
+  ctx->tuning = false;
   ctx->prof_mask = mask0;
   for (int p = 0; p < PNP_NUM_PASSES; ++p) { ctx->prof_ms[p] = ms0[p]; ctx->prof_n[p] = n0[p]; }
   if (st != PNP_OK) return st;
