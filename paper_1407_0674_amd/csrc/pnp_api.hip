@@ -204,7 +204,7 @@ Layout layout_of(int n, int S, int precision, bool hs, bool pairs, bool per_term
   // free-energy partial sums: one per derivative-pass workgroup (at most n^2),
   // kEnergyBlocks pairs from the pair-energy pass, and the four results
   L.energy = o; o = up(o + sizeof(double) * ((size_t)n * n + 2 * kEnergyBlocks + 4));
-  L.hs = o; if (precision == PNP_FP64) o = up(o + (size_t)L.M * 4 * S * ts);  // FP32 weights live in registers
+  L.hs = o; if (precision == PNP_FP64) o = up(o + (size_t)L.M * 2 * S * ts);  // FP32 weights live in registers
   L.pair = o; if (pairs) o = up(o + (size_t)L.M * prow * ts);
   L.pair2 = o; if (pairs && per_term) o = up(o + (size_t)L.M * prow * ts);
   L.A = o; o = up(o + (size_t)S * L.fstride * 2 * ts);

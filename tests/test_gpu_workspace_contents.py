@@ -82,3 +82,13 @@ def test_other_entries(n):
     finally:
         e._ws = {}
         e.close()
+
+
+# the bytes asked for are those of the arrays that the passes use
+@pytest.mark.parametrize("n,S", [(16, 1), (48, 8), (64, 5)])
+def test_size(ev, n, S):
+    prob, _ = P.many_species(8, S, 5400 + S, precision=FP64, terms=P.TERM_HS)
+    h, m = n // 2, 3 * (n // 2) ** 2 + 1
+    spectra = (2 * S + 10) * (n * n * h + n * n) * 16
+    need = 256 + (n * n + 2 * 1024 + 4) * 8 + m * S * 16 + spectra
+    assert need <= ev.workspace_bytes(prob.with_(n=n)) <= need + 8 * 256
