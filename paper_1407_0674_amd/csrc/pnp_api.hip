@@ -371,6 +371,14 @@ constexpr size_t kMaxGroup = 2048, kStencilBytes = 2u << 20;
 constexpr size_t kRingBytes = up(up(sizeof(TableArgs) * kMaxGroup) + sizeof(EvalArgs) * kMaxGroup);
 static_assert(kRingBytes >= 2 * kStencilBytes && kRingBytes <= (5u << 20), "ring: two sets of stencils, a little over 4 MiB");
 
+// Launch with the status of this launch alone: the thread's last error may be one
+// that another library's call left there.
+template <class... A>
+bool launch(void (*kernel)(A...), dim3 grid, dim3 block, hipStream_t s, A... a) {
+  void* args[] = {&a...};
+  return hipLaunchKernel((const void*)kernel, grid, block, args, 0, s) == hipSuccess;
+}
+
 // Copy host bytes into the context's device ring (stream ordered).  The few
 // KB of a single call go as kernel parameters: a copy from pageable memory
 // costs a staging copy, a blit and its gaps (about 12 us before the first
@@ -393,9 +401,10 @@ void* upload(pnp_ctx c, const void* src, size_t bytes, hipStream_t s) {
     const int words = (int)((n + 15) / 16);
     b.w[words - 1] = uint4{0, 0, 0, 0};
     std::memcpy(&b, (const char*)src + at, n);
-    hipLaunchKernelGGL(k_put, dim3(1), dim3(kPutBytes / 16), 0, s, b, (uint4*)((char*)dst + at), words);
+    uint4* to = (uint4*)((char*)dst + at);
+    if (!launch(k_put, dim3(1), dim3(kPutBytes / 16), s, b, to, words)) return nullptr;
   }
-  return hipPeekAtLastError() == hipSuccess ? dst : nullptr;
+  return dst;
 }
 
 // the table and evaluation records of a launch list in one copy (each copy
@@ -448,8 +457,8 @@ bool read_blocks(pnp_ctx c, const void* const* src, int count, uint32_t* words, 
       if (any < 0) continue;
       for (int i = 0; i < m; ++i)
         if (!g.src[i]) g.src[i] = g.src[any];
-      hipLaunchKernelGGL(k_gather_status, dim3(1), dim3(kGather), 0, s, g, (uint4*)c->pin_dev + k, m);
-      if (hipPeekAtLastError() != hipSuccess) return false;
+      uint4* to = (uint4*)c->pin_dev + k;
+      if (!launch(k_gather_status, dim3(1), dim3(kGather), s, g, to, m)) return false;
     }
     if (hipStreamSynchronize(s) != hipSuccess) return false;
     std::memcpy(words + 4 * (size_t)at, c->pin, 16 * (size_t)n);
