@@ -217,8 +217,9 @@ pnp_status pnp_cdft_mu_ex(pnp_ctx ctx, const pnp_grid* grid, int32_t S,
  *   - PNP_E_NOMEM when pnp_workspace_bytes() of the call exceeds 64 MiB
  *     (for example mixed precision up to 96^3 with S <= 4, FP64 up to 64^3
  *     with S <= 8; the aperiodic mode needs the doubled grid's workspace);
- *   - PNP_E_ARG on a stream that is capturing a graph (the argument records
- *     are copied from host memory at call time), and nothing is enqueued;
+ *   - PNP_E_ARG on a stream that is capturing a graph (a replay would write the
+ *     argument records into the context's ring again, over those of later
+ *     calls), and nothing is enqueued;
  *   - PNP_E_DEVICE when the array has no address on this device.
  * Every call on one GPU shares that GPU's array, whichever context, stream or
  * thread makes it: calls that overlap on one GPU race and give undefined
@@ -328,9 +329,9 @@ pnp_status pnp_weighted_densities(pnp_ctx ctx, const pnp_grid* grid, int32_t S,
  *   out        device, float64 [F][4][nx][ny][nz]: (I, I_x, I_y, I_z) per field
  * The stencil (at most a few hundred offsets per field for R / h <= 4) is
  * built on the host in double and copied to the context's ring on `stream`
- * from host memory that the call frees before it returns, so the call
- * cannot be recorded into a HIP graph: on a capturing stream it returns
- * PNP_E_ARG and enqueues nothing.  Errors: PNP_E_ARG,
+ * (where it is large, from host memory that the call frees before it
+ * returns), so the call cannot be recorded into a HIP graph: on a capturing
+ * stream it returns PNP_E_ARG and enqueues nothing.  Errors: PNP_E_ARG,
  * PNP_E_UNSUPPORTED_SIZE, PNP_E_DEVICE.
  */
 pnp_status pnp_sphere_quadrature(pnp_ctx ctx, const pnp_grid* grid, int32_t F, const double* f,

@@ -1089,8 +1089,8 @@ pnp_status pnp_cdft_mu_ex_noalloc(pnp_ctx ctx, const pnp_grid* g, int32_t S, con
     return fail(ctx, PNP_E_NOMEM, "this evaluation needs " + std::to_string(need) + " bytes of scratch; the static "
                                   "scratch array holds " + std::to_string(kScratchBytes));
   if (hipSetDevice(ctx->device) != hipSuccess) return device_check(ctx, "set device");
-  // argument records are copied from host memory at call time: a captured
-  // copy would read them again at every replay
+  // the argument records lie in the context's ring: a captured call would write
+  // them there again at every replay, over those of later calls
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) return device_check(ctx, "capture query");
   if (capture != hipStreamCaptureStatusNone)

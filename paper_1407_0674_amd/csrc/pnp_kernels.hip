@@ -1701,9 +1701,13 @@ struct XAddr {
 // former layout: 512 threads, two exchange buffers and 114 KB of LDS at 256^3)
 // its loads, LDS exchanges and arithmetic took turns at the barriers, at
 // 46 % (forward) and 40 % (back) of 8 TB/s.  Hence
-//  * many elements per thread (16 in FP32: two radix-16 stages and one
-//    exchange at 256^3), so that a group is 256 threads of at most 256
-//    registers;
+//  * many elements per thread, so that a group fits half a compute unit's
+//    registers: in FP32 16 (256 threads of at most 256 registers at 256^3, two
+//    radix-16 stages and one exchange) or, in the secondary schedule, 8 (512
+//    threads of at most 128, three stages).  The faster one is the default by
+//    size (mixed, three species, forward and back: 256^3 181 and 267 us with 16,
+//    168 and 246 with 8; 128^3 32 and 47, 30 and 43; 192^3 with 12 and 6 91 and
+//    130, 102 and 149);
 //  * one exchange buffer, of real parts only where it has to be half as large
 //    (SPLIT), beside the weights: at most 80 KB per group;
 //  * the weights (j0, w3) of all species at the N / 2 + 1 distinct |s_x| of
