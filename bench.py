@@ -39,36 +39,49 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+VECTOR_PEAK_TFLOPS = 78.6  # FP64, and FP32 without packed instructions
 F = 10  # weighted-density fields
 
 
-FV = 8  # fields between the x passes and the y passes: each vector density
-        # travels as two fields there ([x] and Q_b or the khat . F partial sum)
+FV = 8  # of them between the x passes and the y passes where each vector
+        # density travels as two fields ([x] and Q_b or the khat . F partial sum)
 
 
-def pass_bytes_per_point(S: int, precision: int, slot: bool = True):
-    """Algorithmic HBM bytes per grid point of each pass: every pass reads its
-    inputs once and writes its outputs once; a half spectrum of one field
-    holds n^3/2 complex values (c bytes per grid point and field, c = 4 in
-    the mixed path, 8 in FP64); densities in and mu / exp(-mu) out are FP64.
-    The ten FMT fields are 8 stored fields on either side of the y/z passes
-    (60 S + 28.8 F bytes per point in the mixed path; 60 S + 32 F with all
-    ten fields in every pass).  This is the yardstick; the passes now move one
-    field less each way, 8 c bytes per point in all (the second vector density
-    is formed from n3's spectrum)."""
+def _pass_table(S, precision, slot, fx, fz):
+    # every pass reads its inputs once and writes its outputs once; a half
+    # spectrum of one field holds n^3/2 complex values (c bytes per grid point
+    # and field, c = 4 in the mixed path, 8 in FP64); densities in and
+    # mu / exp(-mu) out are FP64; fx and fz: FMT fields stored on the x and on
+    # the z side of the y passes
     c = 4 if precision == 1 else 8
     out = 16 if slot else 8
     return {
         "z_fwd_rho": (8 + c) * S,
         "y_fwd_rho": 2 * c * S,
-        "x_fwd_weights": c * S + c * FV,
-        "y_inv_n": c * FV + c * F,
-        "z_deriv": 2 * c * F,
-        "y_fwd_dphi": c * F + c * FV,
-        "x_back_pairs": c * FV + 2 * c * S,
+        "x_fwd_weights": c * S + c * fx,
+        "y_inv_n": c * fx + c * fz,
+        "z_deriv": 2 * c * fz,
+        "y_fwd_dphi": c * fz + c * fx,
+        "x_back_pairs": c * fx + 2 * c * S,
         "y_inv_mu": 2 * c * S,
         "z_inv_final": c * S + out * S,
     }
+
+
+def moved_bytes_per_point(S: int, precision: int, slot: bool = True):
+    """HBM bytes per grid point that each pass moves (up to four species), which
+    every rate and fraction below divides by: nine FMT fields on the z side of
+    the y passes and seven on the x side (the second vector density is formed
+    from n3's spectrum), 60 S + 256 bytes in the mixed path."""
+    return _pass_table(S, precision, slot, 7, 9)
+
+
+def pass_bytes_per_point(S: int, precision: int, slot: bool = True):
+    """The same with all ten fields stored on the z side and eight on the x side
+    (60 S + 28.8 F bytes in the mixed path), as earlier kernels moved them: a
+    fixed yardstick, 8 c bytes more than the passes move, kept to compare runs
+    over time."""
+    return _pass_table(S, precision, slot, FV, F)
 
 
 def all_fields_bytes_per_point(S: int, precision: int):
@@ -297,7 +310,7 @@ def bench_batch(ev, steps, warmup):
     slots = [torch.empty_like(r) for r in rhos]
     wss = [torch.empty(ev.workspace_bytes(p), dtype=torch.uint8, device="cuda:0") for p in probs]
     pts = sum(p.n ** 3 * p.S for p in probs)
-    bytes_model = sum(sum(pass_bytes_per_point(p.S, p.precision).values()) * p.n ** 3 for p in probs)
+    bytes_model = sum(sum(moved_bytes_per_point(p.S, p.precision).values()) * p.n ** 3 for p in probs)
 
     probs64 = [p.with_(precision=0) for p in probs]
     wss64 = [torch.empty(ev.workspace_bytes(p), dtype=torch.uint8, device="cuda:0") for p in probs64]
@@ -370,7 +383,7 @@ def bench_batch(ev, steps, warmup):
         "dtype": "f32 FFTs/weights/products + f64 ln(1-n3), 1/(1-n3)^k, constants, output", "data": "synthetic (seeded)",
         "config": {"workload": "64 instances, n in {32,48,64,96,128}, S in {2,3,4}, T 250-350 K, HS+EC+SW, mixed",
                    "sizes": hist, "grid_pt_species": pts},
-        "hbm": {"model_bytes_per_step": bytes_model, "GBps": bytes_model / 1e9 / (ms / 1e3),
+        "hbm": {"moved_bytes_per_step": bytes_model, "GBps": bytes_model / 1e9 / (ms / 1e3),
                 "pct_peak": 100.0 * bytes_model / 1e9 / (ms / 1e3) / HBM_PEAK_GBS,
                 "note": "instances up to 128^3 partly stay in the 256 MB Infinity Cache between passes"},
         "timing": "one captured HIP graph (pnp_plan) replayed per step, statuses read after the last; "
@@ -457,13 +470,50 @@ def sphere_stencil_size(r, k, cubic=False):
     return len(seen)
 
 
+def sphere_issued_flops(r, k, outputs, cubic=False):
+    """Floating-point operations per grid point that the kernel issues for one
+    sphere (radius r in grid units, k-by-k rule of even order): the merged offsets
+    lie in columns along x over the mirror images of (|dy|, |dz|), whose values are
+    folded once per plane of a thread's column of `outputs` points and its reach (7
+    operations for four images, 2 for two); each offset dx of a column then takes
+    two multiply-adds, one more for each of dy and dz that is not zero."""
+    import numpy as np
+    x, w = np.polynomial.legendre.leggauss(k)
+    cells = {}
+    for i in range(k):
+        th = 2.0 * math.pi * i / k
+        for j in range(k):
+            ph = 0.5 * math.pi * (x[j] + 1.0)
+            nd = np.array([math.cos(th) * math.sin(ph), math.sin(th) * math.sin(ph), math.cos(ph)])
+            b = np.floor(r * nd)
+            t = r * nd - b
+            offs = (-1, 0, 1, 2) if cubic else (0, 1)
+            ax = [{c: np.prod([(v - o) / (c - o) for o in offs if o != c]) for c in offs} for v in t]
+            for c in itertools.product(offs, repeat=3):
+                key = tuple(int(v) for v in b + np.array(c))
+                tw = math.sin(ph) * w[j] * ax[0][c[0]] * ax[1][c[1]] * ax[2][c[2]]
+                cells[key] = cells.get(key, 0.0) + tw * np.array([1.0, *nd])
+    tol = 1e-14 * max(np.max(np.abs(v)) for v in cells.values())  # of a node touched by rounding alone
+    columns = {}
+    for (dx, dy, dz), v in cells.items():
+        if np.max(np.abs(v)) > tol:
+            columns.setdefault((abs(dy), abs(dz)), set()).add(dx)
+    total = 0.0
+    for (dy, dz), dxs in columns.items():
+        fold = 7 if dy and dz else 2 if dy or dz else 0
+        planes = outputs + 2 * max(abs(d) for d in dxs)
+        total += fold * planes / outputs + len(dxs) * (4 + 2 * (dy > 0) + 2 * (dz > 0))
+    return total
+
+
 def bench_sphere(ev, steps, warmup, no_cpu):
     """Sec. 3.5 sphere quadrature (pnp_sphere_quadrature) on the benchmark's
     256^3 densities with the three species' radii d/2 (1.5, 3 and 4 grid
     spacings), order 8 (64 nodes per sphere), mixed and FP64.  One step = one
     call for the three fields (scalar and vector integrals).  The kernel is
-    bound by its FMAs (four per stencil offset per output, one LDS read each):
-    roofline against the vector ALU peak.  Also: the oracle's throughput on a
+    bound by the vector ALU (folding of mirror columns and multiply-adds):
+    roofline against the vector ALU peak without packed FP32 instructions, which
+    the build leaves out, on the operations that the folded kernel issues.  Also: the oracle's throughput on a
     64^3 sample, and the accuracy of the spectral delta-shell weights and of
     the quadrature (orders 4, 8, 16) on a Gaussian bump against its exact
     sphere integrals, both measured here on the GPU."""
@@ -478,7 +528,10 @@ def bench_sphere(ev, steps, warmup, no_cpu):
     out = torch.empty((prob.S, 4) + rho.shape[1:], dtype=torch.float64, device="cuda:0")
     n3 = prob.n ** 3
     entries = [sphere_stencil_size(R / prob.h, k) for R in radii]
-    flops = 8.0 * n3 * sum(entries)
+    flops = 8.0 * n3 * sum(entries)  # of each offset by itself: a yardstick
+    # outputs per thread along x: 8 (FP32, reach 4 and 5), 4 (FP64, reach 4)
+    issued = {name: n3 * sum(sphere_issued_flops(R / prob.h, k, tx, cub) for R in radii)
+              for name, tx, cub in (("mixed", 8, False), ("fp64", 4, False), ("mixed_cubic", 8, True))}
     hbm = n3 * prob.S * (8 + 4 * 8)
     entries_cubic = [sphere_stencil_size(R / prob.h, k, cubic=True) for R in radii]
     flops_cubic = 8.0 * n3 * sum(entries_cubic)
@@ -496,7 +549,8 @@ def bench_sphere(ev, steps, warmup, no_cpu):
         e1.record()
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / steps
-        res[name] = {"ms": ms, "tflops": fo / (ms / 1e3) / 1e12, "hbm_GBps": hbm / (ms / 1e3) / 1e9}
+        res[name] = {"ms": ms, "issued_tflops": issued[name] / (ms / 1e3) / 1e12,
+                     "yardstick_tflops": fo / (ms / 1e3) / 1e12, "hbm_GBps": hbm / (ms / 1e3) / 1e9}
     ev.sphere_quadrature(rd, radii, prob.h, k, precision=MIXED, out=out)   # waits: errors surface here
     del out, rd
     torch.cuda.empty_cache()
@@ -547,13 +601,15 @@ def bench_sphere(ev, steps, warmup, no_cpu):
         "config": {"workload": "sphere quadrature (Sec. 3.5) of the channel electrolyte's 256^3 densities, S=3, "
                                "R = 1.5, 3, 4 h, order 8 (64 nodes), scalar + vector integrals, mixed"},
         "stencil_offsets": entries,
-        # the flops of each stencil offset on its own: the kernel folds mirror
-        # offsets first and issues fewer, so this can pass the non-packed 78.6
-        "roofline": {"bound": "alu", "achieved": res["mixed"]["tflops"], "peak": 157.3, "unit": "TFLOP/s",
-                     "frac": res["mixed"]["tflops"] / 157.3, "traffic": traffic_from_profile("sphere_quad", 1)},
-        "fp64": dict(res["fp64"], frac_of_78_6=res["fp64"]["tflops"] / 78.6),
+        # the yardstick counts four multiply-adds for each offset by itself, more
+        # than the folded kernel issues: to compare runs over time only
+        "roofline": {"bound": "alu", "achieved": res["mixed"]["issued_tflops"], "peak": VECTOR_PEAK_TFLOPS,
+                     "unit": "TFLOP/s", "frac": res["mixed"]["issued_tflops"] / VECTOR_PEAK_TFLOPS,
+                     "yardstick_tflops": res["mixed"]["yardstick_tflops"],
+                     "traffic": traffic_from_profile("sphere_quad", 1)},
+        "fp64": dict(res["fp64"], frac=res["fp64"]["issued_tflops"] / VECTOR_PEAK_TFLOPS),
         "mixed_cubic": dict(res["mixed_cubic"], stencil_offsets=entries_cubic,
-                            frac_of_157_3=res["mixed_cubic"]["tflops"] / 157.3),
+                            frac=res["mixed_cubic"]["issued_tflops"] / VECTOR_PEAK_TFLOPS),
         "hbm_GBps_effective": res["mixed"]["hbm_GBps"],
         "accuracy_vs_exact_gaussian_bump_64": acc,
         "cpu_baseline": cpu,
@@ -718,7 +774,8 @@ def main():
     # table; its slowest pass is the dominant kernel), then the timed region
     # with events around that pass only
     ev.mu_ex(prob, rho_d, out=out, slot=slot)
-    bpp = pass_bytes_per_point(S, prec)
+    bpp = moved_bytes_per_point(S, prec)
+    yardstick = sum(pass_bytes_per_point(S, prec).values()) * n3
     for _ in range(max(1, args.warmup)):
         ev.mu_ex(prob, rho_d, out=out, slot=slot)
     ev.profile(True)
@@ -744,7 +801,7 @@ def main():
         entry = {"avg_ms": avg, "launches": cnt}
         if name in bpp:
             gb = bpp[name] * n3 / 1e9
-            entry["alg_GB"] = gb
+            entry["moved_GB"] = gb
             entry["GBps"] = gb / (avg / 1e3)
             entry["frac"] = entry["GBps"] / HBM_PEAK_GBS
             entry["frac_all_fields_model"] = sbp[name] * n3 / 1e9 / (avg / 1e3) / HBM_PEAK_GBS
@@ -820,16 +877,18 @@ def main():
         "data": "synthetic (seeded)",
         "config": {"workload": desc, "grid": n, "species": S, "global_batch": 1,
                    "precision": "mixed" if prec == 1 else "fp64"},
-        "hbm": {"model_bytes_per_step": total_bytes,
-                "moved_bytes_per_step": total_bytes - 8 * (4 if prec == 1 else 8) * n3,
+        "hbm": {"moved_bytes_per_step": total_bytes,
                 "GBps": total_bytes / 1e9 / (ms / 1e3),
                 "pct_peak": 100.0 * total_bytes / 1e9 / (ms / 1e3) / HBM_PEAK_GBS,
                 "kernel_ms_per_step": kernel_ms, "copy_kernel_GBps": copy["GBps"],
-                "pct_of_copy": 100.0 * total_bytes / 1e9 / (ms / 1e3) / copy["GBps"]},
+                "pct_of_copy": 100.0 * total_bytes / 1e9 / (ms / 1e3) / copy["GBps"],
+                # more bytes than the passes move: to compare runs over time only
+                "yardstick_bytes_per_step": yardstick,
+                "yardstick_pct_peak": 100.0 * yardstick / 1e9 / (ms / 1e3) / HBM_PEAK_GBS},
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": dom_gbps, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": dom_gbps / HBM_PEAK_GBS,
                      "traffic": traffic_from_profile(dom, 1),
-                     "alg_bytes_per_launch": bpp[dom] * n3, "avg_ms": dom_ms, "launches": dom_cnt,
+                     "moved_bytes_per_launch": bpp[dom] * n3, "avg_ms": dom_ms, "launches": dom_cnt,
                      "frac_all_fields_model": sbp[dom] * n3 / 1e9 / (dom_ms / 1e3) / HBM_PEAK_GBS,
                      "chosen_by": "largest average time in this run's per-pass table",
                      "lowest_frac_pass": {"kernel": lowest, "frac": per_pass[lowest]["frac"]},
