@@ -470,13 +470,15 @@ def sphere_stencil_size(r, k, cubic=False):
     return len(seen)
 
 
-def sphere_issued_flops(r, k, outputs, cubic=False):
+def sphere_issued_flops(r, k, outputs, cubic=False, fp32=True):
     """Floating-point operations per grid point that the kernel issues for one
     sphere (radius r in grid units, k-by-k rule of even order): the merged offsets
     lie in columns along x over the mirror images of (|dy|, |dz|), whose values are
     folded once per plane of a thread's column of `outputs` points and its reach (7
-    operations for four images, 2 for two); each offset dx of a column then takes
-    two multiply-adds, one more for each of dy and dz that is not zero."""
+    operations for four images, 2 for two, 3 more for the rounding error that FP32
+    keeps); +-dx of a column then take an addition and a multiply-add for each
+    integral that has a weight there (two additions more for the x integral with
+    the rounding errors), dx = 0 the multiply-adds."""
     import numpy as np
     x, w = np.polynomial.legendre.leggauss(k)
     cells = {}
@@ -500,9 +502,12 @@ def sphere_issued_flops(r, k, outputs, cubic=False):
             columns.setdefault((abs(dy), abs(dz)), set()).add(dx)
     total = 0.0
     for (dy, dz), dxs in columns.items():
-        fold = 7 if dy and dz else 2 if dy or dz else 0
+        err = fp32 and (dy or dz)
+        fold = (7 if dy and dz else 2 if dy or dz else 0) + (3 if err else 0)
         planes = outputs + 2 * max(abs(d) for d in dxs)
-        total += fold * planes / outputs + len(dxs) * (4 + 2 * (dy > 0) + 2 * (dz > 0))
+        odd = (dy > 0) + (dz > 0)  # of the y and z integrals
+        total += fold * planes / outputs + (0 in dxs) * 2 * (1 + odd)
+        total += sum(d > 0 for d in dxs) * (3 * (2 + odd) + (2 if err else 0))
     return total
 
 
@@ -530,7 +535,7 @@ def bench_sphere(ev, steps, warmup, no_cpu):
     entries = [sphere_stencil_size(R / prob.h, k) for R in radii]
     flops = 8.0 * n3 * sum(entries)  # of each offset by itself: a yardstick
     # outputs per thread along x: 8 (FP32, reach 4 and 5), 4 (FP64, reach 4)
-    issued = {name: n3 * sum(sphere_issued_flops(R / prob.h, k, tx, cub) for R in radii)
+    issued = {name: n3 * sum(sphere_issued_flops(R / prob.h, k, tx, cub, name != "fp64") for R in radii)
               for name, tx, cub in (("mixed", 8, False), ("fp64", 4, False), ("mixed_cubic", 8, True))}
     hbm = n3 * prob.S * (8 + 4 * 8)
     entries_cubic = [sphere_stencil_size(R / prob.h, k, cubic=True) for R in radii]

@@ -23,11 +23,12 @@
 // It is bound by the vector ALU (three fields at 192^3 move 850 MB, 130 us at
 // 6.6 TB/s).  The rule's symmetry in y and z lets a thread fold the four mirror
 // columns of a (|dy|, |dz|) into three sums once per tile plane, and all the
-// offsets along x of those columns share them: 4 multiply-adds and a share of
-// the folding per four offsets, against 12 operations and four LDS reads when
-// each offset was paired with its antipode alone.  192^3, order 8, mixed,
-// R = 1.4, 2.6 and 3.9 h: 82, 140 and 192 us with pairs, 73, 92 and 134 with
-// columns (FP64 88, 179 and 289; 81, 132 and 218).
+// offsets along x of those columns share them; a rule of even order is symmetric in
+// x too, so the eight offsets (+-dx, +-dy, +-dz) then take four multiply-adds, four
+// to six additions and a share of the folding, against 24 operations and eight LDS
+// reads when each offset was paired with its antipode alone.  192^3, order 8, mixed,
+// R = 1.4, 2.6 and 3.9 h: 102, 164 and 232 us with pairs, 65, 91 and 123 with columns
+// (FP64 120, 237 and 418; 72, 123 and 218).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -50,8 +51,8 @@ constexpr size_t kQuadMaxLds = 163840;   // the most LDS one workgroup can hold 
 // ds = a + b - c - d and the z weight sd = a - b + c - d.
 struct QuadColumn {
   int32_t near_lds, far_lds;  // tile positions of (dy, dz) and (dy, -dz) relative to the output's
-  uint32_t dx;                // bit k: a weight at dx = k; bit 16 + k: at dx = -k
-  int32_t w;                  // first weight, in units of four, of the offsets in the order 0, 1, -1, 2, -2, ..
+  uint32_t dx;                // bit k: a weight at dx = k (even orders: at +-k); bit 16 + k: at dx = -k (odd ones)
+  int32_t w;                  // first weight, in units of four, of the bits set in the order 0, 1, -1, 2, -2, ..
 };
 
 // Kinds of columns: bit 0 dy = 0 (two images, ds = 0), bit 1 dz = 0 (sd = 0).
@@ -102,39 +103,61 @@ constexpr int quad_split(int H, size_t elem) {
   return tx < 2 ? 1 : 2;
 }
 
+// The rounding error of s = a + b (exact where |a| >= |b|, else to the rounding of
+// s - a); finite where s is not, so that an infinite value stays one.
+__device__ __forceinline__ float sum_error(float a, float b, float s) {
+  return __builtin_amdgcn_fmed3f(b - (s - a), -__FLT_MAX__, __FLT_MAX__);
+}
+
 // Sum the columns [c0, c1) of one kind into a thread's TX outputs.  A column's
 // values are read and folded once per tile plane, at most TX + 2H of them, and
 // serve all its dx: level k reads the two planes that dx = +-k adds.
-// EVEN: a rule of even order, whose columns have both of +-k or neither.  Rules of
-// odd order are not even in x: a point that only the mirror offset touches has no
-// part in the sum, not even times zero (it may be infinite or NaN).  Testing each
-// offset cost even rules 2 to 5 % where the reach is 4 or more, hence two forms.
+// EVEN: a rule of even order, which is even in x too: +-k share their weights, the
+// x weight up to sign and times the difference of the two values.  Rules of odd
+// order have no such symmetry: a point that only the mirror offset touches has no
+// part in the sum, not even times zero (it may be infinite or NaN).
+//
+// Rounding: the vector integrals are small differences of large sums.  The odd
+// combinations ds and sd are formed from differences of single values, exact for
+// like ones, and FP32 keeps the rounding error es of each ss for the x integral.
+// Error against the same rule with its antipodal offsets in pairs, whose
+// differences are of single values throughout (geometric mean over radii of 0.8 to
+// 5 h and orders 4 to 20; scalar, x, y, z): FP32 0.76, 0.83, 0.81, 0.86, FP64 0.90,
+// 0.69, 0.81, 0.87.  Without es the FP32 x integral is at 1.14 (192^3, R = 3.9 h
+// 123 us with, 114 without), with each x offset times its own weight at 1.31, FP64
+// at 1.99 and up to 10.
 template <typename T, int H, int TX, int KIND, bool EVEN>
 __device__ __forceinline__ void quad_columns(const QuadColumn* columns, int c0, int c1, const T* weights, const T* col,
                                              T (&acc)[TX][4]) {
   constexpr int PLANE = (kQuadTY + 2 * H) * (kQuadTZ + 2 * H);
   constexpr bool Y = !(KIND & 1), Z = !(KIND & 2);
+  constexpr bool ERR = EVEN && sizeof(T) == 4 && (Y || Z);
 #pragma unroll 1
   for (int e = c0; e < c1; ++e) {
     const QuadColumn q = columns[e];
     const T* w = weights + 4 * (size_t)q.w;
     const uint32_t levels = (q.dx | q.dx >> 16) & 0xffffu;
-    T ss[TX + 2 * H], ds[TX + 2 * H], sd[TX + 2 * H];
+    T ss[TX + 2 * H], ds[TX + 2 * H], sd[TX + 2 * H], es[TX + 2 * H];
     auto read = [&](int i) {  // plane i - H relative to the first output's
       const T* p = col + (i - H) * PLANE;
       if constexpr (Y && Z) {
         const T va = p[q.near_lds], vb = p[q.far_lds], vc = p[-q.far_lds], vd = p[-q.near_lds];
-        const T ab = va + vb, cd = vc + vd;
-        ss[i] = ab + cd;
-        ds[i] = ab - cd;
-        sd[i] = (va - vb) + (vc - vd);
+        // differences before sums: those of like values are exact
+        const T ad = va - vd, bc = vb - vc;
+        const T p1 = va + vd, p2 = vb + vc;
+        ss[i] = p1 + p2;
+        if constexpr (ERR) es[i] = sum_error(p1, p2, ss[i]);
+        ds[i] = ad + bc;
+        sd[i] = ad - bc;
       } else if constexpr (Y) {
         const T va = p[q.near_lds], vd = p[-q.near_lds];
         ss[i] = va + vd;
+        if constexpr (ERR) es[i] = sum_error(va, vd, ss[i]);
         ds[i] = va - vd;
       } else if constexpr (Z) {
         const T va = p[q.near_lds], vd = p[-q.near_lds];
         ss[i] = va + vd;
+        if constexpr (ERR) es[i] = sum_error(va, vd, ss[i]);
         sd[i] = va - vd;
       } else {
         ss[i] = p[0];
@@ -152,7 +175,16 @@ __device__ __forceinline__ void quad_columns(const QuadColumn* columns, int c0, 
 #pragma unroll
     for (int i = H; i < H + TX; ++i) read(i);
     if (q.dx & 1) {
-      add(0, w);
+      if constexpr (EVEN) {
+#pragma unroll
+        for (int x = 0; x < TX; ++x) {
+          acc[x][0] += w[0] * ss[x + H];
+          if constexpr (Y) acc[x][2] += w[2] * ds[x + H];
+          if constexpr (Z) acc[x][3] += w[3] * sd[x + H];
+        }
+      } else {
+        add(0, w);
+      }
       w += 4;
     }
 #pragma unroll
@@ -161,10 +193,17 @@ __device__ __forceinline__ void quad_columns(const QuadColumn* columns, int c0, 
       read(H - k);
       read(H + TX - 1 + k);
       if constexpr (EVEN) {
-        if (levels >> k & 1) {
-          add(k, w);
-          add(-k, w + 4);
-          w += 8;
+        if (q.dx >> k & 1) {
+#pragma unroll
+          for (int x = 0; x < TX; ++x) {
+            const int u = x + H + k, d = x + H - k;
+            acc[x][0] += w[0] * (ss[u] + ss[d]);
+            if constexpr (ERR) acc[x][1] += w[1] * ((ss[u] - ss[d]) + (es[u] - es[d]));
+            else acc[x][1] += w[1] * (ss[u] - ss[d]);
+            if constexpr (Y) acc[x][2] += w[2] * (ds[u] + ds[d]);
+            if constexpr (Z) acc[x][3] += w[3] * (sd[u] + sd[d]);
+          }
+          w += 4;
         }
       } else {
         if (q.dx >> k & 1) {
@@ -387,9 +426,9 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
     const int ox = (int)(cell / ((size_t)side * side)), oy = (int)(cell / side % side), oz = (int)(cell % side);
     s.span = std::max(s.span, std::max(std::abs(ox - Hc), std::max(std::abs(oy - Hc), std::abs(oz - Hc))));
   }
-  // The merged weights are even in y and z (odd for that axis' vector weight)
-  // in exact arithmetic; the node coordinates differ in the last bits, and the
-  // mean over the images is taken.
+  // The merged weights are even in y and z, and for even orders in x (odd for that
+  // axis' vector weight), in exact arithmetic; the node coordinates differ in the
+  // last bits, and the mean over the images is taken.
   for (int dy = 0; dy <= Hc; ++dy)
     for (int dz = 0; dz <= Hc; ++dz) {
       QuadStencil::Column col;
@@ -399,30 +438,31 @@ inline QuadStencil build_quad_stencil(double r, double R, int k, bool cubic) {
       // the mean weights at dx; false if none is above tol
       auto weights = [&](int dx, double* m) {
         for (int q = 0; q < 4; ++q) m[q] = 0.0;
-        for (int iy = 0; iy < 2; ++iy)
-          for (int iz = 0; iz < 2; ++iz) {
-            const int oy = Hc + (iy ? -dy : dy), oz = Hc + (iz ? -dz : dz);
-            const double* v = &acc[(((size_t)(dx + Hc) * side + oy) * side + oz) * 4];
-            m[0] += 0.25 * v[0];
-            m[1] += 0.25 * v[1];
-            m[2] += (iy ? -0.25 : 0.25) * v[2];
-            m[3] += (iz ? -0.25 : 0.25) * v[3];
-          }
+        const int nx = even ? 2 : 1;
+        const double part = 0.25 / nx;
+        for (int ix = 0; ix < nx; ++ix)
+          for (int iy = 0; iy < 2; ++iy)
+            for (int iz = 0; iz < 2; ++iz) {
+              const int ox = Hc + (ix ? -dx : dx), oy = Hc + (iy ? -dy : dy), oz = Hc + (iz ? -dz : dz);
+              const double* v = &acc[(((size_t)ox * side + oy) * side + oz) * 4];
+              m[0] += part * v[0];
+              m[1] += (ix ? -part : part) * v[1];
+              m[2] += (iy ? -part : part) * v[2];
+              m[3] += (iz ? -part : part) * v[3];
+            }
         double big = 0.0;
         for (int q = 0; q < 4; ++q) big = std::max(big, std::fabs(m[q]));
         return big > tol;
       };
       for (int k = 0; k <= Hc; ++k) {
-        double m[8];
-        bool up = weights(k, m), down = k > 0 && weights(-k, m + 4);
-        if (even && k > 0) up = down = up || down;  // alike but for rounding
-        if (up) {
+        double m[4];
+        if (weights(k, m)) {
           col.c.insert(col.c.end(), m, m + 4);
           col.up |= 1u << k;
           hx = k;
         }
-        if (down) {
-          col.c.insert(col.c.end(), m + 4, m + 8);
+        if (!even && k > 0 && weights(-k, m)) {
+          col.c.insert(col.c.end(), m, m + 4);
           col.down |= 1u << k;
           hx = k;
         }

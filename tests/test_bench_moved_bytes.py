@@ -38,14 +38,15 @@ def test_kernels_store_as_many_fields():
 def test_sphere_operations_of_a_small_rule():
     # r = 1/2, order 2: four nodes at (+-a, 0, +-b) (theta 0 and pi), a = sin, b = |cos| of
     # phi = pi (1 - 1/sqrt 3) / 2, half a cell off the axes in x and z at most: offsets
-    # -1, 0, 1 in x and z, 0 in y; columns dz = 0 and |dz| = 1 with three offsets each
-    want = 3 * 4 + 3 * 6 + 2 * (8 + 2) / 8
-    assert bench.sphere_issued_flops(0.5, 2, 8) == pytest.approx(want)
+    # -1, 0, 1 in x and z, 0 in y; columns dz = 0 and |dz| = 1 with dx = 0 and +-1 each
+    fold = (8 + 2) / 8  # planes read per output
+    assert bench.sphere_issued_flops(0.5, 2, 8, fp32=False) == pytest.approx((2 + 6) + (4 + 9) + 2 * fold)
+    assert bench.sphere_issued_flops(0.5, 2, 8) == pytest.approx((2 + 6) + (4 + 11) + 5 * fold)
 
 
 @pytest.mark.parametrize("r,k,cubic", [(1.5, 8, False), (3.0, 8, False), (2.2, 6, True)])
 def test_sphere_operations_below_the_unfolded_count(r, k, cubic):
     unfolded = 8.0 * bench.sphere_stencil_size(r, k, cubic)
-    assert 0.25 * unfolded < bench.sphere_issued_flops(r, k, 8, cubic) < unfolded
+    assert 0.2 * unfolded < bench.sphere_issued_flops(r, k, 8, cubic) < unfolded
     # thinner columns share the folding among fewer outputs
     assert bench.sphere_issued_flops(r, k, 2, cubic) > bench.sphere_issued_flops(r, k, 8, cubic)
